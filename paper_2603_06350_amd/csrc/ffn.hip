@@ -35,8 +35,7 @@
 // XCDs) walks a contiguous range of the tile list with the m-tiles of one weight
 // panel adjacent: CUs that share an L2 share weight tiles.
 //
-// Generic kernel (fp32, or bf16 shapes whose d or F is not a multiple of 64): a plain
-// LDS-tiled FMA GEMM with fp32 accumulation.
+// Generic kernel (fp32): a plain LDS-tiled FMA GEMM with fp32 accumulation.
 #include <type_traits>
 
 #include "moe_internal.h"
@@ -276,6 +275,21 @@ constexpr int BROWS = 256;      // weight rows per block tile
 constexpr int BK = BK_ELEMS;    // K elements per stage
 constexpr int ROWB = BK * 2;    // bytes per tile row in LDS (eight 16-byte chunks)
 
+// Shapes whose K or N is not a multiple of 64 (RAGGED kernels; both are multiples of 8, so 16-byte
+// chunks are valid or invalid as a whole).  The last K stage of a tile holds K % 64 valid elements per row:
+// a lane whose chunk lies past them sets the top bit of its offset, which puts the request beyond the
+// 2 GiB that the buffer resource admits, and the bounds check of the load unit fills the chunk's LDS
+// bytes with zeros for both operands.  Weight rows past N do the same in the even tiles (their row
+// groups share one per-lane offset); the ring tiles re-read the last valid row.  The alternative
+// these shapes had before, a 64 x 64 fp32-FMA kernel, ran at 50 TFLOP/s (T = 1501, d = 1048, E = 12,
+// k = 3, F = 1864: 1.10 ms per layer, now 0.133).
+constexpr uint32_t PAST_END = 0x80000000u;
+// what a lane that loads chunk `chunk` (0 .. 7) of its rows adds to the offset in the last stage
+__device__ __forceinline__ uint32_t ragged_tail(int K, int chunk) {
+  const int valid = (K & (BK - 1)) >> 3;          // whole chunks in the last stage (0: all eight)
+  return valid != 0 && chunk >= valid ? PAST_END : 0u;
+}
+
 // Chunk swizzle of a 128-byte tile row: XOR with the row so that 16 consecutive rows x one
 // logical chunk cover a 256-byte bank window exactly once.
 __device__ __forceinline__ int swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
@@ -404,7 +418,7 @@ __device__ __forceinline__ void ffn_sum_parts(f32x4_t (&acc)[NI][MI], const Tile
 // --------------------------------------------------------------------------------------------
 constexpr int ffn_ring_lds_bytes(int bm, int nstage) { return nstage * (bm + BROWS) * ROWB; }
 
-template <int BM, bool GATED, int WM, int WN, int NSTAGE, bool SPLIT>
+template <int BM, bool GATED, int WM, int WN, int NSTAGE, bool SPLIT, bool RAGGED>
 __device__ __forceinline__ void ffn_ring_tile(const GemmArgs& p, const TileCoord& tc, unsigned char* lds) {
   constexpr int NW = WM * WN;                     // waves per block
   constexpr int KSTEPS = BK / 32;                 // MFMA k-steps per stage
@@ -423,7 +437,7 @@ __device__ __forceinline__ void ffn_ring_tile(const GemmArgs& p, const TileCoord
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MOE_WAVE);
   const int wm = wave / WN, wn = wave % WN;
   const int K = p.K, N = p.N;
-  int kt_first = 0, kt_count = K / BK;            // this block's K stages
+  int kt_first = 0, kt_count = RAGGED ? (K + BK - 1) / BK : K / BK;   // this block's K stages
   if (SPLIT && tc.nparts > 1) {
     kt_first = tc.part * kt_count / tc.nparts;
     kt_count = (tc.part + 1) * kt_count / tc.nparts - kt_first;
@@ -484,17 +498,20 @@ __device__ __forceinline__ void ffn_ring_tile(const GemmArgs& p, const TileCoord
   // of ring tiles alone: for the small experts of a skewed batch, inside a launch of even tiles,
   // the hint gained nothing measurable.)
   const bool wgt_nt = p.mode == TILES_FIXED && tc.sharers <= 1;   // block-uniform
+  static_assert(!RAGGED || NW % 2 == 0, "one K chunk per lane in every load");
+  const uint32_t tail = RAGGED ? ragged_tail(K, (lane & 7) ^ swz(wave * 8 + (lane >> 3))) : 0u;
   // instruction i of stage kt into LDS stage `stage` (1 KiB per wave instruction)
   auto issue_load = [&](int i, int kt, int stage) {
     const __amdgpu_buffer_rsrc_t rs = (i < NLA) ? rs_a : (!GATED || i < NLA + NLB) ? rs_b0 : rs_b1;
+    const uint32_t off = RAGGED && kt == KT - 1 ? soff[i] | tail : soff[i];
     if (i < NLA || !wgt_nt)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           rs, (__attribute__((address_space(3))) void*)(lds + stage * STAGE + (i * NW + wave) * 1024), 16,
-          static_cast<int>(soff[i]), kt * ROWB, 0, 0);
+          static_cast<int>(off), kt * ROWB, 0, 0);
     else
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
           rs, (__attribute__((address_space(3))) void*)(lds + stage * STAGE + (i * NW + wave) * 1024), 16,
-          static_cast<int>(soff[i]), kt * ROWB, 0, 2);             // aux bit 1: nt
+          static_cast<int>(off), kt * ROWB, 0, 2);                 // aux bit 1: nt
   };
 
   // ---- LDS read addresses of the MFMA fragments ------------------------------------------------
@@ -572,12 +589,12 @@ __device__ __forceinline__ void ffn_ring_tile(const GemmArgs& p, const TileCoord
   ffn_store_tile<GATED, MI, NI, WN, NW>(acc, tc, p, lds, wave, lane, mi_valid, wm * (BM / WM));
 }
 
-template <int BM, bool GATED, int WM, int WN, int NSTAGE, bool SPLIT = false>
+template <int BM, bool GATED, int WM, int WN, int NSTAGE, bool SPLIT, bool RAGGED>
 __global__ __launch_bounds__(WM * WN * 64) void ffn_ring_kernel(GemmArgs p) {
   extern __shared__ __align__(1024) unsigned char lds[];
   TileCoord tc;
   if (!decode_tile<SPLIT>(p, tc)) return;
-  ffn_ring_tile<BM, GATED, WM, WN, NSTAGE, SPLIT>(p, tc, lds);
+  ffn_ring_tile<BM, GATED, WM, WN, NSTAGE, SPLIT, RAGGED>(p, tc, lds);
 }
 
 // Adds the parts of a split ring tile and stores it.
@@ -661,7 +678,7 @@ __device__ __forceinline__ void even_wave_rows(int rows_valid, int wm, int& miv,
 // make a third weight buffer (160 KiB), and the weight rows are requested a stage earlier than the
 // activation rows: they are the operand that misses the L2 (an XCD's tiles share activation
 // rows far more often than weight rows), so their requests take longest to return.
-template <bool GATED, bool SPLIT, bool ALTERNATE, bool WNT, int MI>
+template <bool GATED, bool SPLIT, bool ALTERNATE, bool WNT, bool RAGGED, int MI>
 __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord& tc, unsigned char* lds) {
   constexpr int NW = 8, WN = 2;
   constexpr int BM = MI * 64, NI = 8;
@@ -683,7 +700,7 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
   const int lw = alternate ? (wave & 3) : wave;   // this wave's place among them
   const int lset = alternate ? (wave >> 2) : 0;   // ... and the stages it loads: stage & 1 == lset
   const int K = p.K, N = p.N;
-  int KT = K / BK, k_first = 0;                   // this block's K stages
+  int KT = RAGGED ? (K + BK - 1) / BK : K / BK, k_first = 0;   // this block's K stages
   if (SPLIT && tc.nparts > 1) {
     const int kt_first = tc.part * KT / tc.nparts;
     KT = (tc.part + 1) * KT / tc.nparts - kt_first;
@@ -722,18 +739,21 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
     const int chunk = (lane & 7) ^ swz(br);
     soff_w = static_cast<uint32_t>(br) * static_cast<uint32_t>(K) * 2u + static_cast<uint32_t>(chunk) * 16u;
   }
+  // (the row groups a lane loads, of either operand, are an even number of groups apart: one chunk)
+  const uint32_t tail = RAGGED ? ragged_tail(K, (lane & 7) ^ swz(lw * 8 + (lane >> 3))) : 0u;
   // The activation rows of stage kt go to activation buffer kt % 2 and are requested two stages
   // ahead, the weight rows to weight buffer kt % NWB, NWB stages ahead.  With ALTERNATE the requests
   // made after the barrier of stage j (activations of j + 2, weights of j + NWB) all come from
   // wave set j & 1.
   auto issue_act = [&](int kt) {
     if (alternate && lset != (kt & 1)) return;
+    const uint32_t past = RAGGED && kt == KT - 1 ? tail : 0u;
 #pragma unroll
     for (int i = 0; i < NLA; ++i)
       if (i < n_act)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             rs_a, (__attribute__((address_space(3))) void*)(lds + (kt & 1) * ACT + (i * ns + lw) * 1024),
-            16, static_cast<int>(soff_a[i]), kt * ROWB, 0, 0);
+            16, static_cast<int>(RAGGED ? soff_a[i] | past : soff_a[i]), kt * ROWB, 0, 0);
   };
   // Every wave makes the same number of weight requests per stage (W_LOADS), so that a wait can
   // leave exactly one stage's weight requests outstanding: a group outside the weight matrix (the
@@ -751,21 +771,27 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
   const bool wgt_nt = WNT && tc.sharers <= WGT_NT_MAX_SHARERS;       // block-uniform
   auto issue_wgt_with = [&](int kt, int wb, auto aux_c) {
     constexpr int AUX = decltype(aux_c)::value;
+    const uint32_t base = RAGGED && kt == KT - 1 ? soff_w | tail : soff_w;
 #pragma unroll
     for (int i = 0; i < W_LOADS; ++i) {
       // group i * ns + lw of the 32 weight row groups; gated: groups 0-15 are W1 rows 0-127 of the
       // tile, groups 16-31 the same rows of W3
       const int g0 = i * ns * 8;                  // first row of the step (lw = 0)
       int jr = GATED ? (g0 & 127) : g0;           // ... inside its matrix
-      if (jr >= w_rows) jr = 0;
+      uint32_t off = base;
+      if (RAGGED) {                               // N % 64 != 0: the wave's own group of the step may lie past the end
+        if (jr + lw * 8 >= w_rows) off |= PAST_END;
+      } else if (jr >= w_rows) {
+        jr = 0;
+      }
       if (!GATED || g0 < 128)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             rs_b0, (__attribute__((address_space(3))) void*)(lds + W_BASE + wb * EVEN_WGT + (i * ns + lw) * 1024),
-            16, static_cast<int>(soff_w), kt * ROWB + jr * K * 2, 0, AUX);
+            16, static_cast<int>(off), kt * ROWB + jr * K * 2, 0, AUX);
       else
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             rs_b1, (__attribute__((address_space(3))) void*)(lds + W_BASE + wb * EVEN_WGT + (i * ns + lw) * 1024),
-            16, static_cast<int>(soff_w), kt * ROWB + jr * K * 2, 0, AUX);
+            16, static_cast<int>(off), kt * ROWB + jr * K * 2, 0, AUX);
     }
   };
   auto issue_wgt = [&](int kt, int wb) {
@@ -935,18 +961,18 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
 // long, 1 % slower, so it keeps two weight buffers for every tile.)
 constexpr int EVEN_ROWS_3WB = 256;
 
-template <bool GATED, bool SPLIT, bool ALTERNATE, bool WNT>
+template <bool GATED, bool SPLIT, bool ALTERNATE, bool WNT, bool RAGGED>
 __global__ __launch_bounds__(512) void ffn_even_kernel(GemmArgs p) {
   extern __shared__ __align__(1024) unsigned char lds[];
   TileCoord tc;
   if (!decode_tile<SPLIT>(p, tc)) return;
   const int rows = tc.m_end - tc.m_begin;         // block-uniform
   if (rows <= RING_ROWS)
-    ffn_ring_tile<RING_ROWS, GATED, 2, 4, 4, SPLIT>(p, tc, lds);
+    ffn_ring_tile<RING_ROWS, GATED, 2, 4, 4, SPLIT, RAGGED>(p, tc, lds);
   else if (!GATED && rows <= EVEN_ROWS_3WB)
-    ffn_even_tile<GATED, SPLIT, ALTERNATE, WNT, 4>(p, tc, lds);
+    ffn_even_tile<GATED, SPLIT, ALTERNATE, WNT, RAGGED, 4>(p, tc, lds);
   else
-    ffn_even_tile<GATED, SPLIT, ALTERNATE, WNT, 5>(p, tc, lds);
+    ffn_even_tile<GATED, SPLIT, ALTERNATE, WNT, RAGGED, 5>(p, tc, lds);
 }
 
 // The launch after ffn_even_kernel<.., SPLIT>: adds the parts of every split tile and stores it.
@@ -1118,29 +1144,39 @@ static int launch_grouped_gemm(GemmArgs a, int mode, int bm, int64_t A, int thre
   return rc;
 }
 
+// Shapes the RAGGED kernels take (they are not cut along K: a workspace is ignored).
+static bool ragged(const GemmArgs& a) { return a.K % BK_ELEMS != 0 || a.N % BK_ELEMS != 0; }
+
 template <bool GATED, bool ALTERNATE, bool WNT>
 static int launch_even(const GemmArgs& a, int64_t A, bool row_split, hipStream_t st) {
-  static LdsOnce once[2], once_sum;
-  if (a.split_ws && a.K >= SPLIT_MIN_K)
-    return launch_grouped_gemm(a, TILES_EVEN, EVEN_BM, A, 512, EVEN_LDS, ffn_even_kernel<GATED, true, ALTERNATE, WNT>,
-                               once[1], ffn_even_sum_parts_kernel<GATED>, once_sum, st);
+  static LdsOnce once[2], once_ragged, once_sum;
   GemmArgs b = a;
   b.m_split = row_split ? 1 : 0;
-  return launch_grouped_gemm(b, TILES_EVEN, EVEN_BM, A, 512, EVEN_LDS, ffn_even_kernel<GATED, false, ALTERNATE, WNT>,
-                             once[0], nullptr, once_sum, st);
+  if (ragged(a))
+    return launch_grouped_gemm(b, TILES_EVEN, EVEN_BM, A, 512, EVEN_LDS,
+                               ffn_even_kernel<GATED, false, ALTERNATE, true, true>, once_ragged, nullptr, once_sum, st);
+  if (a.split_ws && a.K >= SPLIT_MIN_K)
+    return launch_grouped_gemm(a, TILES_EVEN, EVEN_BM, A, 512, EVEN_LDS,
+                               ffn_even_kernel<GATED, true, ALTERNATE, WNT, false>, once[1],
+                               ffn_even_sum_parts_kernel<GATED>, once_sum, st);
+  return launch_grouped_gemm(b, TILES_EVEN, EVEN_BM, A, 512, EVEN_LDS,
+                             ffn_even_kernel<GATED, false, ALTERNATE, WNT, false>, once[0], nullptr, once_sum, st);
 }
 
 template <bool GATED>
 static int launch_ring(const GemmArgs& a, int64_t A, hipStream_t st) {
   constexpr int BM = 64, WM = 2, WN = 4, NSTAGE = 4;
   constexpr int lds_bytes = ffn_ring_lds_bytes(BM, NSTAGE);
-  static LdsOnce once[2], once_sum;
+  static LdsOnce once[2], once_ragged, once_sum;
+  if (ragged(a))
+    return launch_grouped_gemm(a, TILES_FIXED, BM, A, WM * WN * 64, lds_bytes,
+                               ffn_ring_kernel<BM, GATED, WM, WN, NSTAGE, false, true>, once_ragged, nullptr, once_sum, st);
   if (a.split_ws && a.K >= SPLIT_MIN_K)
     return launch_grouped_gemm(a, TILES_FIXED, BM, A, WM * WN * 64, lds_bytes,
-                               ffn_ring_kernel<BM, GATED, WM, WN, NSTAGE, true>, once[1],
+                               ffn_ring_kernel<BM, GATED, WM, WN, NSTAGE, true, false>, once[1],
                                ffn_ring_sum_parts_kernel<BM, GATED, WM, WN>, once_sum, st);
   return launch_grouped_gemm(a, TILES_FIXED, BM, A, WM * WN * 64, lds_bytes,
-                             ffn_ring_kernel<BM, GATED, WM, WN, NSTAGE, false>, once[0], nullptr, once_sum, st);
+                             ffn_ring_kernel<BM, GATED, WM, WN, NSTAGE, false, false>, once[0], nullptr, once_sum, st);
 }
 
 template <typename T, bool GATED>
@@ -1224,21 +1260,13 @@ static int grouped_ffn_impl(const moe_shape_t* shape, const void* x_perm, const 
               nullptr, 1, static_cast<int>(A), n_cu, static_cast<float*>(split_ws), 0,
               combine_w ? src_assign : nullptr, combine_w, shape->T};
   const bool up = parts & 1, down = parts & 2;
-  if (shape->dtype == MOE_BF16 && d % 64 == 0 && F % 64 == 0) {
+  if (shape->dtype == MOE_BF16) {
     g1.n_tiles = (F + 127) / 128;
     g2.n_tiles = (d + 255) / 256;
     return mfma_ffn(g1, g2, up, down, A, row_split, st);
   }
   g1.n_tiles = (F + 63) / 64;
   g2.n_tiles = (d + 63) / 64;
-  if (shape->dtype == MOE_BF16) {
-    if (up) {
-      rc = launch_generic<bf16_t, true>(g1, A, st);
-      if (rc != MOE_OK) return rc;
-    }
-    if (down) rc = launch_generic<bf16_t, false>(g2, A, st);
-    return rc;
-  }
   if (up) {
     rc = launch_generic<float, true>(g1, A, st);
     if (rc != MOE_OK) return rc;

@@ -510,6 +510,20 @@ def test_grouped_ffn_every_stage_count_of_the_two_stage_pipeline(d, F):
     check_ffn(cfg, L, idx)
 
 
+@pytest.mark.parametrize("d,F", [(8, 8), (16, 120), (56, 72), (64, 136), (72, 64), (136, 264), (248, 1032), (520, 392)])
+@pytest.mark.parametrize("T,E", [(37, 5), (1000, 3), (1700, 11)])
+def test_grouped_ffn_widths_that_are_multiples_of_8(T, E, d, F):
+    # K tails of 1 to 7 chunks (also a single, partial stage), N tails of one row group up to one
+    # short of a tile; ring tiles, even tiles with all waves loading (154 rows per expert) and with
+    # the waves taking turns (333), ragged last sub-tiles
+    cfg = si.small_config(T=T, d=d, E=E, k=1, F=F, seed=d + F)
+    L = si.make_layer(cfg)
+    idx = np.random.default_rng(T).integers(0, E, size=(T, 1)).astype(np.int32)
+    if T == 1000:
+        idx[:400] = 0                             # tiles of 304 and of 320 rows and more
+    check_ffn(cfg, L, idx)
+
+
 @pytest.mark.parametrize("rows", [1, 15, 16, 17, 47, 64, 65, 130, 255, 257, 319, 320, 321, 336, 641, 1000])
 def test_grouped_ffn_even_tiles_every_wave_share(rows):
     # one hot expert with `rows` rows among experts of 128 rows (so that the mean stays above the
