@@ -35,7 +35,7 @@
 // XCDs) walks a contiguous range of the tile list with the m-tiles of one weight
 // panel adjacent: CUs that share an L2 share weight tiles.
 //
-// Generic kernel (fp32): a plain LDS-tiled FMA GEMM with fp32 accumulation.
+// fp32 layers: ffn_f32_kernel, the same tiles on the fp32 matrix instruction.
 #include <type_traits>
 
 #include "moe_internal.h"
@@ -1002,91 +1002,149 @@ __global__ __launch_bounds__(512) void ffn_even_sum_parts_kernel(GemmArgs p) {
 }
 
 // --------------------------------------------------------------------------------------------
-// generic kernel: 64x64 output tile, K step 16, 4x4 outputs per thread, fp32 FMA
+// fp32 layers: v_mfma_f32_16x16x4_f32 (fp32 products and sums; twice the rate of the vector FMA).
+// The matrix instruction is 32 cycles for two 4-byte operands per lane, so LDS and L2 have ten times
+// the bf16 kernels' time per byte and small tiles cost little: a block is 4 waves on at most BM = 32
+// or 64 activation rows x 64 weight rows (gated: 64 of each matrix), three blocks or more per CU,
+// which spreads the few hundred tiles of a small batch over the chip and lets one block's barriers
+// and epilogue overlap the others' loops.  Each wave takes all the tile's 16-row sub-tiles against
+// its own 16 weight rows of each matrix, so the waves are equally busy whatever the row count is;
+// segments are cut evenly (TILES_EVEN), so 129 rows are 48 + 48 + 33 and not 64 + 64 + 1.  K step 32
+// (128-byte tile rows as in the bf16 kernels, the same swizzle and chunk order; a chunk is four
+// k-values, one per instruction).  Bound by the matrix pipe where there are tiles enough (8000 tokens,
+// d = 1024, E = 16, k = 2, F = 2048: 125 TFLOP/s, the vendor's fp32 GEMM of that size 141), by the
+// last round below.  Two stages for the gated tiles (three: 11 % slower, a block per CU less).
+// The 64 x 64 vector-FMA kernel this replaces: 1000 tokens of that shape 869 us for both GEMMs, now 280.
 // --------------------------------------------------------------------------------------------
-template <typename T> __device__ __forceinline__ float ld_elem(const T* p);
-template <> __device__ __forceinline__ float ld_elem<float>(const float* p) { return *p; }
-template <> __device__ __forceinline__ float ld_elem<bf16_t>(const bf16_t* p) { return bf16_to_f32(*p); }
-__device__ __forceinline__ void st_elem(float* p, float v) { *p = v; }
-__device__ __forceinline__ void st_elem(bf16_t* p, float v) { *p = f32_to_bf16(v); }
+constexpr int F32_NW = 4, F32_BN = 64, F32_BK = 32;
+constexpr int f32_stages(bool gated) { return gated ? 2 : 3; }
+constexpr int ffn_f32_lds_bytes(bool gated, int bm) { return f32_stages(gated) * (bm + (gated ? 2 : 1) * F32_BN) * ROWB; }
 
-template <typename T, bool GATED>
-__global__ __launch_bounds__(256) void ffn_generic_kernel(GemmArgs p) {
-  constexpr int TM = 64, TN = 64, TK = 16;
-  __shared__ float As[TK][TM + 4];
-  __shared__ float Bs[GATED ? 2 : 1][TK][TN + 4];
+template <bool GATED, int BM>
+__global__ __launch_bounds__(F32_NW * MOE_WAVE, 3) void ffn_f32_kernel(GemmArgs p) {
+  extern __shared__ __align__(1024) unsigned char lds[];
+  constexpr int NMAT = GATED ? 2 : 1;
+  constexpr int NSTAGE = f32_stages(GATED);
+  constexpr int STAGE = (BM + NMAT * F32_BN) * ROWB;
+  constexpr int NLA = BM / 8 / F32_NW, NLB = F32_BN / 8 / F32_NW, NLOAD = NLA + NMAT * NLB;
+  constexpr int MI = BM / 16;
   TileCoord tc;
   if (!decode_tile(p, tc)) return;
-  const int K = p.K, N = p.N;
-  const int n0 = tc.n_tile * TN;
-  const T* A = static_cast<const T*>(p.a);
-  const T* B0 = static_cast<const T*>(p.b0) + static_cast<int64_t>(tc.e) * N * K;
-  const T* B1 = GATED ? static_cast<const T*>(p.b1) + static_cast<int64_t>(tc.e) * N * K : nullptr;
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;         // thread's 4 columns / 4 rows
-  const int lr = tid >> 2, lk = (tid & 3) * 4;    // loader: row 0..63, k offset 0,4,8,12
-  float acc[GATED ? 2 : 1][4][4];
+  const int lane = lane_id();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MOE_WAVE);
+  const int K = p.K, N = p.N, KT = (K + F32_BK - 1) / F32_BK;
+  const int n0 = tc.n_tile * F32_BN;
+  const int rows_valid = min(tc.m_end - tc.m_begin, BM);
+  const bool gathered = p.src_assign != nullptr;
+  const float* A = static_cast<const float*>(p.a) + (gathered ? 0 : static_cast<int64_t>(tc.m_begin) * K);
+  const int64_t b_off = (static_cast<int64_t>(tc.e) * N + n0) * K;
+  const float* B0 = static_cast<const float*>(p.b0) + b_off;
+  const float* B1 = GATED ? static_cast<const float*>(p.b1) + b_off : B0;
+  const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(A), 0, 0x7FFFFFFF, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rs_b0 = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B0), 0, 0x7FFFFFFF, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rs_b1 = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B1), 0, 0x7FFFFFFF, 0x00020000);
+  // instruction i of a wave fills 8-row group i * 4 + wave of the stage: activation rows, then the rows
+  // of W1 (or W2), then of W3; rows past the end re-read the last valid one; chunks past K in the
+  // last stage come out as zeros (see ragged_tail)
+  const int chunk = (lane & 7) ^ swz(wave * 8 + (lane >> 3));
+  uint32_t soff[NLOAD];
 #pragma unroll
-  for (int s = 0; s < (GATED ? 2 : 1); ++s)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[s][i][j] = 0.f;
-  const int a_row = a_row_of(p, min(tc.m_begin + lr, tc.m_end - 1));
-  const int b_row = min(n0 + lr, N - 1);
-  for (int k0 = 0; k0 < K; k0 += TK) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int kk = k0 + lk + q;
-      As[lk + q][lr] = kk < K ? ld_elem<T>(A + static_cast<int64_t>(a_row) * K + kk) : 0.f;
-      Bs[0][lk + q][lr] = kk < K ? ld_elem<T>(B0 + static_cast<int64_t>(b_row) * K + kk) : 0.f;
-      if constexpr (GATED)
-        Bs[1][lk + q][lr] = kk < K ? ld_elem<T>(B1 + static_cast<int64_t>(b_row) * K + kk) : 0.f;
+  for (int i = 0; i < NLOAD; ++i) {
+    const int row = (i * F32_NW + wave) * 8 + (lane >> 3);
+    int r;
+    if (i < NLA) {
+      r = min(row, rows_valid - 1);
+      if (gathered) r = a_row_of(p, tc.m_begin + r);
+    } else {
+      r = min((row - BM) & (F32_BN - 1), N - 1 - n0);
     }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < TK; ++kk) {
-      float av[4], bv[GATED ? 2 : 1][4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int s = 0; s < (GATED ? 2 : 1); ++s)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) bv[s][j] = Bs[s][kk][tx * 4 + j];
-#pragma unroll
-      for (int s = 0; s < (GATED ? 2 : 1); ++s)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[s][i][j] = fmaf(av[i], bv[s][j], acc[s][i][j]);
-    }
-    __syncthreads();
+    soff[i] = static_cast<uint32_t>(r) * static_cast<uint32_t>(K) * 4u + static_cast<uint32_t>(chunk) * 16u;
   }
-  T* out = static_cast<T*>(p.out);
+  const int tail_chunks = (K & (F32_BK - 1)) >> 2;
+  const uint32_t tail = tail_chunks != 0 && chunk >= tail_chunks ? PAST_END : 0u;
+  auto issue = [&](int kt, int stage) {
+    const uint32_t past = kt == KT - 1 ? tail : 0u;
+#pragma unroll
+    for (int i = 0; i < NLOAD; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          i < NLA ? rs_a : i < NLA + NLB ? rs_b0 : rs_b1,
+          (__attribute__((address_space(3))) void*)(lds + stage * STAGE + (i * F32_NW + wave) * 1024), 16,
+          static_cast<int>(soff[i] | past), kt * ROWB, 0, 0);
+  };
+  const int l16 = lane & 15, f = swz(l16), kgrp = ((lane >> 4) & 1) * 2 + (lane >> 5);
+  int koff[2];
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) koff[kk] = ((kk * 4 + kgrp) ^ f) << 4;
+  const int x_base = l16 * ROWB;
+  const int w_base = (BM + wave * 16 + l16) * ROWB;
+  f32x4_t acc[NMAT][MI];
+#pragma unroll
+  for (int m = 0; m < NMAT; ++m)
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) acc[m][mi] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  constexpr int DIST = NSTAGE - 1;
+#pragma unroll
+  for (int s = 0; s < DIST; ++s)
+    if (s < KT) issue(s, s);
+  auto k_loop = [&](auto miv_c) {
+    constexpr int MIV = decltype(miv_c)::value;
+    for (int kt = 0; kt < KT; ++kt) {
+      const int later = min(DIST - 1, KT - 1 - kt);
+      if (later >= 2) wait_vmcnt<2 * NLOAD>();
+      else if (later == 1) wait_vmcnt<NLOAD>();
+      else wait_vmcnt<0>();
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      if (kt + DIST < KT) issue(kt + DIST, (kt + DIST) % NSTAGE);
+      const unsigned char* s = lds + (kt % NSTAGE) * STAGE;
+      f32x4_t xf[2][MIV], wf[2][NMAT];
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+        for (int m = 0; m < NMAT; ++m)
+          wf[kk][m] = *reinterpret_cast<const f32x4_t*>(s + w_base + m * (F32_BN * ROWB) + koff[kk]);
+#pragma unroll
+        for (int mi = 0; mi < MIV; ++mi)
+          xf[kk][mi] = *reinterpret_cast<const f32x4_t*>(s + x_base + mi * 16 * ROWB + koff[kk]);
+      }
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int m = 0; m < NMAT; ++m)
+#pragma unroll
+            for (int mi = 0; mi < MIV; ++mi)
+              acc[m][mi] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[kk][m][u], xf[kk][mi][u], acc[m][mi], 0, 0, 0);
+    }
+  };
+  switch ((rows_valid + 15) >> 4) {               // block-uniform
+    case 1: k_loop(std::integral_constant<int, 1>{}); break;
+    case 2: k_loop(std::integral_constant<int, 2>{}); break;
+    case 3: if constexpr (MI >= 3) k_loop(std::integral_constant<int, 3>{}); break;
+    default: if constexpr (MI >= 4) k_loop(std::integral_constant<int, 4>{}); break;
+  }
+  // accumulator (v, lane) is row lane % 16 of the sub-tile, columns 4 (lane / 16) .. + 3 of the wave's 16
+  float* out = static_cast<float*>(p.out);
+  const int c = n0 + wave * 16 + 4 * (lane >> 4);
   const int32_t* out_map = GATED ? nullptr : p.out_map;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int gr = tc.m_begin + ty * 4 + i;
-    if (gr >= tc.m_end) continue;
+  for (int mi = 0; mi < MI; ++mi) {
+    int gr = tc.m_begin + mi * 16 + l16;
+    if (gr >= tc.m_end || c >= N) continue;       // (N is a multiple of 4)
     float scale = 1.f;
     if (out_map) {
       gr = min(max(out_map[gr], 0), p.out_rows - 1);
       scale = p.out_scale[gr];
     }
+    f32x4_t o;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int c = n0 + tx * 4 + j;
-      if (c < N) {
-        float v;
-        if (GATED) {
-          const float g = acc[0][i][j];
-          v = g / (1.0f + expf(-g)) * acc[GATED ? 1 : 0][i][j];
-        } else {
-          v = out_map ? acc[0][i][j] * scale : acc[0][i][j];
-        }
-        st_elem(out + static_cast<int64_t>(gr) * N + c, v);
-      }
+    for (int u = 0; u < 4; ++u) {
+      const float v = acc[0][mi][u];
+      o[u] = GATED ? v / (1.0f + expf(-v)) * acc[NMAT - 1][mi][u] : out_map ? v * scale : v;
     }
+    *reinterpret_cast<f32x4_t*>(out + static_cast<int64_t>(gr) * N + c) = o;
   }
 }
 
@@ -1179,16 +1237,19 @@ static int launch_ring(const GemmArgs& a, int64_t A, hipStream_t st) {
                              ffn_ring_kernel<BM, GATED, WM, WN, NSTAGE, false, false>, once[0], nullptr, once_sum, st);
 }
 
-template <typename T, bool GATED>
-static int launch_generic(GemmArgs a, int64_t A, hipStream_t st) {
-  a.mode = TILES_FIXED;
-  a.bm = 64;
-  int64_t grid = max_m_tiles(A, a.E, 64) * a.n_tiles;
-  grid = (grid + 7) / 8 * 8;
-  if (grid > 0x7FFFFFFF) return MOE_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL((ffn_generic_kernel<T, GATED>), dim3(static_cast<unsigned>(grid)), dim3(256), 0,
-                     st, a);
-  return launch_status();
+// 32-row tiles while 64-row tiles would be fewer than 16 per CU (measured, both GEMMs, d = 1024, E = 16,
+// F = 2048, 32- against 64-row tiles: 1000 tokens 280 / 295 us, 2000 tokens 468 / 490; 8000 tokens,
+// 31 and 62 tiles per CU, 1607 / 1587, as every weight row is then staged twice as often).
+template <bool GATED>
+static int launch_f32(GemmArgs a, int64_t A, hipStream_t st) {
+  static LdsOnce once[2], once_sum;
+  a.n_tiles = (a.N + F32_BN - 1) / F32_BN;
+  const int64_t tiles64 = (A + 63) / 64 * a.n_tiles;
+  if (tiles64 < 16 * static_cast<int64_t>(a.n_cu > 0 ? a.n_cu : 256))
+    return launch_grouped_gemm(a, TILES_EVEN, 32, A, F32_NW * MOE_WAVE, ffn_f32_lds_bytes(GATED, 32),
+                               ffn_f32_kernel<GATED, 32>, once[0], nullptr, once_sum, st);
+  return launch_grouped_gemm(a, TILES_EVEN, 64, A, F32_NW * MOE_WAVE, ffn_f32_lds_bytes(GATED, 64),
+                             ffn_f32_kernel<GATED, 64>, once[1], nullptr, once_sum, st);
 }
 
 // Mean rows per expert from which the even tiles take over from the ring tiles, and from which the
@@ -1265,13 +1326,11 @@ static int grouped_ffn_impl(const moe_shape_t* shape, const void* x_perm, const 
     g2.n_tiles = (d + 255) / 256;
     return mfma_ffn(g1, g2, up, down, A, row_split, st);
   }
-  g1.n_tiles = (F + 63) / 64;
-  g2.n_tiles = (d + 63) / 64;
   if (up) {
-    rc = launch_generic<float, true>(g1, A, st);
+    rc = launch_f32<true>(g1, A, st);
     if (rc != MOE_OK) return rc;
   }
-  if (down) rc = launch_generic<float, false>(g2, A, st);
+  if (down) rc = launch_f32<false>(g2, A, st);
   return rc;
 }
 

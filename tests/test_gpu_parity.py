@@ -524,6 +524,31 @@ def test_grouped_ffn_widths_that_are_multiples_of_8(T, E, d, F):
     check_ffn(cfg, L, idx)
 
 
+@pytest.mark.parametrize("d,F", [(4, 4), (28, 60), (32, 64), (36, 68), (64, 132), (136, 100)])
+@pytest.mark.parametrize("rows", [(1, 0, 33), (16, 17, 31, 32), (64, 65, 129, 5)])
+def test_grouped_ffn_fp32_tile_edges(rows, d, F):
+    # K tails of 1 to 7 chunks of four, N tails around the 64 weight rows of a tile, rows around the
+    # 16-row sub-tiles and the 32-row tiles; the last case's down-projection also in 64-row tiles below
+    cfg = si.small_config(T=sum(rows), d=d, E=len(rows), k=1, F=F, dtype=si.F32, seed=d + F + rows[0])
+    check_ffn(cfg, si.make_layer(cfg), np.repeat(np.arange(len(rows), dtype=np.int32), rows)[:, None])
+
+
+def test_grouped_ffn_fp32_64_row_tiles():
+    # enough tiles (16 per compute unit) for the 64-row form of both GEMMs, segments of every row count
+    # modulo 64 that is near an edge
+    rows = (2000, 2049, 2063, 2064, 2111, 63)
+    cfg = si.small_config(T=sum(rows), d=1608, E=len(rows), k=1, F=1612, dtype=si.F32)
+    L = si.make_layer(cfg)
+    idx = np.repeat(np.arange(len(rows), dtype=np.int32), rows)[:, None]
+    counts, offsets = orc.expert_load(idx, cfg.E)     # (token order is already the permuted order)
+    h, yp = gpu_ffn(cfg, L["x"], offsets, L["w1"], L["w3"], L["w2"])
+    at = np.unique(np.concatenate([np.r_[o:min(o + 70, o + n), max(o, o + n - 70):o + n]
+                                   for o, n in zip(offsets[:-1], counts)]))
+    ry, rh = orc.grouped_ffn(L["x"][at], np.searchsorted(at, offsets), L["w1"], L["w3"], L["w2"], return_h=True)
+    assert rel_err(h[at], rh) <= tol_of(cfg.dtype) and rel_err(yp[at], ry) <= tol_of(cfg.dtype)
+    assert np.isfinite(h).all() and np.isfinite(yp).all()
+
+
 @pytest.mark.parametrize("rows", [1, 15, 16, 17, 47, 64, 65, 130, 255, 257, 319, 320, 321, 336, 641, 1000])
 def test_grouped_ffn_even_tiles_every_wave_share(rows):
     # one hot expert with `rows` rows among experts of 128 rows (so that the mean stays above the
