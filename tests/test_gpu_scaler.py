@@ -355,3 +355,29 @@ def test_predictor_with_placement_keeps_warm_replicas_over_rounds():
     assert second[3] == S and np.array_equal(second[0], first[0])
     assert np.array_equal(pred.gpu_of[1].cpu().numpy()[:S], second[0]) and int(pred.n_warm.item()) == S
     assert np.array_equal(pred.gpu_load.cpu().numpy(), second[1])
+
+
+@pytest.mark.parametrize("G", [1, 15, 16, 17, 64])
+@pytest.mark.parametrize("steps", [1023, 1024, 1025, 2049])
+def test_place_replicas_around_the_kernel_s_chunks_of_steps(steps, G):
+    # the kernel prepares 1024 steps at a time and takes the shortest queue over 16 or 64 lanes; with
+    # a previous round (some of its replicas dead) and a slot limit
+    rng = np.random.default_rng(steps + G)
+    E = 100
+    loads = si.zipf_loads(E, 1 << 20, 1.1, steps)
+    replicas = rng.multinomial(steps - E, np.full(E, 1 / E)) + 1
+    prev_r = rng.integers(0, 20, size=E)
+    prev_gpu = rng.integers(-1, G, size=int(prev_r.sum()))
+    check_place(loads, replicas, G, np.concatenate([[0], np.cumsum(prev_r)]), prev_gpu,
+                np.full(G, steps // G + 1))
+
+
+@pytest.mark.parametrize("E", [2, 63, 64, 65, 128, 129, 256])
+def test_loads_that_differ_in_their_last_bits_only(E):
+    # quotients that share the upper word of their doubles (the arg-max and arg-min resolve them by the
+    # lower word), exact ties beside them
+    rng = np.random.default_rng(E)
+    loads = (2 ** 31 - 1 - rng.integers(0, 3, size=E)).astype(np.int64)
+    replicas = check_scale(loads, 1, 3 * E // 2, -1.0)
+    check_place(loads, replicas, 16)
+    check_place(loads, replicas, 40)
