@@ -9,12 +9,13 @@
 // accumulators, h stored once) and a plain one for W2.  Both are ragged grouped
 // GEMMs, one launch each: the tile list is derived on the device from `offsets`, so the host
 // never learns the expert loads.
-//   even tiles (128 or more rows per expert on average): an expert's c rows are cut into
-//          ceil(c / 320) tiles of nearly equal height (multiples of 16 rows), each against 256
-//          weight rows; K step 64, two LDS stages, hand-ordered MFMA pipeline (ffn_even_kernel).
-//   ring tiles (decode and small prefill batches, below 128 rows per expert: the call is bound by
-//          streaming the weights once): 64-row tiles against 256 weight rows with a four-stage
-//          LDS ring, three stages of loads in flight (ffn_ring_kernel).
+//   an expert's c rows are cut into ceil(c / 320) tiles of nearly equal height (multiples of 16
+//   rows), each against 256 weight rows; the tile's height then picks its pipeline:
+//   up to 64 rows   ring tile (ffn_ring_tile): paced by the weight stream, four-stage LDS ring;
+//   65 and more     even tile (ffn_even_tile): hand-ordered MFMA pipeline, two activation buffers and
+//                   as many weight buffers as the LDS holds beside them (four, three or two).
+//   A tile takes a whole compute unit, so tiles of a last round that is at most half full are cut
+//   into pieces for the idle units: low ones along the weight rows, high ones along their own rows.
 //
 // moe_grouped_ffn_ws brings a workspace of fp32 partial tiles: a tile takes a whole compute unit,
 // so a GEMM runs in rounds of the chip, and when the last round of a GEMM with a long reduction
@@ -45,7 +46,6 @@ namespace moe {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
-enum TileMode { TILES_FIXED = 0, TILES_EVEN = 1 };
 constexpr int BK_ELEMS = 64;    // K elements per stage of the MFMA kernels
 
 struct GemmArgs {
@@ -56,9 +56,9 @@ struct GemmArgs {
   const int32_t* offsets;
   int E, K, N;
   int n_tiles;      // tiles along N
+  int bn;           // output columns of a whole tile
   int rows;         // T*k; row ranges read from `offsets` are clamped to it
-  int mode;         // TileMode
-  int bm;           // TILES_FIXED: rows of a tile; TILES_EVEN: most rows of a tile
+  int bm;           // most rows of a tile
   // Gathered activations: row r of the GEMM is row src_assign[r] / k_div of `a` (the token that
   // assignment r belongs to) instead of row r itself.  nullptr = `a` is already permuted.
   const int32_t* src_assign;
@@ -76,9 +76,9 @@ struct GemmArgs {
   const int32_t* out_map;
   const float* out_scale;
   int out_rows;     // rows of `out` (mapped row numbers are clamped to it)
-  // TILES_EVEN launches without split_ws: tiles of a last round that is at most half full are cut
-  // along their rows into pieces for the idle units (the grid has a round of extra blocks).
-  int m_split;
+  // Launches without split_ws: tiles of a last round that is at most half full are cut into pieces
+  // for the idle units (the grid has a round of extra blocks).
+  int tail_split;
 };
 
 constexpr int SPLIT_SLOT_FLOATS = 320 * 256;   // one partial tile (the largest: 320 x 256 fp32)
@@ -93,13 +93,22 @@ __device__ __forceinline__ int a_row_of(const GemmArgs& p, int r) {
 }
 
 struct TileCoord {
-  int e, m_begin, m_end, n_tile;
+  int e, m_begin, m_end;
+  int n0;      // first output column
+  int n_pieces;  // 2, 4: this is a piece with that share of the whole tile's weight rows
   // K split of a tile of the last, partial round (nparts == 1: the whole K range)
   int part, nparts;
   int pslot;   // partial-tile slot of this part; the parts of a tile have consecutive slots
   int sharers; // tiles and pieces of tiles of this expert that read the same weight rows
 };
-constexpr int MSPLIT_MAX_PIECES = 4;
+constexpr int TAIL_MAX_PIECES = 4;
+// Tiles of at most RING_ROWS rows have little arithmetic per weight byte and are paced by memory
+// latency, which the ring pipeline's equal depth for both operands hides best.
+constexpr int RING_ROWS = 64;
+// Tiles of the last round up to this height are cut along the weight rows: every weight byte is
+// still requested once, and these tiles wait for weights.  Higher tiles are cut along their own rows:
+// they wait for the matrix pipe, and a piece then takes a pipeline that a whole tile takes too.
+constexpr int NSPLIT_ROWS = 128;
 constexpr int WGT_NT_MAX_SHARERS = 2;
 
 // Inclusive prefix sum over the wave by DPP: four shifted adds inside each row of 16 lanes, then
@@ -119,8 +128,7 @@ __device__ __forceinline__ int wave_scan_add(int x) {
 
 // Maps a work-group to (expert, row range, n-tile).  Every wave computes this on its
 // own from the device-resident offsets; returns false if the group has no tile.
-// An expert with c rows has ceil(c / bm) tiles: TILES_FIXED cuts them at multiples of bm (the last
-// one holds the remainder), TILES_EVEN deals the segment's 16-row sub-tiles evenly to them.
+// An expert with c rows has ceil(c / bm) tiles; the segment's 16-row sub-tiles are dealt to them evenly.
 // Tile order: expert-major, then n-tile, then m-tile (m fastest), cut into 8 contiguous ranges,
 // one per XCD.
 template <bool SPLIT = false>
@@ -186,17 +194,17 @@ __device__ __forceinline__ bool decode_tile(const GemmArgs& p, TileCoord& tc) {
       tc.pslot = xcd * cus_x + j;                // j < tail_x * parts <= cus_x
     }
     if (vid >= total) return false;
-  } else if (p.m_split && slot + max(1, (p.n_cu > 0 ? p.n_cu : 256) / 8) >= per_xcd) {
-    // No workspace: the tiles of a last round that is at most half full are cut along their rows
-    // instead, each piece a tile of its own that streams the whole weight tile (out of the L2, which
-    // its sister pieces fill at the same time).  The outputs are the same bits: a row's sums do not
-    // depend on which rows share its tile.  (Only blocks of the last two rounds come here: the
+  } else if (p.tail_split && slot + max(1, (p.n_cu > 0 ? p.n_cu : 256) / 8) >= per_xcd) {
+    // No workspace: the tiles of a last round that is at most half full are cut along the weight rows
+    // (up to NSPLIT_ROWS high) or along their own rows (each piece then streams the whole weight tile, out
+    // of the L2, which its sister pieces fill at the same time).  The outputs are the same bits: an
+    // element's sum does not depend on what shares its tile.  (Only blocks of the last two rounds come here: the
     // integer divisions below cost a tile of the rounds before them half a percent of its time.)
     const int cus_x = max(1, (p.n_cu > 0 ? p.n_cu : 256) / 8);
     const int full_x = per_xcd / cus_x * cus_x;
     const int tail_x = per_xcd - full_x;
     if (slot >= full_x) {
-      if (tail_x > 0 && 2 * tail_x <= cus_x) m_pieces = min(cus_x / tail_x, MSPLIT_MAX_PIECES);
+      if (tail_x > 0 && 2 * tail_x <= cus_x) m_pieces = min(cus_x / tail_x, TAIL_MAX_PIECES);
       const int j = slot - full_x;
       const int t_local = j / m_pieces;
       if (t_local >= tail_x) return false;
@@ -232,33 +240,37 @@ __device__ __forceinline__ bool decode_tile(const GemmArgs& p, TileCoord& tc) {
   const int seg_begin = max(__builtin_amdgcn_readlane(found_ob, src), 0);
   const int seg_end = min(__builtin_amdgcn_readlane(found_oe, src), p.rows);
   tc.e = e;
-  tc.n_tile = loc / m_tiles;
+  tc.n0 = loc / m_tiles * p.bn;
+  tc.n_pieces = 1;
   tc.sharers = m_tiles;
-  if (p.mode == TILES_EVEN) {
-    // The segment's 16-row sub-tiles are dealt in pairs: a tile's sub-tiles go to four wave rows,
-    // and wave rows 0, 2 and 1, 3 share their SIMDs, so a tile with an odd number of sub-tiles is
-    // as slow as one with the next even number.  67 sub-tiles become 17, 16, 16, 18 (9 + 8 + 8 + 9
-    // per SIMD pair), not 16, 17, 17, 17 (8 + 9 + 9 + 9).  An odd one out goes to the first tile,
-    // which has the fewest pairs (so no tile exceeds 20 sub-tiles).
-    const int sub = (seg_end - seg_begin + 15) / 16;
-    const int pairs = sub >> 1, odd = sub & 1;
-    const int b0 = m_idx == 0 ? 0 : 2 * (m_idx * pairs / m_tiles) + odd;
-    const int b1 = 2 * ((m_idx + 1) * pairs / m_tiles) + odd;
-    int s0 = b0, s1 = b1;
-    if (m_pieces > 1) {
-      const int n_sub = b1 - b0;
+  // The segment's 16-row sub-tiles are dealt in pairs: a tile's sub-tiles go to four wave rows,
+  // and wave rows 0, 2 and 1, 3 share their SIMDs, so a tile with an odd number of sub-tiles is
+  // as slow as one with the next even number.  67 sub-tiles become 17, 16, 16, 18 (9 + 8 + 8 + 9
+  // per SIMD pair), not 16, 17, 17, 17 (8 + 9 + 9 + 9).  An odd one out goes to the first tile,
+  // which has the fewest pairs (so no tile exceeds 20 sub-tiles).
+  const int sub = (seg_end - seg_begin + 15) / 16;
+  const int pairs = sub >> 1, odd = sub & 1;
+  const int b0 = m_idx == 0 ? 0 : 2 * (m_idx * pairs / m_tiles) + odd;
+  const int b1 = 2 * ((m_idx + 1) * pairs / m_tiles) + odd;
+  int s0 = b0, s1 = b1;
+  if (m_pieces > 1) {
+    const int n_sub = b1 - b0;
+    if (n_sub <= NSPLIT_ROWS / 16) {
+      const int pieces = m_pieces >= 4 && n_sub <= RING_ROWS / 16 ? 4 : 2;
+      if (m_piece >= pieces) return false;
+      tc.n_pieces = pieces;
+      tc.n0 += m_piece * (p.bn / pieces);
+      if (tc.n0 >= p.N) return false;
+    } else {
       const int pieces = min(m_pieces, max(1, n_sub / 4));    // a piece keeps 64 rows or more
       if (m_piece >= pieces) return false;
       tc.sharers = m_tiles + pieces - 1;
       s0 = b0 + m_piece * n_sub / pieces;
       s1 = b0 + (m_piece + 1) * n_sub / pieces;
     }
-    tc.m_begin = seg_begin + s0 * 16;
-    tc.m_end = min(seg_end, seg_begin + s1 * 16);
-  } else {
-    tc.m_begin = seg_begin + m_idx * bm;
-    tc.m_end = min(seg_end, tc.m_begin + bm);
   }
+  tc.m_begin = seg_begin + s0 * 16;
+  tc.m_end = min(seg_end, seg_begin + s1 * 16);
   return tc.m_begin < tc.m_end;
 }
 
@@ -295,15 +307,17 @@ __device__ __forceinline__ uint32_t ragged_tail(int K, int chunk) {
 __device__ __forceinline__ int swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N <= 20, "vmcnt immediate");
-#define MOE_VMCNT_CASE(n) \
-  if constexpr (N == n) asm volatile("s_waitcnt vmcnt(" #n ")" ::: "memory");
-  MOE_VMCNT_CASE(0) MOE_VMCNT_CASE(1) MOE_VMCNT_CASE(2) MOE_VMCNT_CASE(3) MOE_VMCNT_CASE(4)
-  MOE_VMCNT_CASE(5) MOE_VMCNT_CASE(6) MOE_VMCNT_CASE(7) MOE_VMCNT_CASE(8) MOE_VMCNT_CASE(9)
-  MOE_VMCNT_CASE(10) MOE_VMCNT_CASE(11) MOE_VMCNT_CASE(12) MOE_VMCNT_CASE(13) MOE_VMCNT_CASE(14)
-  MOE_VMCNT_CASE(15) MOE_VMCNT_CASE(16) MOE_VMCNT_CASE(17) MOE_VMCNT_CASE(18) MOE_VMCNT_CASE(19)
-  MOE_VMCNT_CASE(20)
-#undef MOE_VMCNT_CASE
+  static_assert(N >= 0 && N <= 63, "vmcnt immediate");
+  asm volatile("s_waitcnt vmcnt(%0)" ::"i"(N) : "memory");
+}
+// Leaves the requests of the last min(LATER, later) stages (NLOAD per stage) in flight.
+template <int LATER, int NLOAD> __device__ __forceinline__ void wait_stages(int later) {
+  if constexpr (LATER == 0) {
+    wait_vmcnt<0>();
+  } else {
+    if (later >= LATER) wait_vmcnt<LATER * NLOAD>();
+    else wait_stages<LATER - 1, NLOAD>(later);
+  }
 }
 
 // Store of a wave's outputs.  Accumulator (v, lane) holds out[row = m-sub-tile + lane%16]
@@ -319,18 +333,17 @@ __device__ __forceinline__ void ffn_store_tile(const f32x4_t (&acc)[NI][MI], con
                                                const GemmArgs& p, unsigned char* lds, int wave, int lane,
                                                int mi_valid, int wave_row0) {
   constexpr int NIH = GATED ? NI / 2 : NI;
-  constexpr int BN_OUT = GATED ? 128 : 256;
   const int wn = wave % WN;
   const int l16 = lane & 15;
   const int N = p.N;
-  const int n0 = tc.n_tile * BN_OUT;
+  const int n0 = tc.n0;
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   constexpr int CW = NIH * 16;                    // output columns of this wave
   constexpr int PITCH = CW * 2 + 32;              // bytes
   constexpr int LPR = CW * 2 / 16;                // lanes that store one row
   constexpr int RPI = 64 / LPR;                   // rows per store instruction
-  static_assert(16 % RPI == 0 && NW * 16 * PITCH <= 40 * 1024, "staging fits the smallest LDS buffer it is given");
+  static_assert((16 % RPI == 0 || RPI == 32) && NW * 16 * PITCH <= 40 * 1024, "staging fits the smallest LDS buffer it is given");
   unsigned char* region = lds + wave * (16 * PITCH);
   bf16_t* out = static_cast<bf16_t*>(p.out);
   const int col0 = n0 + wn * CW;                  // first output column of this wave
@@ -358,8 +371,9 @@ __device__ __forceinline__ void ffn_store_tile(const f32x4_t (&acc)[NI][MI], con
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // same wave: writes land before the reads
 #pragma unroll
-      for (int it = 0; it < 16 / RPI; ++it) {
+      for (int it = 0; it < (16 + RPI - 1) / RPI; ++it) {
         const int r = it * RPI + lane / LPR;
+        if (RPI > 16 && r >= 16) continue;        // a sub-tile narrower than the wave's store
         const int c = (lane % LPR) * 8;           // first column of this lane's 16 bytes
         const uint4 v = *reinterpret_cast<const uint4*>(region + r * PITCH + c * 2);
         const int gr = row_base + r;
@@ -410,27 +424,32 @@ __device__ __forceinline__ void ffn_sum_parts(f32x4_t (&acc)[NI][MI], const Tile
 }
 
 // --------------------------------------------------------------------------------------------
-// Ring tiles: BM x 256 block tile, WM x WN waves, NSTAGE LDS stages of 64 K-elements with
-// NSTAGE - 1 stages of loads in flight (little arithmetic per weight byte: paced by memory
-// latency).  SPLIT: tiles of the last, partial round may be cut along K (see decode_tile): a part
-// leaves its fp32 accumulators in the workspace instead of storing the tile, and
-// ffn_ring_sum_parts_kernel, the next launch on the stream, adds the parts and stores the tile.
+// Ring tiles: BM x WROWS block tile, WM x WN waves, NSTAGE LDS stages of 64 K-elements with
+// NSTAGE - 1 stages of loads in flight.  Bound by the weight stream from HBM: what counts is the bytes
+// a CU keeps in flight (64 x 256 tiles: 96 KiB of weights) and that every CU has a tile.  The
+// pieces of a last round are 64 x 64 (nine stages), 64 x 128 (six) and 128 x 128 (five), the
+// deepest rings that fit.  (Measured, pieces against whole tiles, or 64-row pieces for the 128-row ones:
+// down-projection of the Mixtral shape, 128 tiles of K = 14336, at 300 tokens 242 -> 186 us, at
+// one token, 32 tiles, 154 -> 73 us.)  SPLIT: tiles of the last round may be cut along K
+// instead (see decode_tile): a part leaves its fp32 accumulators in the workspace, and the next launch
+// on the stream adds the parts and stores the tile.
 // --------------------------------------------------------------------------------------------
-constexpr int ffn_ring_lds_bytes(int bm, int nstage) { return nstage * (bm + BROWS) * ROWB; }
+constexpr int ffn_ring_lds_bytes(int bm, int wrows, int nstage) { return nstage * (bm + wrows) * ROWB; }
 
-template <int BM, bool GATED, int WM, int WN, int NSTAGE, bool SPLIT, bool RAGGED>
+template <int BM, int WROWS, bool GATED, int WM, int WN, int NSTAGE, bool SPLIT, bool WNT, bool RAGGED>
 __device__ __forceinline__ void ffn_ring_tile(const GemmArgs& p, const TileCoord& tc, unsigned char* lds) {
   constexpr int NW = WM * WN;                     // waves per block
   constexpr int KSTEPS = BK / 32;                 // MFMA k-steps per stage
   constexpr int MI = BM / WM / 16;                // 16-row activation sub-tiles per wave
-  constexpr int NI = BROWS / WN / 16;             // 16-row weight sub-tiles per wave
+  constexpr int NI = WROWS / WN / 16;             // 16-row weight sub-tiles per wave
   constexpr int NIH = GATED ? NI / 2 : NI;        // gated: sub-tiles per weight matrix
-  constexpr int STAGE = (BM + BROWS) * ROWB;      // bytes per stage
-  constexpr int NLOAD = (BM + BROWS) / 8 / NW;    // direct-to-LDS instructions per wave per stage
+  constexpr int WHALF = GATED ? WROWS / 2 : WROWS;  // weight rows per matrix
+  constexpr int STAGE = (BM + WROWS) * ROWB;      // bytes per stage
+  constexpr int NLOAD = (BM + WROWS) / 8 / NW;    // direct-to-LDS instructions per wave per stage
   constexpr int NLA = BM / 8 / NW;                // ... of which load activation rows
-  constexpr int NLB = 128 / 8 / NW;               // ... per 128 weight rows
-  constexpr int BN_OUT = GATED ? 128 : 256;       // output columns per block tile
-  static_assert(NLA * 8 * NW == BM && NLB * 8 * NW == 128 && MI >= 1 && NIH >= 1, "tile shape");
+  constexpr int NLB = WHALF / 8 / NW;             // ... of each weight matrix
+  constexpr bool MIXED = GATED && NLB == 0;       // one instruction loads both: half the waves each
+  static_assert(NLA * 8 * NW == BM && (NLOAD - NLA) * 8 * NW == WROWS && MI >= 1 && NIH >= 1, "tile shape");
   static_assert(NSTAGE > 2, "a ring keeps at least two stages of loads in flight");
 
   const int lane = lane_id();
@@ -443,7 +462,7 @@ __device__ __forceinline__ void ffn_ring_tile(const GemmArgs& p, const TileCoord
     kt_count = (tc.part + 1) * kt_count / tc.nparts - kt_first;
   }
   const int KT = kt_count;
-  const int n0 = tc.n_tile * BN_OUT;
+  const int n0 = tc.n0;
   const bf16_t* A = static_cast<const bf16_t*>(p.a);
   const bf16_t* B0 = static_cast<const bf16_t*>(p.b0) + static_cast<int64_t>(tc.e) * N * K;
   const bf16_t* B1 = GATED ? static_cast<const bf16_t*>(p.b1) + static_cast<int64_t>(tc.e) * N * K
@@ -478,7 +497,7 @@ __device__ __forceinline__ void ffn_ring_tile(const GemmArgs& p, const TileCoord
       if (gathered) r = a_row_of(p, tc.m_begin + r);
     } else {
       const int br = row - BM;
-      r = GATED ? min(br & 127, N - 1 - n0) : min(br, N - 1 - n0);
+      r = min(br & (WHALF - 1), N - 1 - n0);
     }
     soff[i] = static_cast<uint32_t>(r) * static_cast<uint32_t>(K) * 2u + static_cast<uint32_t>(chunk) * 16u;
   }
@@ -486,23 +505,21 @@ __device__ __forceinline__ void ffn_ring_tile(const GemmArgs& p, const TileCoord
   // per-lane 32-bit offset and a scalar K offset replace 64-bit per-lane address arithmetic
   const __amdgpu_buffer_rsrc_t rs_a =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(base_a), 0, 0x7FFFFFFF, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rs_b0 =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(base_b0), 0, 0x7FFFFFFF, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rs_b0 = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<unsigned char*>(MIXED && wave >= NW / 2 ? base_b1 : base_b0), 0, 0x7FFFFFFF, 0x00020000);
   const __amdgpu_buffer_rsrc_t rs_b1 = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<unsigned char*>(GATED ? base_b1 : base_b0), 0, 0x7FFFFFFF, 0x00020000);
   // The weight rows of an expert that is this one tile are read once by the whole chip: requested
   // with the non-temporal hint they do not displace what other blocks still share in the L2.
   // (Measured with the hint on every ring tile: decode-shaped layer 0.79 -> 0.72 ms, Mixtral shape
   // at 16 tokens 0.51 -> 0.48 ms, its weights then stream at 5.9 TB/s; with two tiles per expert,
-  // Mixtral shape at 256 and 448 tokens, 1 to 5 % slower, hence the condition.  Only in launches
-  // of ring tiles alone: for the small experts of a skewed batch, inside a launch of even tiles,
-  // the hint gained nothing measurable.)
-  const bool wgt_nt = p.mode == TILES_FIXED && tc.sharers <= 1;   // block-uniform
+  // Mixtral shape at 256 and 448 tokens, 1 to 5 % slower, hence the condition.)
+  const bool wgt_nt = WNT && tc.sharers <= 1;   // block-uniform
   static_assert(!RAGGED || NW % 2 == 0, "one K chunk per lane in every load");
   const uint32_t tail = RAGGED ? ragged_tail(K, (lane & 7) ^ swz(wave * 8 + (lane >> 3))) : 0u;
   // instruction i of stage kt into LDS stage `stage` (1 KiB per wave instruction)
   auto issue_load = [&](int i, int kt, int stage) {
-    const __amdgpu_buffer_rsrc_t rs = (i < NLA) ? rs_a : (!GATED || i < NLA + NLB) ? rs_b0 : rs_b1;
+    const __amdgpu_buffer_rsrc_t rs = (i < NLA) ? rs_a : (!GATED || MIXED || i < NLA + NLB) ? rs_b0 : rs_b1;
     const uint32_t off = RAGGED && kt == KT - 1 ? soff[i] | tail : soff[i];
     if (i < NLA || !wgt_nt)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
@@ -529,7 +546,7 @@ __device__ __forceinline__ void ffn_ring_tile(const GemmArgs& p, const TileCoord
   for (int kk = 0; kk < KSTEPS; ++kk) koff[kk] = (((kk * 4 + kgrp) ^ f) << 4);
   const int x_base = (wm * (BM / WM) + l16) * ROWB;
   // first weight row of sub-tile ni relative to the wave's own first weight row
-  auto w_sub = [](int ni) { return GATED ? (ni / NIH) * 128 + (ni % NIH) * 16 : ni * 16; };
+  auto w_sub = [](int ni) { return GATED ? (ni / NIH) * WHALF + (ni % NIH) * 16 : ni * 16; };
   const int w_base = (BM + (GATED ? wn * (NIH * 16) : wn * (NI * 16)) + l16) * ROWB;
 
   f32x4_t acc[NI][MI];
@@ -567,19 +584,19 @@ __device__ __forceinline__ void ffn_ring_tile(const GemmArgs& p, const TileCoord
 #pragma unroll
       for (int i = 0; i < NLOAD; ++i) issue_load(i, s, s);
     }
+  int cur = 0, fill = DIST;                       // slots of stage kt and of stage kt + DIST
   for (int kt = 0; kt < KT; ++kt) {
     // the loads of stage kt are the oldest outstanding; up to DIST-1 later stages may follow
-    const int later = min(DIST - 1, KT - 1 - kt);
-    if (later >= 2) wait_vmcnt<2 * NLOAD>();
-    else if (later == 1) wait_vmcnt<NLOAD>();
-    else wait_vmcnt<0>();
+    wait_stages<DIST - 1, NLOAD>(KT - 1 - kt);
     __builtin_amdgcn_s_barrier();     // stage kt landed for all waves; the slot of kt-1 is free
     asm volatile("" ::: "memory");
     if (kt + DIST < KT) {
 #pragma unroll
-      for (int i = 0; i < NLOAD; ++i) issue_load(i, kt + DIST, (kt + DIST) % NSTAGE);
+      for (int i = 0; i < NLOAD; ++i) issue_load(i, kt + DIST, fill);
     }
-    if (mi_valid > 0) compute(kt % NSTAGE);
+    if (mi_valid > 0) compute(cur);
+    cur = cur + 1 == NSTAGE ? 0 : cur + 1;
+    fill = fill + 1 == NSTAGE ? 0 : fill + 1;
   }
 
   if (SPLIT && tc.nparts > 1) {
@@ -587,14 +604,6 @@ __device__ __forceinline__ void ffn_ring_tile(const GemmArgs& p, const TileCoord
     return;
   }
   ffn_store_tile<GATED, MI, NI, WN, NW>(acc, tc, p, lds, wave, lane, mi_valid, wm * (BM / WM));
-}
-
-template <int BM, bool GATED, int WM, int WN, int NSTAGE, bool SPLIT, bool RAGGED>
-__global__ __launch_bounds__(WM * WN * 64) void ffn_ring_kernel(GemmArgs p) {
-  extern __shared__ __align__(1024) unsigned char lds[];
-  TileCoord tc;
-  if (!decode_tile<SPLIT>(p, tc)) return;
-  ffn_ring_tile<BM, GATED, WM, WN, NSTAGE, SPLIT, RAGGED>(p, tc, lds);
 }
 
 // Adds the parts of a split ring tile and stores it.
@@ -611,16 +620,6 @@ __device__ __forceinline__ void ffn_ring_sum_tile(const GemmArgs& p, const TileC
   f32x4_t acc[NI][MI];
   ffn_sum_parts<MI, NI, NW * MOE_WAVE>(acc, tc, p);
   ffn_store_tile<GATED, MI, NI, WN, NW>(acc, tc, p, lds, wave, lane, mi_valid, wm * (BM / WM));
-}
-
-// The launch after a ring GEMM whose tiles may have been split: block (xcd, t) adds the parts of
-// split tile t of the XCD's last round and stores the tile.  Finds nothing to do when no tile was split.
-template <int BM, bool GATED, int WM, int WN>
-__global__ __launch_bounds__(WM * WN * 64) void ffn_ring_sum_parts_kernel(GemmArgs p) {
-  extern __shared__ __align__(1024) unsigned char lds[];
-  TileCoord tc;
-  if (!decode_tile<true>(p, tc)) return;
-  ffn_ring_sum_tile<BM, GATED, WM, WN>(p, tc, lds);
 }
 
 // --------------------------------------------------------------------------------------------
@@ -646,25 +645,23 @@ __global__ __launch_bounds__(WM * WN * 64) void ffn_ring_sum_parts_kernel(GemmAr
 // k-step: by then every fragment of the stage is in registers, the stage's buffer takes the loads
 // of the stage after next, and the other buffer (landed: vmcnt(0)) is read from.
 //
-// Who issues the loads (ALTERNATE).  A wave that issues a burst of direct-to-LDS loads is held at every one of
+// Who issues the loads.  A wave that issues a burst of direct-to-LDS loads is held at every one of
 // them until the address unit takes it, and issues no MFMA meanwhile.  If all eight waves load
 // their eighth of a stage right after the barrier, both waves of every SIMD are held at once and
-// the matrix pipe idles.  With ALTERNATE the waves form two sets of four, {0-3} and {4-7}
-// (waves w and w + 4 share a SIMD), that take turns: set (stage & 1) issues the whole stage while
-// the other set goes straight on with its MFMAs, so every SIMD always has a wave that multiplies.
-// Measured on the Mixtral shape: up-projection 6 % faster.  Calls whose experts hold a single tile
-// each (nothing shares a weight tile through the L2, the call waits on HBM) are faster with every
-// wave loading; the host chooses by the mean rows per expert.
+// the matrix pipe idles.  So the waves form two sets of four, {0-3} and {4-7} (waves w and w + 4 share
+// a SIMD), that take turns: set (stage & 1) issues the whole stage while the other set goes
+// straight on with its MFMAs, so every SIMD always has a wave that multiplies.  Measured on the
+// Mixtral shape: up-projection 6 % faster than with every wave loading; llama4 shape (one tile of 256
+// rows per expert) 690 -> 646 us with three weight buffers and turns.  (One set for the weight
+// rows and the other for the activation rows: 12 to 20 % slower on tiles of 65 to 128 rows.)
 constexpr int EVEN_BM = 320;
 constexpr int EVEN_ACT = EVEN_BM * ROWB;                     // one activation buffer
 constexpr int EVEN_WGT = BROWS * ROWB;                       // one weight buffer
-// Tiles of at most RING_ROWS rows (a small expert of a skewed batch, beside experts that hold several
-// full tiles) run the ring pipeline inside the same launch: they have little arithmetic per weight
-// byte and are paced by memory latency, which the ring's three stages in flight hide best.
-constexpr int RING_ROWS = 64;
-constexpr int EVEN_LDS = ffn_ring_lds_bytes(RING_ROWS, 4) > 2 * (EVEN_ACT + EVEN_WGT)
-                             ? ffn_ring_lds_bytes(RING_ROWS, 4) : 2 * (EVEN_ACT + EVEN_WGT);
+constexpr int FFN_LDS = ffn_ring_lds_bytes(RING_ROWS, BROWS, 4) > 2 * (EVEN_ACT + EVEN_WGT)
+                             ? ffn_ring_lds_bytes(RING_ROWS, BROWS, 4) : 2 * (EVEN_ACT + EVEN_WGT);
 
+// LDS of an even tile: two activation buffers of 64 MI rows and as many weight buffers as fit beside them.
+constexpr int even_wgt_buffers(int mi) { return mi <= 2 ? 4 : mi <= 4 ? 3 : 2; }
 // How the tile's sub-tiles are dealt to wave row wm (of 4): count and first row.
 __device__ __forceinline__ void even_wave_rows(int rows_valid, int wm, int& miv, int& row0) {
   const int nsub = (rows_valid + 15) >> 4;
@@ -673,32 +670,36 @@ __device__ __forceinline__ void even_wave_rows(int rows_valid, int wm, int& miv,
   row0 = 16 * (wm * q + min(wm, r));
 }
 
-// MI: 16-row sub-tiles a wave can hold.  MI = 5: tiles of up to 320 rows, two activation and two weight
-// buffers (144 KiB).  MI = 4: tiles of up to 256 rows; the 16 KiB the activation buffers give back
-// make a third weight buffer (160 KiB), and the weight rows are requested a stage earlier than the
-// activation rows: they are the operand that misses the L2 (an XCD's tiles share activation
-// rows far more often than weight rows), so their requests take longest to return.
-template <bool GATED, bool SPLIT, bool ALTERNATE, bool WNT, bool RAGGED, int MI>
+// MI: 16-row sub-tiles a wave can hold.  MI = 5: tiles of up to 320 rows, two weight buffers (144 KiB).
+// MI = 4: tiles of up to 256 rows; the 16 KiB the activation buffers give back make a third weight
+// buffer (160 KiB), and the weight rows are requested a stage earlier than the activation rows:
+// they are the operand that misses the L2 (an XCD's tiles share activation rows far more often
+// than weight rows), so their requests take longest to return.  MI = 2: tiles of up to 128 rows, bound by
+// the weight stream; a fourth weight buffer, and with the two sets of waves taking turns a weight
+// request has three stage times to return (each set waits for its own requests only, and its next
+// ones, whose activation rows are due a stage later, come two stages on).
+// (Measured against two or more 64-row ring tiles per expert, up-projection: Mixtral shape at 500
+// tokens 512 -> 350 us, 5.4 TB/s of weights, phi shape at 600 tokens 385 -> 313 us, 64-expert shape at 1024
+// tokens 186 -> 148 us.)
+template <bool GATED, bool SPLIT, bool WNT, bool RAGGED, int MI>
 __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord& tc, unsigned char* lds) {
   constexpr int NW = 8, WN = 2;
   constexpr int BM = MI * 64, NI = 8;
   constexpr int NIH = GATED ? NI / 2 : NI;
   constexpr int NLA = BM / 8 / 4;                 // up to 10 activation row groups per loading wave and stage
   constexpr int NLW = BROWS / 8 / 4;              // up to 8 weight row groups
-  constexpr int BN_OUT = GATED ? 128 : 256;
   constexpr int ACT = BM * ROWB;                  // one activation buffer
-  constexpr int NWB = MI == 4 ? 3 : 2;            // weight buffers
+  constexpr int NWB = even_wgt_buffers(MI);
   constexpr int W_BASE = 2 * ACT;                 // LDS offset of the weight buffers
-  static_assert(MI == 4 || MI == 5, "wave tile");
-  static_assert(W_BASE + NWB * EVEN_WGT <= EVEN_LDS, "LDS budget");
+  static_assert(MI == 2 || MI == 4 || MI == 5, "wave tile");
+  static_assert(W_BASE + NWB * EVEN_WGT <= FFN_LDS, "LDS budget");
 
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MOE_WAVE);
   const int wm = wave / WN, wn = wave % WN;
-  constexpr bool alternate = ALTERNATE;
-  constexpr int ns = alternate ? 4 : 8;           // waves that share a stage's loads
-  const int lw = alternate ? (wave & 3) : wave;   // this wave's place among them
-  const int lset = alternate ? (wave >> 2) : 0;   // ... and the stages it loads: stage & 1 == lset
+  constexpr int ns = 4;                           // waves that share a stage's loads
+  const int lw = wave & 3;                        // this wave's place among them
+  const int lset = wave >> 2;                     // ... and the stages it loads: stage & 1 == lset
   const int K = p.K, N = p.N;
   int KT = RAGGED ? (K + BK - 1) / BK : K / BK, k_first = 0;   // this block's K stages
   if (SPLIT && tc.nparts > 1) {
@@ -706,7 +707,7 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
     KT = (tc.part + 1) * KT / tc.nparts - kt_first;
     k_first = kt_first * BK;
   }
-  const int n0 = tc.n_tile * BN_OUT;
+  const int n0 = tc.n0;
   const int rows_valid = min(tc.m_end - tc.m_begin, BM);
   int miv, row0;
   even_wave_rows(rows_valid, wm, miv, row0);
@@ -742,11 +743,10 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
   // (the row groups a lane loads, of either operand, are an even number of groups apart: one chunk)
   const uint32_t tail = RAGGED ? ragged_tail(K, (lane & 7) ^ swz(lw * 8 + (lane >> 3))) : 0u;
   // The activation rows of stage kt go to activation buffer kt % 2 and are requested two stages
-  // ahead, the weight rows to weight buffer kt % NWB, NWB stages ahead.  With ALTERNATE the requests
-  // made after the barrier of stage j (activations of j + 2, weights of j + NWB) all come from
-  // wave set j & 1.
+  // ahead, the weight rows to weight buffer kt % NWB, NWB stages ahead.  The requests made after the
+  // barrier of stage j (activations of j + 2, then weights of j + NWB) all come from wave set j & 1.
   auto issue_act = [&](int kt) {
-    if (alternate && lset != (kt & 1)) return;
+    if (lset != (kt & 1)) return;
     const uint32_t past = RAGGED && kt == KT - 1 ? tail : 0u;
 #pragma unroll
     for (int i = 0; i < NLA; ++i)
@@ -795,7 +795,7 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
     }
   };
   auto issue_wgt = [&](int kt, int wb) {
-    if (alternate && lset != ((kt + NWB) & 1)) return;
+    if (lset != ((kt + NWB) & 1)) return;
     if (wgt_nt)
       issue_wgt_with(kt, wb, std::integral_constant<int, 2>{});    // aux bit 1: nt
     else
@@ -876,10 +876,15 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
       part1();
       part2(K1{}, std::integral_constant<int, PAR>{}, wa[1] + wb * EVEN_WGT);
       part1();
-      // Stage kt + 1 must have landed.  Requests return in order, and the last ones this wave made
-      // (after the barrier of stage kt - 1, if it was its turn) were the activation rows of kt + 1,
-      // then, with three weight buffers, the weight rows of kt + 2: those may stay in flight.
-      if (NWB == 3 && kt >= 1 && kt + 2 < KT && (!alternate || lset == ((kt - 1) & 1)))
+      // Stage kt + 1 must have landed.  Requests return in order, and the last ones of the set whose turn
+      // it was after the barrier of stage kt - 1 are the activation rows of kt + 1, then the weight
+      // rows of kt - 1 + NWB: with three buffers or more those may stay in flight.  The last ones of the
+      // other set are a stage older: weight rows of kt - 2 + NWB, which four buffers spare too.
+      const bool turn = lset == ((kt - 1) & 1);
+      bool spare = false;
+      if constexpr (NWB == 3) spare = kt >= 1 && kt + 2 < KT && turn;
+      if constexpr (NWB == 4) spare = kt + (turn ? 3 : 2) < KT;
+      if (NWB >= 3 && spare)
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"i"(W_LOADS) : "memory");
       else
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -911,32 +916,48 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
     asm volatile("s_nop 15\n s_nop 15\n s_nop 15\n s_nop 15" ::: "memory");
   };
 
-  // prologue: stages 0 and 1 requested, the weight rows first: their addresses need no memory, while
-  // the activation rows of a call that reads x through the map wait for the map entries, a trip to
-  // memory that now overlaps the weights'.  Everything this wave requested has landed before the
-  // first barrier (a count that spared stage 1 would depend on how many groups the wave skipped).
+  // prologue: the map entries of a call that reads x through the map are requested first, the weight rows,
+  // whose addresses need no memory, while they travel, then the activation rows of stages 0 and 1.
+  // With four weight buffers the weight rows of stages 2 and 3 come last and stay in flight over
+  // the first barrier, in the order in which the k loop goes on.
 #pragma unroll
-  for (int s = 0; s < NWB; ++s)
+  for (int i = 0; i < NLA; ++i) {
+    const int r = min((i * ns + lw) * 8 + (lane >> 3), rows_valid - 1);
+    soff_a[i] = static_cast<uint32_t>(gathered ? p.src_assign[tc.m_begin + r] : r);
+  }
+#pragma unroll
+  for (int s = 0; s < (NWB == 4 ? 2 : NWB); ++s)
     if (s < KT) issue_wgt(s, s);
 #pragma unroll
   for (int i = 0; i < NLA; ++i) {
-    const int row = (i * ns + lw) * 8 + (lane >> 3);
-    const int chunk = (lane & 7) ^ swz(row);      // the chunk of the row this lane fetches
-    int r = min(row, rows_valid - 1);
-    if (gathered) r = a_row_of(p, tc.m_begin + r);
+    const int chunk = (lane & 7) ^ swz((i * ns + lw) * 8 + (lane >> 3));   // the chunk of the row this lane fetches
+    int r = static_cast<int>(soff_a[i]);
+    if (gathered) r = min(max(r / p.k_div, 0), p.a_rows - 1);
     soff_a[i] = static_cast<uint32_t>(r) * static_cast<uint32_t>(K) * 2u + static_cast<uint32_t>(chunk) * 16u;
   }
   issue_act(0);
   if (KT > 1) issue_act(1);
-  wait_vmcnt<0>();
+  if (NWB == 4) {
+#pragma unroll
+    for (int s = 2; s < NWB; ++s)
+      if (s < KT) issue_wgt(s, s);
+  }
+  if (NWB == 4 && KT >= NWB)
+    asm volatile("s_waitcnt vmcnt(%0)" ::"i"(W_LOADS) : "memory");
+  else
+    wait_vmcnt<0>();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   switch (miv) {                                  // wave-uniform
     case 0: k_loop(std::integral_constant<int, 0>{}); break;
     case 1: k_loop(std::integral_constant<int, 1>{}); break;
     case 2: k_loop(std::integral_constant<int, 2>{}); break;
-    case 3: k_loop(std::integral_constant<int, 3>{}); break;
-    case 4: k_loop(std::integral_constant<int, 4>{}); break;
+    case 3:
+      if constexpr (MI >= 3) k_loop(std::integral_constant<int, 3>{});
+      break;
+    case 4:
+      if constexpr (MI >= 4) k_loop(std::integral_constant<int, 4>{});
+      break;
     default:
       if constexpr (MI >= 5) k_loop(std::integral_constant<int, 5>{});
       break;
@@ -955,27 +976,44 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
   ffn_store_tile<GATED, MI, NI, WN, NW>(acc, tc, p, lds, wave, lane, miv, row0);
 }
 
-// Tiles of at most this many rows of the down-projection take the form with three weight buffers.
-// (Measured on uniform batches at the Mixtral shape, 768 and 1024 rows per expert: the
-// down-projection, whose reduction is 14336 long, 11 % and 4.5 % faster; the up-projection, 4096
-// long, 1 % slower, so it keeps two weight buffers for every tile.)
-constexpr int EVEN_ROWS_3WB = 256;
+// Which pipeline a tile of `rows` rows takes: sub-tiles per wave (MI) of the even tile, 0 for a ring tile.
+// The more weight buffers the better where the weight rows come from HBM.  Where experts hold several
+// tiles each (!WNT), the tiles share them through the L2, and only the down-projection, whose
+// reduction is the longer one, gains from the third buffer.  (Measured: Mixtral shape at 192 rows per
+// expert, up-projection 434 -> 389 us with three; at 1024 rows 1 % slower, down-projection 4.5 %
+// faster; skewed 64-expert layer of 8192 tokens, the cold experts' tiles with four, up-projection
+// 1 % slower.)
+template <bool GATED, bool WNT> __device__ __forceinline__ int tile_mi(int rows) {
+  return rows <= RING_ROWS ? 0 : WNT && rows <= 128 ? 2 : (WNT || !GATED) && rows <= 256 ? 4 : 5;
+}
 
-template <bool GATED, bool SPLIT, bool ALTERNATE, bool WNT, bool RAGGED>
-__global__ __launch_bounds__(512) void ffn_even_kernel(GemmArgs p) {
+template <bool GATED, bool SPLIT, bool WNT, bool RAGGED>
+__global__ __launch_bounds__(512) void ffn_bf16_kernel(GemmArgs p) {
   extern __shared__ __align__(1024) unsigned char lds[];
+  static_assert(ffn_ring_lds_bytes(RING_ROWS, 64, 9) <= FFN_LDS && ffn_ring_lds_bytes(RING_ROWS, 128, 6) <= FFN_LDS &&
+                    ffn_ring_lds_bytes(NSPLIT_ROWS, 128, 5) <= FFN_LDS, "pieces' rings fit the launch's LDS");
   TileCoord tc;
   if (!decode_tile<SPLIT>(p, tc)) return;
   const int rows = tc.m_end - tc.m_begin;         // block-uniform
-  if (rows <= RING_ROWS)
-    ffn_ring_tile<RING_ROWS, GATED, 2, 4, 4, SPLIT, RAGGED>(p, tc, lds);
-  else if (!GATED && rows <= EVEN_ROWS_3WB)
-    ffn_even_tile<GATED, SPLIT, ALTERNATE, WNT, RAGGED, 4>(p, tc, lds);
-  else
-    ffn_even_tile<GATED, SPLIT, ALTERNATE, WNT, RAGGED, 5>(p, tc, lds);
+  if (!SPLIT && tc.n_pieces == 4)
+    ffn_ring_tile<RING_ROWS, 64, GATED, 4, 2, 9, false, WNT, RAGGED>(p, tc, lds);
+  else if (!SPLIT && tc.n_pieces == 2 && rows <= RING_ROWS)
+    ffn_ring_tile<RING_ROWS, 128, GATED, 2, 4, 6, false, WNT, RAGGED>(p, tc, lds);
+  else if (!SPLIT && tc.n_pieces == 2)
+    ffn_ring_tile<NSPLIT_ROWS, 128, GATED, 2, 4, 5, false, WNT, RAGGED>(p, tc, lds);
+  else switch (tile_mi<GATED, WNT>(rows)) {
+    case 0: ffn_ring_tile<RING_ROWS, BROWS, GATED, 2, 4, 4, SPLIT, WNT, RAGGED>(p, tc, lds); break;
+    case 2:
+      if constexpr (WNT) ffn_even_tile<GATED, SPLIT, WNT, RAGGED, 2>(p, tc, lds);
+      break;
+    case 4:
+      if constexpr (WNT || !GATED) ffn_even_tile<GATED, SPLIT, WNT, RAGGED, 4>(p, tc, lds);
+      break;
+    default: ffn_even_tile<GATED, SPLIT, WNT, RAGGED, 5>(p, tc, lds); break;
+  }
 }
 
-// The launch after ffn_even_kernel<.., SPLIT>: adds the parts of every split tile and stores it.
+// The launch after ffn_bf16_kernel<.., SPLIT>: adds the parts of every split tile and stores it.
 template <bool GATED, int MI>
 __device__ __forceinline__ void ffn_even_sum_tile(const GemmArgs& p, const TileCoord& tc, unsigned char* lds) {
   constexpr int NW = 8, WN = 2, NI = 8;
@@ -987,18 +1025,21 @@ __device__ __forceinline__ void ffn_even_sum_tile(const GemmArgs& p, const TileC
   ffn_sum_parts<MI, NI, NW * MOE_WAVE>(acc, tc, p);
   ffn_store_tile<GATED, MI, NI, WN, NW>(acc, tc, p, lds, wave, lane, miv, row0);
 }
-template <bool GATED>
-__global__ __launch_bounds__(512) void ffn_even_sum_parts_kernel(GemmArgs p) {
+template <bool GATED, bool WNT>
+__global__ __launch_bounds__(512) void ffn_bf16_sum_parts_kernel(GemmArgs p) {
   extern __shared__ __align__(1024) unsigned char lds[];
   TileCoord tc;
   if (!decode_tile<true>(p, tc)) return;
-  const int rows = tc.m_end - tc.m_begin;
-  if (rows <= RING_ROWS)                          // its parts came from the ring pipeline
-    ffn_ring_sum_tile<RING_ROWS, GATED, 2, 4>(p, tc, lds);
-  else if (!GATED && rows <= EVEN_ROWS_3WB)
-    ffn_even_sum_tile<GATED, 4>(p, tc, lds);
-  else
-    ffn_even_sum_tile<GATED, 5>(p, tc, lds);
+  switch (tile_mi<GATED, WNT>(tc.m_end - tc.m_begin)) {
+    case 0: ffn_ring_sum_tile<RING_ROWS, GATED, 2, 4>(p, tc, lds); break;
+    case 2:
+      if constexpr (WNT) ffn_even_sum_tile<GATED, 2>(p, tc, lds);
+      break;
+    case 4:
+      if constexpr (WNT || !GATED) ffn_even_sum_tile<GATED, 4>(p, tc, lds);
+      break;
+    default: ffn_even_sum_tile<GATED, 5>(p, tc, lds); break;
+  }
 }
 
 // --------------------------------------------------------------------------------------------
@@ -1009,7 +1050,7 @@ __global__ __launch_bounds__(512) void ffn_even_sum_parts_kernel(GemmArgs p) {
 // which spreads the few hundred tiles of a small batch over the chip and lets one block's barriers
 // and epilogue overlap the others' loops.  Each wave takes all the tile's 16-row sub-tiles against
 // its own 16 weight rows of each matrix, so the waves are equally busy whatever the row count is;
-// segments are cut evenly (TILES_EVEN), so 129 rows are 48 + 48 + 33 and not 64 + 64 + 1.  K step 32
+// segments are cut evenly, so 129 rows are 48 + 48 + 33 and not 64 + 64 + 1.  K step 32
 // (128-byte tile rows as in the bf16 kernels, the same swizzle and chunk order; a chunk is four
 // k-values, one per instruction).  Bound by the matrix pipe where there are tiles enough (8000 tokens,
 // d = 1024, E = 16, k = 2, F = 2048: 125 TFLOP/s, the vendor's fp32 GEMM of that size 141), by the
@@ -1033,7 +1074,7 @@ __global__ __launch_bounds__(F32_NW * MOE_WAVE, 3) void ffn_f32_kernel(GemmArgs 
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MOE_WAVE);
   const int K = p.K, N = p.N, KT = (K + F32_BK - 1) / F32_BK;
-  const int n0 = tc.n_tile * F32_BN;
+  const int n0 = tc.n0;
   const int rows_valid = min(tc.m_end - tc.m_begin, BM);
   const bool gathered = p.src_assign != nullptr;
   const float* A = static_cast<const float*>(p.a) + (gathered ? 0 : static_cast<int64_t>(tc.m_begin) * K);
@@ -1175,12 +1216,11 @@ constexpr int SPLIT_MIN_K = 96 * BK_ELEMS;
 // One grouped GEMM.  main_kernel: void (*)(GemmArgs); the grid is an upper bound of the tile count
 // (surplus blocks exit at once), plus a round of blocks for the parts when tiles may be split; the
 // summing kernel (one block per possible split tile) follows on the same stream.
-static int launch_grouped_gemm(GemmArgs a, int mode, int bm, int64_t A, int threads, int lds_bytes,
+static int launch_grouped_gemm(GemmArgs a, int bm, int64_t A, int threads, int lds_bytes,
                                void (*main_kernel)(GemmArgs), LdsOnce& once_main,
                                void (*sum_kernel)(GemmArgs), LdsOnce& once_sum, hipStream_t st) {
   if (ensure_dynamic_lds(once_main, reinterpret_cast<const void*>(main_kernel), lds_bytes) != MOE_OK)
     return MOE_ERR_HIP;
-  a.mode = mode;
   a.bm = bm;
   a.split_phase = 0;
   if (!sum_kernel) a.split_ws = nullptr;
@@ -1188,7 +1228,7 @@ static int launch_grouped_gemm(GemmArgs a, int mode, int bm, int64_t A, int thre
   if (grid == 0) return MOE_OK;
   grid = (grid + 7) / 8 * 8;
   const int cu8 = (a.n_cu > 0 ? a.n_cu : 256) / 8 * 8;
-  if (sum_kernel || a.m_split) grid += cu8;
+  if (sum_kernel || a.tail_split) grid += cu8;
   if (grid > 0x7FFFFFFF) return MOE_ERR_UNSUPPORTED;
   hipLaunchKernelGGL(main_kernel, dim3(static_cast<unsigned>(grid)), dim3(threads), lds_bytes, st, a);
   int rc = launch_status();
@@ -1205,36 +1245,29 @@ static int launch_grouped_gemm(GemmArgs a, int mode, int bm, int64_t A, int thre
 // Shapes the RAGGED kernels take (they are not cut along K: a workspace is ignored).
 static bool ragged(const GemmArgs& a) { return a.K % BK_ELEMS != 0 || a.N % BK_ELEMS != 0; }
 
-template <bool GATED, bool ALTERNATE, bool WNT>
-static int launch_even(const GemmArgs& a, int64_t A, bool row_split, hipStream_t st) {
-  static LdsOnce once[2], once_ragged, once_sum;
-  GemmArgs b = a;
-  b.m_split = row_split ? 1 : 0;
-  if (ragged(a))
-    return launch_grouped_gemm(b, TILES_EVEN, EVEN_BM, A, 512, EVEN_LDS,
-                               ffn_even_kernel<GATED, false, ALTERNATE, true, true>, once_ragged, nullptr, once_sum, st);
-  if (a.split_ws && a.K >= SPLIT_MIN_K)
-    return launch_grouped_gemm(a, TILES_EVEN, EVEN_BM, A, 512, EVEN_LDS,
-                               ffn_even_kernel<GATED, true, ALTERNATE, WNT, false>, once[1],
-                               ffn_even_sum_parts_kernel<GATED>, once_sum, st);
-  return launch_grouped_gemm(b, TILES_EVEN, EVEN_BM, A, 512, EVEN_LDS,
-                             ffn_even_kernel<GATED, false, ALTERNATE, WNT, false>, once[0], nullptr, once_sum, st);
-}
+// Most rows of a bf16 tile, by the mean rows per expert.  Below 128 rows most experts are one tile under
+// either limit; what the limit changes is a hot expert of a skewed batch, whose few high tiles would be the
+// launch's longest.  (Measured, whole layer, limit 320 against the one below: skewed 64-expert layer at
+// 512 / 680 tokens, 48 and 64 rows per expert, 270 / 311 -> 244 / 267 us; at 1024 tokens, 96 rows,
+// 342 -> 317 us with 192; unskewed layers within 1 %.  With 192 up to 192 rows per expert the
+// 128-expert layer at 2500 tokens is 4 % slower.)
+static int most_tile_rows(int64_t mean_rows) { return mean_rows < 96 ? 128 : mean_rows < 128 ? 192 : EVEN_BM; }
 
-template <bool GATED>
-static int launch_ring(const GemmArgs& a, int64_t A, hipStream_t st) {
-  constexpr int BM = 64, WM = 2, WN = 4, NSTAGE = 4;
-  constexpr int lds_bytes = ffn_ring_lds_bytes(BM, NSTAGE);
+template <bool GATED, bool WNT>
+static int launch_bf16(const GemmArgs& a, int64_t A, bool row_split, hipStream_t st) {
   static LdsOnce once[2], once_ragged, once_sum;
+  const int bm = most_tile_rows(A / a.E);
+  GemmArgs b = a;
+  b.tail_split = row_split ? 1 : 0;
   if (ragged(a))
-    return launch_grouped_gemm(a, TILES_FIXED, BM, A, WM * WN * 64, lds_bytes,
-                               ffn_ring_kernel<BM, GATED, WM, WN, NSTAGE, false, true>, once_ragged, nullptr, once_sum, st);
+    return launch_grouped_gemm(b, bm, A, 512, FFN_LDS,
+                               ffn_bf16_kernel<GATED, false, true, true>, once_ragged, nullptr, once_sum, st);
   if (a.split_ws && a.K >= SPLIT_MIN_K)
-    return launch_grouped_gemm(a, TILES_FIXED, BM, A, WM * WN * 64, lds_bytes,
-                               ffn_ring_kernel<BM, GATED, WM, WN, NSTAGE, true, false>, once[1],
-                               ffn_ring_sum_parts_kernel<BM, GATED, WM, WN>, once_sum, st);
-  return launch_grouped_gemm(a, TILES_FIXED, BM, A, WM * WN * 64, lds_bytes,
-                             ffn_ring_kernel<BM, GATED, WM, WN, NSTAGE, false, false>, once[0], nullptr, once_sum, st);
+    return launch_grouped_gemm(a, bm, A, 512, FFN_LDS,
+                               ffn_bf16_kernel<GATED, true, WNT, false>, once[1],
+                               ffn_bf16_sum_parts_kernel<GATED, WNT>, once_sum, st);
+  return launch_grouped_gemm(b, bm, A, 512, FFN_LDS,
+                             ffn_bf16_kernel<GATED, false, WNT, false>, once[0], nullptr, once_sum, st);
 }
 
 // 32-row tiles while 64-row tiles would be fewer than 16 per CU (measured, both GEMMs, d = 1024, E = 16,
@@ -1243,21 +1276,16 @@ static int launch_ring(const GemmArgs& a, int64_t A, hipStream_t st) {
 template <bool GATED>
 static int launch_f32(GemmArgs a, int64_t A, hipStream_t st) {
   static LdsOnce once[2], once_sum;
+  a.bn = F32_BN;
   a.n_tiles = (a.N + F32_BN - 1) / F32_BN;
   const int64_t tiles64 = (A + 63) / 64 * a.n_tiles;
   if (tiles64 < 16 * static_cast<int64_t>(a.n_cu > 0 ? a.n_cu : 256))
-    return launch_grouped_gemm(a, TILES_EVEN, 32, A, F32_NW * MOE_WAVE, ffn_f32_lds_bytes(GATED, 32),
+    return launch_grouped_gemm(a, 32, A, F32_NW * MOE_WAVE, ffn_f32_lds_bytes(GATED, 32),
                                ffn_f32_kernel<GATED, 32>, once[0], nullptr, once_sum, st);
-  return launch_grouped_gemm(a, TILES_EVEN, 64, A, F32_NW * MOE_WAVE, ffn_f32_lds_bytes(GATED, 64),
+  return launch_grouped_gemm(a, 64, A, F32_NW * MOE_WAVE, ffn_f32_lds_bytes(GATED, 64),
                              ffn_f32_kernel<GATED, 64>, once[1], nullptr, once_sum, st);
 }
 
-// Mean rows per expert from which the even tiles take over from the ring tiles, and from which the
-// waves of a SIMD take turns loading (two or more tiles of an expert then share each weight tile
-// through the L2; measured on five layer shapes: 4 to 6 % faster from 512 rows per expert on, 2 %
-// slower at 256, where each expert is a single tile).
-constexpr int EVEN_MIN_ROWS = 128;
-constexpr int ALTERNATE_MIN_ROWS = 384;
 // Mean rows per expert below which the kernels are built with the per-tile choice of the
 // non-temporal hint for weight rows (experts of at most two tiles are then the rule).
 constexpr int WGT_NT_ROWS = 2 * EVEN_BM;
@@ -1266,26 +1294,12 @@ constexpr int WGT_NT_ROWS = 2 * EVEN_BM;
 static int mfma_ffn(GemmArgs g1, GemmArgs g2, bool up, bool down, int64_t A, bool row_split,
                     hipStream_t st) {
   int rc = MOE_OK;
-  if (A / g1.E < EVEN_MIN_ROWS) {
-    // Few rows per expert (decode, small prefill batches): the call is bound by streaming each
-    // expert's weights once, which the latency-hiding ring of the 64-row tiles does best.
-    // (Measured, whole layer, ring tiles against even tiles for every expert: Mixtral shape 64 / 96
-    // rows per expert 0.60 / 0.63 ms against 0.70 / 0.74; skewed 64-expert layer at 256 ... 1280
-    // tokens, where a hot expert holds ten times the mean, 0.22 ... 0.39 ms against 0.27 ... 0.41;
-    // only the fine-grained layer at 96 rows per expert is faster with even tiles, 0.28 against 0.33 ms.)
-    if (up && (rc = launch_ring<true>(g1, A, st)) != MOE_OK) return rc;
-    if (down) rc = launch_ring<false>(g2, A, st);
-    return rc;
-  }
   if (A / g1.E >= WGT_NT_ROWS) {
-    if (up && (rc = launch_even<true, true, false>(g1, A, row_split, st)) != MOE_OK) return rc;
-    if (down) rc = launch_even<false, true, false>(g2, A, row_split, st);
-  } else if (A / g1.E >= ALTERNATE_MIN_ROWS) {
-    if (up && (rc = launch_even<true, true, true>(g1, A, row_split, st)) != MOE_OK) return rc;
-    if (down) rc = launch_even<false, true, true>(g2, A, row_split, st);
+    if (up && (rc = launch_bf16<true, false>(g1, A, row_split, st)) != MOE_OK) return rc;
+    if (down) rc = launch_bf16<false, false>(g2, A, row_split, st);
   } else {
-    if (up && (rc = launch_even<true, false, true>(g1, A, row_split, st)) != MOE_OK) return rc;
-    if (down) rc = launch_even<false, false, true>(g2, A, row_split, st);
+    if (up && (rc = launch_bf16<true, true>(g1, A, row_split, st)) != MOE_OK) return rc;
+    if (down) rc = launch_bf16<false, true>(g2, A, row_split, st);
   }
   return rc;
 }
@@ -1314,16 +1328,18 @@ static int grouped_ffn_impl(const moe_shape_t* shape, const void* x_perm, const 
   const int64_t A = static_cast<int64_t>(shape->T) * shape->k;
   const int d = shape->d, F = shape->F, E = shape->E;
   const int n_cu = device_cu_count();
-  GemmArgs g1{x_perm, w1, w3, h, offsets, E, d, F, 0, static_cast<int>(A), TILES_FIXED, 64,
+  GemmArgs g1{x_perm, w1, w3, h, offsets, E, d, F, 0, 0, static_cast<int>(A), EVEN_BM,
               src_assign, shape->k, src_assign ? shape->T : static_cast<int>(A), n_cu,
               static_cast<float*>(split_ws), 0, nullptr, nullptr, 0};
-  GemmArgs g2{h, w2, nullptr, y_perm, offsets, E, F, d, 0, static_cast<int>(A), TILES_FIXED, 64,
+  GemmArgs g2{h, w2, nullptr, y_perm, offsets, E, F, d, 0, 0, static_cast<int>(A), EVEN_BM,
               nullptr, 1, static_cast<int>(A), n_cu, static_cast<float*>(split_ws), 0,
               combine_w ? src_assign : nullptr, combine_w, shape->T};
   const bool up = parts & 1, down = parts & 2;
   if (shape->dtype == MOE_BF16) {
-    g1.n_tiles = (F + 127) / 128;
-    g2.n_tiles = (d + 255) / 256;
+    g1.bn = 128;
+    g2.bn = 256;
+    g1.n_tiles = (F + g1.bn - 1) / g1.bn;
+    g2.n_tiles = (d + g2.bn - 1) / g2.bn;
     return mfma_ffn(g1, g2, up, down, A, row_split, st);
   }
   if (up) {

@@ -568,6 +568,17 @@ def test_grouped_ffn_even_tiles_every_wave_share(rows):
         check_ffn(cfg, L, idx)
 
 
+@pytest.mark.parametrize("d", [64, 128, 192, 256, 320, 448, 520, 704])
+@pytest.mark.parametrize("E,rows,F", [(3, 50, 200), (4, 64, 640), (20, 33, 640), (20, 100, 640), (5, 128, 328), (6, 129, 192)])
+def test_grouped_ffn_pieces_of_low_tiles(E, rows, F, d):
+    # low tiles of an under-filled round: quarters (E = 3, 4) and halves (E = 20, 81 to 128 tiles) of the
+    # weight rows, pieces past the end of the matrix, on either side of the 64- and 128-row limits; whole
+    # (the second form gpu_ffn runs) they take the ring and the three and four weight buffers.  1 to 11
+    # stages, below and above every ring's depth; widths with K and N tails.
+    cfg = si.small_config(T=E * rows, d=d, E=E, k=1, F=F, seed=d + F + rows)
+    check_ffn(cfg, si.make_layer(cfg), np.repeat(np.arange(E, dtype=np.int32), rows)[:, None])
+
+
 ROUND_CASES = [
     # (rows per expert, d, F): enough tiles for whole rounds of the chip's 256 compute units plus a
     # last round that is under-filled (its tiles are cut along their rows), just over half full
