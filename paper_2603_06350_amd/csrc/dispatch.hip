@@ -3,8 +3,8 @@
 // of the T*k assignments and the row gather that realises the single-GPU "scatter"
 // of Section 2.2.
 //
-// Three launches on the caller's stream (two for batches of at most 256 assignments, where
-// rank_small_kernel replaces 1 and 2), no host synchronisation:
+// Three launches on the caller's stream (batches of up to DR_MAX_A assignments: rank_direct_kernel
+// replaces all three), no host synchronisation:
 //   1. hist_kernel   one thread per token; LDS histogram of the block's
 //                    assignments -> partial[block][expert]              (integer)
 //   2. rank_kernel   same token partition.  Every block sums `partial` to get
@@ -177,73 +177,103 @@ __global__ __launch_bounds__(NTH) void rank_kernel(const int32_t* __restrict__ t
   }
 }
 
-// Small batches (T*k <= RS_MAX_A): one block does the whole dispatch.  The rank of an assignment
-// is counted directly, as the number of earlier assignments of the same expert (all assignments
-// sit in LDS and are read as broadcasts), so there is no table to clear or scan and one launch
-// replaces two.
-// Measured: 8.5 us for 256 assignments against 10.5 - 16 us for the two launches, but 20 us for 384
-// and 97 us for 1024 (the count is quadratic), where the two launches still take 11 - 17 us.
-constexpr int RS_MAX_A = 256;
-__global__ __launch_bounds__(256) void rank_small_kernel(const int32_t* __restrict__ topk_idx, int A,
-                                                         int E, int32_t* __restrict__ counts,
-                                                         int32_t* __restrict__ offsets,
-                                                         int32_t* __restrict__ dst_row,
-                                                         int32_t* __restrict__ src_assign) {
-  __shared__ __align__(16) int32_t idx[RS_MAX_A];
-  __shared__ int32_t cnt[MOE_MAX_E];
-  __shared__ int32_t off[MOE_MAX_E + 1];
-  const int tid = threadIdx.x;
-  const int lane = tid & (MOE_WAVE - 1);
-  for (int e = tid; e < E; e += 256) cnt[e] = 0;
-  for (int a = tid; a < RS_MAX_A; a += 256) {
-    int e = a < A ? topk_idx[a] : -1;
-    if (static_cast<unsigned>(e) >= static_cast<unsigned>(E)) e = -1;   // invalid: never matches
-    idx[a] = e;
+// Batches of up to DR_MAX_A assignments: one launch does the whole dispatch.  The place of assignment a
+// with expert e is the number of assignments b with (expert, b) < (e, a) in lexicographic order, so with
+// keys expert << 13 | b it is a plain count of smaller keys, and offsets[e] is the same count for the key
+// e << 13: no histogram, no table, no second launch.  Every block keeps all keys in LDS; a wave
+// answers two queries in one walk over them (two vector instructions per query and 64 keys), waves
+// past the assignments those of expert e and e + 1.  With x_perm a wave also copies the rows of its two
+// assignments (COPY).  The count is quadratic: bound by latency up to about 4000 assignments, by the
+// vector pipe above.  (Measured, assignments: hist + rank_kernel -> this, us: 1000 (8 experts)
+// 9.5 -> 4.8, 4503 (12) 10.1 -> 6.4, 6000 (64) 14.6 -> 7.4, 8192 (8) 9.5 -> 10.0, which sets
+// DR_MAX_A; against the one-block kernel that batches of up to 256 took, 256 of 128 experts
+// 9.0 -> 4.9; with the row copy, hist + rank + gather_kernel -> this: 2000 assignments, 4 KiB rows, 29.7 ->
+// 11.5, 4503, 2 KiB rows, 30.1 -> 16.7, 6000, 8 KiB rows, 46.5 -> 35.6; two or four 16-byte loads per
+// lane and row in flight instead of one: up to 4 us slower.  Four queries per wave: up to 0.8 us slower.)
+constexpr int DR_THREADS = 512;
+constexpr int DR_KEY_BITS = 13;
+constexpr int DR_MAX_A = 6144;
+static_assert(DR_MAX_A <= 1 << DR_KEY_BITS, "an assignment's number fits its key");
+constexpr int DR_STEP = 4 * MOE_WAVE;             // keys a wave compares per LDS read
+constexpr uint32_t DR_NO_KEY = 0xFFFFFFFFu;       // not counted by any query
+
+template <bool COPY>
+__global__ __launch_bounds__(DR_THREADS) void rank_direct_kernel(
+    const int32_t* __restrict__ topk_idx, int A, int E, int k, int32_t* __restrict__ counts,
+    int32_t* __restrict__ offsets, int32_t* __restrict__ dst_row, int32_t* __restrict__ src_assign,
+    const uint4* __restrict__ x, uint4* __restrict__ x_perm, int row16) {
+  extern __shared__ __align__(16) uint32_t keys[];        // A rounded up to a multiple of DR_STEP
+  const int lane = threadIdx.x & (MOE_WAVE - 1);
+  const int steps = (A + DR_STEP - 1) / DR_STEP;
+  constexpr int UNR = 8;                                  // loads in flight per thread
+  for (int b0 = threadIdx.x; b0 < steps * DR_STEP; b0 += UNR * DR_THREADS) {
+    int e[UNR];
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      const int b = b0 + u * DR_THREADS;
+      e[u] = b < A ? topk_idx[b] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      const int b = b0 + u * DR_THREADS;
+      if (b < steps * DR_STEP)
+        keys[b] = static_cast<unsigned>(e[u]) < static_cast<unsigned>(E)
+                      ? static_cast<uint32_t>(e[u]) << DR_KEY_BITS | static_cast<uint32_t>(b) : DR_NO_KEY;
+    }
   }
   __syncthreads();
-  for (int a = tid; a < A; a += 256)
-    if (idx[a] >= 0) atomicAdd(&cnt[idx[a]], 1);
-  __syncthreads();
-  if (tid < MOE_WAVE) {                         // exclusive scan over experts by wave 0
-    const int per = (E + MOE_WAVE - 1) / MOE_WAVE;
-    const int e0 = lane * per;
-    int local = 0;
-    for (int i = 0; i < per; ++i)
-      if (e0 + i < E) local += cnt[e0 + i];
-    int incl = local;
-    for (int o = 1; o < MOE_WAVE; o <<= 1) {
-      const int up = __shfl_up(incl, o);
-      if (lane >= o) incl += up;
-    }
-    int run = incl - local;
-    for (int i = 0; i < per; ++i) {
-      const int e = e0 + i;
-      if (e < E) {
-        off[e] = run;
-        counts[e] = cnt[e];
-        offsets[e] = run;
-        run += cnt[e];
-      }
-    }
-    if (lane == MOE_WAVE - 1) offsets[E] = incl;
+  const int w = __builtin_amdgcn_readfirstlane(blockIdx.x * (DR_THREADS / MOE_WAVE) + threadIdx.x / MOE_WAVE);
+  constexpr int Q = 2;                                    // queries per wave
+  const int a_waves = (A + Q - 1) / Q;
+  const bool experts = w >= a_waves;                      // wave-uniform
+  const int q0 = experts ? w - a_waves : w * Q;
+  if (experts && q0 >= E) return;
+  uint32_t key[Q];
+  int cnt[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    if (experts) key[q] = static_cast<uint32_t>(min(q0 + q, E)) << DR_KEY_BITS;
+    else key[q] = q0 + q < A ? __builtin_amdgcn_readfirstlane(keys[min(q0 + q, A - 1)]) : DR_NO_KEY;
+    cnt[q] = 0;
   }
-  __syncthreads();
-  const int a4 = (A + 3) & ~3;
-  for (int a = tid; a < A; a += 256) {
-    const int e = idx[a];
-    if (e < 0) {
-      dst_row[a] = 0;                           // invalid expert index: value unspecified, in bounds
-      continue;
+  for (int s = 0; s < steps; ++s) {
+    const uint4 v = *reinterpret_cast<const uint4*>(keys + s * DR_STEP + lane * 4);
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      cnt[q] += (v.x < key[q]) + (v.y < key[q]) + (v.z < key[q]) + (v.w < key[q]);
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) cnt[q] = __builtin_amdgcn_readlane(wave_scan_add(cnt[q]), MOE_WAVE - 1);
+  if (experts) {
+    if (lane == 0) {
+      counts[q0] = cnt[1] - cnt[0];
+      offsets[q0] = cnt[0];
+      if (q0 == E - 1) offsets[E] = cnt[1];
     }
-    int r = 0;
-    for (int b0 = 0; b0 < a4; b0 += 4) {
-      const int4 v = *reinterpret_cast<const int4*>(idx + b0);
-      r += (v.x == e && b0 < a) + (v.y == e && b0 + 1 < a) + (v.z == e && b0 + 2 < a) +
-           (v.w == e && b0 + 3 < a);
+    return;
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int a = q0 + q;
+    if (a >= A) break;
+    const bool valid = key[q] != DR_NO_KEY;
+    // invalid expert index: dst_row's value is unspecified, stays in bounds
+    if (lane == 0) dst_row[a] = valid ? cnt[q] : 0;
+    if (lane == 0 && valid) src_assign[cnt[q]] = a;
+  }
+  if (COPY) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (q0 + q >= A || key[q] == DR_NO_KEY) cnt[q] = -1;
+    for (int c = lane; c < row16; c += MOE_WAVE) {
+      uint4 v[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        if (cnt[q] >= 0) v[q] = x[static_cast<int64_t>((q0 + q) / k) * row16 + c];
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        if (cnt[q] >= 0) x_perm[static_cast<int64_t>(cnt[q]) * row16 + c] = v[q];
     }
-    const int dst = off[e] + r;
-    dst_row[a] = dst;
-    src_assign[dst] = a;
   }
 }
 
@@ -321,9 +351,16 @@ static int count_and_permute_impl(const moe_shape_t* shape, const void* x, const
   const size_t lds = static_cast<size_t>(E) * nth * 2 + static_cast<size_t>(E) * 8;
   // T == 0 still defines counts = 0 and offsets = 0: one block with no tokens does that.
   const int grid = nb > 0 ? nb : 1;
-  if (static_cast<int64_t>(T) * k <= RS_MAX_A) {
-    hipLaunchKernelGGL(rank_small_kernel, dim3(1), dim3(256), 0, st, topk_idx, T * k, E, counts,
-                       offsets, dst_row, src_assign);
+  const int64_t A = static_cast<int64_t>(T) * k;
+  bool copy = T > 0 && x_perm;
+  const int row16 = static_cast<int>(static_cast<int64_t>(shape->d) * elem_bytes(shape->dtype) / 16);
+  if (A <= DR_MAX_A) {
+    const int lds_keys = static_cast<int>((A + DR_STEP - 1) / DR_STEP) * DR_STEP * 4;
+    const int blocks = static_cast<int>(((A + 1) / 2 + E + DR_THREADS / MOE_WAVE - 1) / (DR_THREADS / MOE_WAVE));
+    hipLaunchKernelGGL(copy ? rank_direct_kernel<true> : rank_direct_kernel<false>, dim3(blocks), dim3(DR_THREADS),
+                       lds_keys, st, topk_idx, static_cast<int>(A), E, k, counts, offsets, dst_row, src_assign,
+                       static_cast<const uint4*>(x), static_cast<uint4*>(x_perm), row16);
+    copy = false;
   } else if (nth == 256) {
     static LdsOnce once;
     if (ensure_dynamic_lds(once, reinterpret_cast<const void*>(rank_kernel<256>),
@@ -341,8 +378,7 @@ static int count_and_permute_impl(const moe_shape_t* shape, const void* x, const
     hipLaunchKernelGGL(rank_kernel<128>, dim3(grid), dim3(128), lds, st, topk_idx, T, k, E, partial,
                        grid, counts, offsets, dst_row, src_assign);
   }
-  if (T > 0 && x_perm) {
-    const int row16 = static_cast<int>(static_cast<int64_t>(shape->d) * elem_bytes(shape->dtype) / 16);
+  if (copy) {
     hipLaunchKernelGGL(gather_kernel, dim3((T + 3) / 4), dim3(256), 0, st,
                        static_cast<const uint4*>(x), dst_row, static_cast<uint4*>(x_perm), T, k,
                        row16, T * k);

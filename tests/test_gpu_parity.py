@@ -416,6 +416,37 @@ def test_count_and_permute_degenerate_loads():
     check_dispatch(cfg2, L2["x"], idx)
 
 
+@pytest.mark.parametrize("T,d,E,k", [(1, 64, 1, 1), (255, 72, 3, 1), (64, 520, 5, 4), (257, 64, 65, 1), (512, 1032, 256, 2),
+                                     (6143, 64, 9, 1), (1536, 64, 256, 4), (6145, 64, 9, 1), (1537, 64, 256, 4)])
+def test_count_and_permute_on_both_sides_of_the_single_launch_limit(T, d, E, k):
+    """Batches of up to 6144 assignments are ranked by counting smaller keys, larger ones by histogram
+    and scan: the largest and smallest of each, blocks of 256 keys and 512-element rows over- and underfilled."""
+    cfg = si.small_config(T=T, d=d, E=E, k=k, F=64)
+    L = si.make_layer(cfg, parts=("x",))
+    idx = np.random.default_rng(T + E).integers(0, E, size=(T, k)).astype(np.int32)
+    check_dispatch(cfg, L["x"], idx)
+
+
+def test_count_and_permute_leaves_invalid_experts_out():
+    cfg = si.small_config(T=301, d=64, E=6, k=2, F=64)
+    idx = np.random.default_rng(2).integers(0, 6, size=(cfg.T, 2)).astype(np.int32)
+    idx[5, 0], idx[299, 1] = -1, 6
+    sh, flat = shape_of(cfg), idx.reshape(-1)
+    A = flat.size
+    out = [torch.full((n,), -7, dtype=torch.int32, device="cuda") for n in (6, 7, A, A)]
+    nb = B.moe_workspace_bytes(sh)
+    ws = torch.empty((nb,), dtype=torch.uint8, device="cuda")
+    B.moe_count_and_permute(sh, None, dev(idx), *out, None, ws, nb)
+    torch.cuda.synchronize()
+    counts, offsets, dst, src = (host(o) for o in out)
+    valid = (flat >= 0) & (flat < 6)
+    order = np.flatnonzero(valid)[np.argsort(flat[valid], kind="stable")]
+    assert np.array_equal(counts, np.bincount(flat[valid], minlength=6))
+    assert np.array_equal(offsets, np.concatenate([[0], np.cumsum(counts)]))
+    assert np.array_equal(src[:order.size], order) and np.array_equal(dst[order], np.arange(order.size))
+    assert ((dst >= 0) & (dst < A)).all()
+
+
 def test_count_and_permute_no_tokens():
     cfg = si.small_config(T=0, d=64, E=8, k=2, F=64)
     sh = shape_of(cfg)
