@@ -735,6 +735,24 @@ def test_combine_matches_oracle(case):
     assert rel_err(orc.to_f64(host(y)), ref) <= (1e-6 if cfg.dtype == si.F32 else 4e-3)
 
 
+@pytest.mark.parametrize("T,d,k,dtype", [(1, 1016, 1, si.BF16), (5, 1024, 5, si.BF16), (3, 1032, 2, si.BF16),
+                                         (4, 2048, 4, si.BF16), (6, 2056, 3, si.BF16), (7, 508, 1, si.F32),
+                                         (2, 512, 5, si.F32), (9, 516, 2, si.F32)])
+def test_combine_at_the_edges_of_its_column_slabs(T, d, k, dtype):
+    """A wave sums 2 KiB of a row: rows one chunk short of, equal to and one chunk past whole slabs, and
+    tokens that do not fill a block of four."""
+    cfg = si.small_config(T=T, d=d, E=8, k=k, F=64, dtype=dtype)
+    rng = np.random.default_rng(d)
+    w = rng.random((T, k), dtype=np.float32)
+    dst = rng.permutation(T * k).astype(np.int32)
+    yp = si.make_layer(si.small_config(T=T * k, d=d, E=1, k=1, F=8, dtype=dtype, seed=99), parts=("x",))["x"]
+    y = torch.zeros((T, d), dtype=tdtype(cfg), device="cuda")
+    B.moe_combine(shape_of(cfg), dev(yp), dev(dst), dev(w), y)
+    torch.cuda.synchronize()
+    # the same bounds as above: k fp32 products and sums, for bf16 one rounding to 8 bits
+    assert rel_err(orc.to_f64(host(y)), orc.combine(yp, dst, w)) <= (1e-6 if dtype == si.F32 else 4e-3)
+
+
 # ----------------------------------------------------------------------------- whole layer
 LAYER_CASES = [
     si.CONFIGS["tiny"],
