@@ -259,9 +259,11 @@ __device__ __forceinline__ bool decode_tile(const GemmArgs& p, TileCoord& tc) {
   return tc.m_begin < tc.m_end;
 }
 
-// silu(g) * u with the hardware exponential and reciprocal (about 1 ulp each; the result is
-// rounded to bf16 right after)
-__device__ __forceinline__ float silu_mul(float g, float u) {
+// silu(g) * u.  EXACT: silu first, by expf and a true division (fp32 layers, and bf16 layers whose widths
+// are multiples of 8 only).  Otherwise with the hardware exponential and reciprocal (about 1 ulp each;
+// the result is rounded to bf16 right after).
+template <bool EXACT> __device__ __forceinline__ float silu_mul(float g, float u) {
+  if constexpr (EXACT) return g / (1.0f + expf(-g)) * u;
   return g * u * __builtin_amdgcn_rcpf(1.0f + __expf(-g));
 }
 
@@ -313,7 +315,7 @@ template <int LATER, int NLOAD> __device__ __forceinline__ void wait_stages(int 
 // every wave must be done with whatever else the block kept in that LDS.
 // MI, NI: accumulator sub-tiles of a wave; WN: waves along the weight rows; the wave's first
 // mi_valid sub-tiles are stored, the first one starting at row wave_row0 of the tile.
-template <bool GATED, int MI, int NI, int WN, int NW>
+template <bool GATED, bool EXACT, int MI, int NI, int WN, int NW>
 __device__ __forceinline__ void ffn_store_tile(const f32x4_t (&acc)[NI][MI], const TileCoord& tc,
                                                const GemmArgs& p, unsigned char* lds, int wave, int lane,
                                                int mi_valid, int wave_row0) {
@@ -346,7 +348,7 @@ __device__ __forceinline__ void ffn_store_tile(const f32x4_t (&acc)[NI][MI], con
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           if (GATED)
-            o[u] = silu_mul(acc[ni][mi][u], acc[GATED ? ni + NIH : ni][mi][u]);
+            o[u] = silu_mul<EXACT>(acc[ni][mi][u], acc[GATED ? ni + NIH : ni][mi][u]);
           else
             o[u] = out_map ? acc[ni][mi][u] * scale : acc[ni][mi][u];
         }
@@ -588,7 +590,7 @@ __device__ __forceinline__ void ffn_ring_tile(const GemmArgs& p, const TileCoord
     ffn_store_part<MI, NI, NW * MOE_WAVE>(acc, tc, p);
     return;
   }
-  ffn_store_tile<GATED, MI, NI, WN, NW>(acc, tc, p, lds, wave, lane, mi_valid, wm * (BM / WM));
+  ffn_store_tile<GATED, RAGGED, MI, NI, WN, NW>(acc, tc, p, lds, wave, lane, mi_valid, wm * (BM / WM));
 }
 
 // Adds the parts of a split ring tile and stores it.
@@ -604,7 +606,7 @@ __device__ __forceinline__ void ffn_ring_sum_tile(const GemmArgs& p, const TileC
   const int mi_valid = max(0, min(MI, (rows_valid - wm * (BM / WM) + 15) / 16));
   f32x4_t acc[NI][MI];
   ffn_sum_parts<MI, NI, NW * MOE_WAVE>(acc, tc, p);
-  ffn_store_tile<GATED, MI, NI, WN, NW>(acc, tc, p, lds, wave, lane, mi_valid, wm * (BM / WM));
+  ffn_store_tile<GATED, false, MI, NI, WN, NW>(acc, tc, p, lds, wave, lane, mi_valid, wm * (BM / WM));
 }
 
 // --------------------------------------------------------------------------------------------
@@ -958,7 +960,7 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
   }
   // the store turns the sub-tiles around in activation buffer 0 (every wave has read its last
   // fragments before the store's barrier)
-  ffn_store_tile<GATED, MI, NI, WN, NW>(acc, tc, p, lds, wave, lane, miv, row0);
+  ffn_store_tile<GATED, RAGGED, MI, NI, WN, NW>(acc, tc, p, lds, wave, lane, miv, row0);
 }
 
 // Which pipeline a tile of `rows` rows takes: sub-tiles per wave (MI) of the even tile, 0 for a ring tile.
@@ -1008,7 +1010,7 @@ __device__ __forceinline__ void ffn_even_sum_tile(const GemmArgs& p, const TileC
   even_wave_rows(min(tc.m_end - tc.m_begin, MI * 64), wave / WN, miv, row0);
   f32x4_t acc[NI][MI];
   ffn_sum_parts<MI, NI, NW * MOE_WAVE>(acc, tc, p);
-  ffn_store_tile<GATED, MI, NI, WN, NW>(acc, tc, p, lds, wave, lane, miv, row0);
+  ffn_store_tile<GATED, false, MI, NI, WN, NW>(acc, tc, p, lds, wave, lane, miv, row0);
 }
 template <bool GATED, bool WNT>
 __global__ __launch_bounds__(512) void ffn_bf16_sum_parts_kernel(GemmArgs p) {
@@ -1168,7 +1170,7 @@ __global__ __launch_bounds__(F32_NW * MOE_WAVE, 3) void ffn_f32_kernel(GemmArgs 
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const float v = acc[0][mi][u];
-      o[u] = GATED ? v / (1.0f + expf(-v)) * acc[NMAT - 1][mi][u] : out_map ? v * scale : v;
+      o[u] = GATED ? silu_mul<true>(v, acc[NMAT - 1][mi][u]) : out_map ? v * scale : v;
     }
     *reinterpret_cast<f32x4_t*>(out + static_cast<int64_t>(gr) * N + c) = o;
   }

@@ -555,6 +555,36 @@ def test_grouped_ffn_widths_that_are_multiples_of_8(T, E, d, F):
     check_ffn(cfg, L, idx)
 
 
+@pytest.mark.parametrize("rows", [40, 100, 300])
+def test_grouped_ffn_extreme_gates_at_widths_that_are_multiples_of_8(rows):
+    # finite gates whose product with the up value, or whose exponential, leaves the fp32 range: silu is
+    # taken before the product, by a true division (ring tiles, and even tiles of 100 and 300 rows)
+    d, F = 72, 136
+    cfg = si.small_config(T=rows, d=d, E=1, k=1, F=F)
+    L = si.make_layer(cfg)
+    f32 = lambda a: (a.astype(np.uint32) << 16).view(np.float32)
+    bits = lambda a: (np.ascontiguousarray(a, dtype=np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    x, w1, w3 = (f32(L[n]).copy() for n in ("x", "w1", "w3"))
+    x[:, 0], x[:, 1] = 1.0, 0.0
+    gates = np.array([-1e20, 1e18, -1e38, -200.0, -104.0, -88.0, -86.5, -60.0], np.float32)
+    ups = np.array([1e20, 1e18, -1e38, 2e38, 1e38, 2.0 ** 100, -2.0 ** 110, 2.0 ** 90], np.float32)
+    w1[0, :8], w3[0, :8] = 0.0, 0.0               # these eight columns: gate and up value are the constants above
+    w1[0, :8, 0], w3[0, :8, 0] = gates, ups
+    x, w1, w3 = bits(x), bits(w1), bits(w3)
+    offsets = np.array([0, rows], np.int32)
+    h = torch.zeros((rows, F), dtype=torch.bfloat16, device="cuda")
+    yp = torch.zeros((rows, d), dtype=torch.bfloat16, device="cuda")
+    B.moe_grouped_ffn(shape_of(cfg), dev(x), dev(offsets), dev(w1), dev(w3), dev(L["w2"]), h, yp)
+    torch.cuda.synchronize()
+    g, u = f32(w1[0, :8, 0]).astype(np.float64), f32(w3[0, :8, 0]).astype(np.float64)
+    want = np.array([a * b / (1.0 + np.exp(-a)) if a > -700.0 else 0.0 for a, b in zip(g, u)])
+    got = h[:, :8].float().cpu().numpy().astype(np.float64)
+    # beyond exp(-g) = inf in fp32 (g below -88.7) silu is 0; else a few fp32 roundings and one to bf16 (2^-9)
+    want[g < -88.7] = 0.0
+    assert np.isfinite(got).all()
+    assert (np.abs(got - want) <= 2.0 ** -8 * np.abs(want)).all(), (got[0], want)
+
+
 @pytest.mark.parametrize("d,F", [(4, 4), (28, 60), (32, 64), (36, 68), (64, 132), (136, 100)])
 @pytest.mark.parametrize("rows", [(1, 0, 33), (16, 17, 31, 32), (64, 65, 129, 5)])
 def test_grouped_ffn_fp32_tile_edges(rows, d, F):
