@@ -36,7 +36,8 @@
 // XCDs) walks a contiguous range of the tile list with the m-tiles of one weight
 // panel adjacent: CUs that share an L2 share weight tiles.
 //
-// fp32 layers: ffn_f32_kernel, the same tiles on the fp32 matrix instruction.
+// fp32 layers: ffn_f32_kernel, smaller tiles on the fp32 matrix instruction.  Layers so wide that the
+// MFMA kernels' 32-bit offsets do not reach over a tile: ffn_wide_kernel.
 #include <type_traits>
 
 #include "moe_internal.h"
@@ -1176,6 +1177,77 @@ __global__ __launch_bounds__(F32_NW * MOE_WAVE, 3) void ffn_f32_kernel(GemmArgs 
   }
 }
 
+// --------------------------------------------------------------------------------------------
+// Very wide layers (a tile's operand spans 2 GiB or more, see tile_fits): 64 x 64 output tile, K step 16,
+// 4 x 4 outputs per thread, fp32 FMA, 64-bit addresses throughout.  Bound by the vector pipe (50 TFLOP/s
+// where there are tiles enough); no model is this wide, the kernel keeps such calls right.
+// --------------------------------------------------------------------------------------------
+constexpr int WIDE_T = 64;
+__device__ __forceinline__ float ld_elem(const float* p) { return *p; }
+__device__ __forceinline__ float ld_elem(const bf16_t* p) { return bf16_to_f32(*p); }
+__device__ __forceinline__ void st_elem(float* p, float v) { *p = v; }
+__device__ __forceinline__ void st_elem(bf16_t* p, float v) { *p = f32_to_bf16(v); }
+
+template <typename T, bool GATED>
+__global__ __launch_bounds__(256) void ffn_wide_kernel(GemmArgs p) {
+  constexpr int TK = 16, NMAT = GATED ? 2 : 1;
+  __shared__ float As[TK][WIDE_T + 4];
+  __shared__ float Bs[NMAT][TK][WIDE_T + 4];
+  TileCoord tc;
+  if (!decode_tile(p, tc)) return;
+  const int64_t K = p.K;
+  const int N = p.N, n0 = tc.n0;
+  const int tid = threadIdx.x;
+  const int tx = tid & 15, ty = tid >> 4;         // thread's 4 columns / 4 rows
+  const int lr = tid >> 2, lk = (tid & 3) * 4;    // loader: row 0..63, k offset 0,4,8,12
+  const T* a = static_cast<const T*>(p.a) + a_row_of(p, min(tc.m_begin + lr, tc.m_end - 1)) * K;
+  const int64_t b_off = (static_cast<int64_t>(tc.e) * N + min(n0 + lr, N - 1)) * K;
+  const T* b[NMAT];
+  b[0] = static_cast<const T*>(p.b0) + b_off;
+  if constexpr (GATED) b[1] = static_cast<const T*>(p.b1) + b_off;
+  float acc[NMAT][4][4] = {};
+  for (int64_t k0 = 0; k0 < K; k0 += TK) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t kk = k0 + lk + q;
+      As[lk + q][lr] = kk < K ? ld_elem(a + kk) : 0.f;
+#pragma unroll
+      for (int m = 0; m < NMAT; ++m) Bs[m][lk + q][lr] = kk < K ? ld_elem(b[m] + kk) : 0.f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int kk = 0; kk < TK; ++kk)
+#pragma unroll
+      for (int m = 0; m < NMAT; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[m][i][j] = fmaf(As[kk][ty * 4 + i], Bs[m][kk][tx * 4 + j], acc[m][i][j]);
+    __syncthreads();
+  }
+  T* out = static_cast<T*>(p.out);
+  const int32_t* out_map = GATED ? nullptr : p.out_map;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    int gr = tc.m_begin + ty * 4 + i;
+    if (gr >= tc.m_end) continue;
+    float scale = 1.f;
+    if (out_map) {
+      gr = min(max(out_map[gr], 0), p.out_rows - 1);
+      scale = p.out_scale[gr];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int c = n0 + tx * 4 + j;
+      if (c >= N) continue;
+      const float v = acc[0][i][j];
+      st_elem(out + static_cast<int64_t>(gr) * N + c,
+              GATED ? silu_mul<true>(v, acc[NMAT - 1][i][j]) : out_map ? v * scale : v);
+    }
+  }
+}
+
 // Compute units of the current device, looked up once per device (0 if the query fails: the
 // kernels then assume 256).
 static int device_cu_count() {
@@ -1240,10 +1312,26 @@ static bool ragged(const GemmArgs& a) { return a.K % BK_ELEMS != 0 || a.N % BK_E
 // 128-expert layer at 2500 tokens is 4 % slower.)
 static int most_tile_rows(int64_t mean_rows) { return mean_rows < 96 ? 128 : mean_rows < 128 ? 192 : EVEN_BM; }
 
+// The MFMA kernels address a tile's rows of an operand by 32-bit byte offsets from its first row, below the
+// 2 GiB that a buffer resource admits (requests beyond it come back as zeros: see PAST_END).  True if
+// `rows` rows of the GEMM's reduction stay inside.
+static bool tile_fits(const GemmArgs& a, int rows, int elem) {
+  return static_cast<int64_t>(rows) * a.K * elem < (int64_t(1) << 31);
+}
+
+template <typename T, bool GATED>
+static int launch_wide(GemmArgs a, int64_t A, hipStream_t st) {
+  static LdsOnce once[2];
+  a.bn = WIDE_T;
+  a.n_tiles = (a.N + WIDE_T - 1) / WIDE_T;
+  return launch_grouped_gemm(a, WIDE_T, A, 256, 0, ffn_wide_kernel<T, GATED>, once[0], nullptr, once[1], st);
+}
+
 template <bool GATED, bool WNT>
 static int launch_bf16(const GemmArgs& a, int64_t A, bool row_split, hipStream_t st) {
   static LdsOnce once[2], once_ragged, once_sum;
   const int bm = most_tile_rows(A / a.E);
+  if (!tile_fits(a, bm > BROWS ? bm : BROWS, 2)) return launch_wide<bf16_t, GATED>(a, A, st);
   GemmArgs b = a;
   b.tail_split = row_split ? 1 : 0;
   if (ragged(a))
@@ -1263,6 +1351,7 @@ static int launch_bf16(const GemmArgs& a, int64_t A, bool row_split, hipStream_t
 template <bool GATED>
 static int launch_f32(GemmArgs a, int64_t A, hipStream_t st) {
   static LdsOnce once[2], once_sum;
+  if (!tile_fits(a, F32_BN, 4)) return launch_wide<float, GATED>(a, A, st);
   a.bn = F32_BN;
   a.n_tiles = (a.N + F32_BN - 1) / F32_BN;
   const int64_t tiles64 = (A + 63) / 64 * a.n_tiles;

@@ -610,6 +610,64 @@ def test_grouped_ffn_fp32_64_row_tiles():
     assert np.isfinite(h).all() and np.isfinite(yp).all()
 
 
+@pytest.mark.parametrize("dtype,T,d,F,form", [
+    (si.F32, 64, 4, 2 ** 23 + 4, "perm"), (si.F32, 64, 4, 2 ** 23 + 4, "k1"),   # 64 activation rows of the down-projection
+    (si.F32, 2, 2 ** 23 + 4, 64, "perm"),                                       # 64 weight rows of the up-projection
+    (si.BF16, 320, 8, 3355448, "perm"),                                         # 320 activation rows
+    (si.BF16, 3, 256, 2 ** 22 + 8, "perm"), (si.BF16, 3, 256, 2 ** 22, "gather"),   # 256 weight rows
+    (si.F32, 64, 4, 2 ** 23 - 4, "perm"), (si.BF16, 320, 8, 3355440, "perm")])  # the widest that 32 bits reach
+def test_grouped_ffn_rows_around_the_limit_of_32_bit_offsets(dtype, T, d, F, form):
+    """One tile's rows of an operand span 2 GiB or more, or just less.  Reference: fp64 sums over slices, on
+    the GPU."""
+    tdt = torch.float32 if dtype == si.F32 else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(7)
+
+    def randn(shape, std):
+        t = torch.empty(shape, dtype=tdt, device="cuda")
+        return t.normal_(0.0, std, generator=gen)
+
+    x, w1, w3 = randn((T, d), 1.0), randn((1, F, d), d ** -0.5), randn((1, F, d), d ** -0.5)
+    w2 = randn((1, d, F), F ** -0.5)
+    src = torch.randperm(T, device="cuda", generator=gen).to(torch.int32) if form != "perm" else None
+    scale = torch.rand(T, device="cuda", generator=gen) + 0.5 if form == "k1" else None
+    off = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+    h, y = torch.zeros((T, F), dtype=tdt, device="cuda"), torch.zeros((T, d), dtype=tdt, device="cuda")
+    sh = B.make_shape(T, d, 1, 1, F, dtype, 1)
+    if form == "k1":
+        B.moe_grouped_ffn_combine_k1(sh, x, src, off, w1, w3, w2, scale, h, y)
+    elif form == "gather":
+        B.moe_grouped_ffn_gather(sh, x, src, off, w1, w3, w2, h, y)
+    else:
+        B.moe_grouped_ffn(sh, x, off, w1, w3, w2, h, y)
+    torch.cuda.synchronize()
+    rows = x if src is None else x[src.long()]
+
+    def product(a, w):                            # a [T, K] times w [N, K] transposed, fp64, sliced along both
+        n_step, k_step = max(1, 2 ** 24 // min(w.shape[1], 2 ** 16)), 2 ** 16
+        out = torch.zeros((a.shape[0], w.shape[0]), dtype=torch.float64, device="cuda")
+        for n in range(0, w.shape[0], n_step):
+            for k in range(0, w.shape[1], k_step):
+                out[:, n:n + n_step] += a[:, k:k + k_step].double() @ w[n:n + n_step, k:k + k_step].double().t().contiguous()
+        return out
+
+    # an fp32 sum of K terms one after the other (rounding 2^-24 of partial sums that grow as a random walk:
+    # below sqrt(K) 2^-24 of the result's scale), and a rounding to bf16 where stored so; zeros in
+    # place of one row would be off by the whole scale
+    def bound(K):
+        return 4.0 * K ** 0.5 * 2.0 ** -24 + (2.0 ** -8 if dtype == si.BF16 else 2.0 ** -22)
+
+    g, u = product(rows, w1[0]), product(rows, w3[0])
+    ref = g / (1.0 + torch.exp(-g)) * u
+    assert float((h.double() - ref).abs().max() / ref.abs().max()) <= bound(d)
+    del g, u, ref
+    ref = product(h, w2[0])
+    if form == "k1":
+        scattered = torch.empty_like(ref)
+        scattered[src.long()] = ref
+        ref = scattered * scale.double()[:, None]
+    assert float((y.double() - ref).abs().max() / ref.abs().max()) <= bound(F)
+
+
 @pytest.mark.parametrize("rows", [1, 15, 16, 17, 47, 64, 65, 130, 255, 257, 319, 320, 321, 336, 641, 1000])
 def test_grouped_ffn_even_tiles_every_wave_share(rows):
     # one hot expert with `rows` rows among experts of 128 rows (so that the mean stays above the
