@@ -311,7 +311,8 @@ __global__ __launch_bounds__(256) void place_kernel(
     int32_t* __restrict__ n_warm) {
   __shared__ __align__(16) PlaceStep step[PL_CHUNK + 1];   // (one more: the read ahead of the last step)
   __shared__ double key[MOE_MAX_E];
-  __shared__ int seg_start[MOE_MAX_E], prev_start[MOE_MAX_E], prev_n[MOE_MAX_E], rep[MOE_MAX_E];
+  __shared__ int seg_start[MOE_MAX_E], prev_n[MOE_MAX_E], rep[MOE_MAX_E];
+  __shared__ long long prev_start[MOE_MAX_E];    // (the previous round's counts are the caller's: their sum may pass 2^31)
   __shared__ int order[MOE_MAX_E], order_start[MOE_MAX_E + 1];
   __shared__ long long part[3][4];
   const int tid = threadIdx.x, lane = lane_id();
@@ -321,7 +322,7 @@ __global__ __launch_bounds__(256) void place_kernel(
   const double my_key = tid < E ? static_cast<double>(max(loads[tid], 0)) / static_cast<double>(my_r) : -1.0;
   long long total, dummy;
   seg_start[tid] = static_cast<int>(block_prefix(my_r, part[0], &total));    // (at most 256 * 65537)
-  prev_start[tid] = saturate31(block_prefix(my_p, part[1], &dummy));
+  prev_start[tid] = block_prefix(my_p, part[1], &dummy);
   prev_n[tid] = my_p;
   rep[tid] = my_r;
   key[tid] = my_key;

@@ -3,6 +3,8 @@ moe_replica_segments against oracle/scaler_oracle.py, bit-exact on every integer
 CV values within 1e-12 relative (both sides compute them in fp64, in a different summation order).
 The decision CV > V is taken in fp64 on both sides; each case first checks, on the oracle's trace,
 that no step sits on the knife edge |CV - V| < 1e-9 where the order of an fp64 sum could decide."""
+import collections
+
 import numpy as np
 import pytest
 
@@ -381,3 +383,24 @@ def test_loads_that_differ_in_their_last_bits_only(E):
     replicas = check_scale(loads, 1, 3 * E // 2, -1.0)
     check_place(loads, replicas, 16)
     check_place(loads, replicas, 40)
+
+
+def test_place_replicas_after_a_round_of_more_than_2_31_replicas():
+    # the replicas of experts 1 and 2 lie past index 2^31 of the previous round's list
+    prev_r, G = [2 ** 31 - 1, 5, 3], 3
+    start = np.concatenate([[0], np.cumsum(np.array(prev_r, dtype=np.int64))])
+    warm = {0: 2, int(start[1]): 1, int(start[1]) + 1: 1, int(start[1]) + 2: 0, int(start[2]): 2, int(start[2]) + 1: 1}
+    loads, replicas = [10, 40, 6], [2, 4, 2]
+    want = pl.expert_placement(loads, replicas, G, start, collections.defaultdict(lambda: -1, warm))
+    assert want[3] == len(warm)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    prev_gpu = torch.full((int(start[-1]),), -1, **i32)
+    for i, g in warm.items():
+        prev_gpu[i] = g
+    gpu_of, count, n_warm = torch.full((8,), -9, **i32), torch.zeros(G, **i32), torch.zeros(1, **i32)
+    load = torch.zeros(G, dtype=torch.float64, device="cuda")
+    B.moe_place_replicas(3, torch.tensor(loads, **i32), torch.tensor(replicas, **i32), G, torch.tensor(prev_r, **i32),
+                         prev_gpu, None, 8, gpu_of, load, count, n_warm)
+    torch.cuda.synchronize()
+    assert np.array_equal(gpu_of.cpu().numpy(), want[0]) and np.array_equal(load.cpu().numpy(), want[1])
+    assert np.array_equal(count.cpu().numpy(), want[2]) and int(n_warm.item()) == want[3]
