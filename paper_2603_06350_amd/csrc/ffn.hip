@@ -308,6 +308,16 @@ template <int LATER, int NLOAD> __device__ __forceinline__ void wait_stages(int 
   }
 }
 
+// Barrier at which LDS changes hands: after it, other waves or direct-to-LDS loads overwrite what this
+// wave has read, so its reads must have returned (a read still under way when its slot is
+// refilled would see the new data).  The wait is stated here and not left to where the compiler puts the reads'
+// first use; it costs nothing, as the reads have been consumed by then.
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // Store of a wave's outputs.  Accumulator (v, lane) holds out[row = m-sub-tile + lane%16]
 // [col = n-sub-tile + 4*(lane/16) + v]: 8-byte pieces scattered over 16 rows.  Each wave turns its
 // 16-row sub-tile around in a private LDS region (row pitch = row bytes + 32: the 32-byte runs
@@ -325,8 +335,7 @@ __device__ __forceinline__ void ffn_store_tile(const f32x4_t (&acc)[NI][MI], con
   const int l16 = lane & 15;
   const int N = p.N;
   const int n0 = tc.n0;
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
+  lds_barrier();
   constexpr int CW = NIH * 16;                    // output columns of this wave
   constexpr int PITCH = CW * 2 + 32;              // bytes
   constexpr int LPR = CW * 2 / 16;                // lanes that store one row
@@ -576,8 +585,7 @@ __device__ __forceinline__ void ffn_ring_tile(const GemmArgs& p, const TileCoord
   for (int kt = 0; kt < KT; ++kt) {
     // the loads of stage kt are the oldest outstanding; up to DIST-1 later stages may follow
     wait_stages<DIST - 1, NLOAD>(KT - 1 - kt);
-    __builtin_amdgcn_s_barrier();     // stage kt landed for all waves; the slot of kt-1 is free
-    asm volatile("" ::: "memory");
+    lds_barrier();                    // stage kt landed for all waves; the slot of kt-1 is free
     if (kt + DIST < KT) {
 #pragma unroll
       for (int i = 0; i < NLOAD; ++i) issue_load(i, kt + DIST, fill);
@@ -934,8 +942,7 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
     asm volatile("s_waitcnt vmcnt(%0)" ::"i"(W_LOADS) : "memory");
   else
     wait_vmcnt<0>();
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
+  lds_barrier();
   switch (miv) {                                  // wave-uniform
     case 0: k_loop(std::integral_constant<int, 0>{}); break;
     case 1: k_loop(std::integral_constant<int, 1>{}); break;
@@ -1123,8 +1130,7 @@ __global__ __launch_bounds__(F32_NW * MOE_WAVE, 3) void ffn_f32_kernel(GemmArgs 
       if (later >= 2) wait_vmcnt<2 * NLOAD>();
       else if (later == 1) wait_vmcnt<NLOAD>();
       else wait_vmcnt<0>();
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
+      lds_barrier();
       if (kt + DIST < KT) issue(kt + DIST, (kt + DIST) % NSTAGE);
       const unsigned char* s = lds + (kt % NSTAGE) * STAGE;
       f32x4_t xf[2][MIV], wf[2][NMAT];
