@@ -54,3 +54,16 @@ def test_every_barrier_of_the_ffn_kernels_waits_for_the_wave_s_lds_reads(code_ob
                 settled = False
     assert barriers > 50
     assert not bad, f"{len(bad)} of {barriers} barriers, in {sorted(set(bad))}"
+
+
+def test_the_ffn_kernels_spill_no_scalar_registers(code_objects):
+    # a spilled scalar is a lane of a vector register, read back inside the K loops
+    spills = {}
+    for path in code_objects:
+        notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", path], check=True, capture_output=True,
+                               text=True).stdout
+        for name, count in re.findall(r"\.name:\s+(\S+).*?\.sgpr_spill_count:\s+(\d+)", notes, re.S):
+            if "ffn_" in name:
+                spills[name] = int(count)
+    assert len(spills) > 10
+    assert not any(spills.values()), {k: v for k, v in spills.items() if v}
