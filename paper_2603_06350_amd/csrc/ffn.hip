@@ -80,6 +80,7 @@ struct GemmArgs {
   // Launches without split_ws: tiles of a last round that is at most half full are cut into pieces
   // for the idle units (the grid has a round of extra blocks).
   int tail_split;
+  int few_buffers;  // up-projections: experts of several tiles keep two weight buffers (see tile_mi)
 };
 
 constexpr int SPLIT_SLOT_FLOATS = 320 * 256;   // one partial tile (the largest: 320 x 256 fp32)
@@ -101,6 +102,7 @@ struct TileCoord {
   int part, nparts;
   int pslot;   // partial-tile slot of this part; the parts of a tile have consecutive slots
   int sharers; // tiles and pieces of tiles of this expert that read the same weight rows
+  int height;  // rows that pick the pipeline
 };
 constexpr int TAIL_MAX_PIECES = 4;
 // Tiles of at most RING_ROWS rows have little arithmetic per weight byte and are paced by memory
@@ -117,7 +119,15 @@ constexpr int WGT_NT_MAX_SHARERS = 2;
 // An expert with c rows has ceil(c / bm) tiles; the segment's 16-row sub-tiles are dealt to them evenly.
 // Tile order: expert-major, then n-tile, then m-tile (m fastest), cut into 8 contiguous ranges,
 // one per XCD.
-template <bool SPLIT = false>
+// BY_EXPERT: all tiles of an expert (and the sister pieces of a tile) take the pipeline that the highest of
+// them needs; otherwise each the one for its own rows.  Tiles that read the same weight rows side by side
+// with the non-temporal hint have to keep pace, or the second one finds them gone from the L2; in two
+// different pipelines they drift apart.  (Measured at 500 to 530 rows per expert, where most
+// experts are a tile below and one above 256 rows, by expert against by own rows: llama4 shape at 8480
+// tokens 1925 -> 1830 us, phi shape at 4000 tokens 1115 -> 1095, down-projection of the Mixtral shape at 2000
+// tokens 407 -> 389.  Where weight rows stay in the L2, !WNT, the third weight buffer of the lower tiles is
+// worth more: 64-expert shape at 8192 tokens, down-projection 266 us by own rows, 273 by expert.)
+template <bool SPLIT = false, bool BY_EXPERT = false>
 __device__ __forceinline__ bool decode_tile(const GemmArgs& p, TileCoord& tc) {
   const int32_t* __restrict__ offsets = p.offsets;
   const int E = p.E, n_tiles = p.n_tiles, bm = p.bm;
@@ -239,6 +249,11 @@ __device__ __forceinline__ bool decode_tile(const GemmArgs& p, TileCoord& tc) {
   const int b0 = m_idx == 0 ? 0 : 2 * (m_idx * pairs / m_tiles) + odd;
   const int b1 = 2 * ((m_idx + 1) * pairs / m_tiles) + odd;
   int s0 = b0, s1 = b1;
+  int top = b1 - b0;
+  if (BY_EXPERT) {
+    const int q = pairs / m_tiles;
+    top = max(2 * (q + (q * m_tiles < pairs ? 1 : 0)), 2 * q + odd);
+  }
   if (m_pieces > 1) {
     const int n_sub = b1 - b0;
     if (n_sub <= NSPLIT_ROWS / 16) {
@@ -253,10 +268,12 @@ __device__ __forceinline__ bool decode_tile(const GemmArgs& p, TileCoord& tc) {
       tc.sharers = m_tiles + pieces - 1;
       s0 = b0 + m_piece * n_sub / pieces;
       s1 = b0 + (m_piece + 1) * n_sub / pieces;
+      top = BY_EXPERT ? (n_sub + pieces - 1) / pieces : s1 - s0;
     }
   }
   tc.m_begin = seg_begin + s0 * 16;
   tc.m_end = min(seg_end, seg_begin + s1 * 16);
+  tc.height = BY_EXPERT ? top * 16 : tc.m_end - tc.m_begin;
   return tc.m_begin < tc.m_end;
 }
 
@@ -980,15 +997,16 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
   ffn_store_tile<GATED, RAGGED, MI, NI, WN, NW>(acc, tc, p, lds, wave, lane, miv, row0);
 }
 
-// Which pipeline a tile of `rows` rows takes: sub-tiles per wave (MI) of the even tile, 0 for a ring tile.
+// Which pipeline a tile takes: sub-tiles per wave (MI) of the even tile, 0 for a ring tile.
 // The more weight buffers the better where the weight rows come from HBM.  Where experts hold several
 // tiles each (!WNT), the tiles share them through the L2, and only the down-projection, whose
 // reduction is the longer one, gains from the third buffer.  (Measured: Mixtral shape at 192 rows per
 // expert, up-projection 434 -> 389 us with three; at 1024 rows 1 % slower, down-projection 4.5 %
 // faster; skewed 64-expert layer of 8192 tokens, the cold experts' tiles with four, up-projection
-// 1 % slower.)
-template <bool GATED, bool WNT> __device__ __forceinline__ int tile_mi(int rows) {
-  return rows <= RING_ROWS ? 0 : WNT && rows <= 128 ? 2 : (WNT || !GATED) && rows <= 256 ? 4 : 5;
+// 1 % slower.)  few_buffers: see launch_bf16.
+template <bool GATED, bool WNT> __device__ __forceinline__ int tile_mi(const GemmArgs& p, const TileCoord& tc) {
+  const bool three = GATED ? WNT && !(p.few_buffers && tc.sharers > 1) : true;
+  return tc.height <= RING_ROWS ? 0 : WNT && tc.height <= 128 ? 2 : three && tc.height <= 256 ? 4 : 5;
 }
 
 template <bool GATED, bool SPLIT, bool WNT, bool RAGGED>
@@ -997,7 +1015,7 @@ __global__ __launch_bounds__(512) void ffn_bf16_kernel(GemmArgs p) {
   static_assert(ffn_ring_lds_bytes(RING_ROWS, 64, 9) <= FFN_LDS && ffn_ring_lds_bytes(RING_ROWS, 128, 6) <= FFN_LDS &&
                     ffn_ring_lds_bytes(NSPLIT_ROWS, 128, 5) <= FFN_LDS, "pieces' rings fit the launch's LDS");
   TileCoord tc;
-  if (!decode_tile<SPLIT>(p, tc)) return;
+  if (!decode_tile<SPLIT, WNT>(p, tc)) return;
   const int rows = tc.m_end - tc.m_begin;         // block-uniform
   if (!SPLIT && tc.n_pieces == 4)
     ffn_ring_tile<RING_ROWS, 64, GATED, 4, 2, 9, false, WNT, RAGGED>(p, tc, lds);
@@ -1005,7 +1023,7 @@ __global__ __launch_bounds__(512) void ffn_bf16_kernel(GemmArgs p) {
     ffn_ring_tile<RING_ROWS, 128, GATED, 2, 4, 6, false, WNT, RAGGED>(p, tc, lds);
   else if (!SPLIT && tc.n_pieces == 2)
     ffn_ring_tile<NSPLIT_ROWS, 128, GATED, 2, 4, 5, false, WNT, RAGGED>(p, tc, lds);
-  else switch (tile_mi<GATED, WNT>(rows)) {
+  else switch (tile_mi<GATED, WNT>(p, tc)) {
     case 0: ffn_ring_tile<RING_ROWS, BROWS, GATED, 2, 4, 4, SPLIT, WNT, RAGGED>(p, tc, lds); break;
     case 2:
       if constexpr (WNT) ffn_even_tile<GATED, SPLIT, WNT, RAGGED, 2>(p, tc, lds);
@@ -1033,8 +1051,8 @@ template <bool GATED, bool WNT>
 __global__ __launch_bounds__(512) void ffn_bf16_sum_parts_kernel(GemmArgs p) {
   extern __shared__ __align__(1024) unsigned char lds[];
   TileCoord tc;
-  if (!decode_tile<true>(p, tc)) return;
-  switch (tile_mi<GATED, WNT>(tc.m_end - tc.m_begin)) {
+  if (!decode_tile<true, WNT>(p, tc)) return;
+  switch (tile_mi<GATED, WNT>(p, tc)) {
     case 0: ffn_ring_sum_tile<RING_ROWS, GATED, 2, 4>(p, tc, lds); break;
     case 2:
       if constexpr (WNT) ffn_even_sum_tile<GATED, 2>(p, tc, lds);
@@ -1342,11 +1360,20 @@ static int launch_wide(GemmArgs a, int64_t A, hipStream_t st) {
   return launch_grouped_gemm(a, WIDE_T, A, 256, 0, ffn_wide_kernel<T, GATED>, once[0], nullptr, once[1], st);
 }
 
+// Mean rows per expert from which most experts are two tiles or more.
+constexpr int FEW_BUFFERS_ROWS = 384;
+
 template <bool GATED, bool WNT>
-static int launch_bf16(const GemmArgs& a, int64_t A, bool row_split, hipStream_t st) {
+static int launch_bf16(GemmArgs a, int64_t A, bool row_split, hipStream_t st) {
   static LdsOnce once[2], once_ragged, once_sum;
   const int bm = most_tile_rows(A / a.E);
   if (!tile_fits(a, bm > BROWS ? bm : BROWS, 2)) return launch_wide<bf16_t, GATED>(a, A, st);
+  // Two tiles of 192 to 256 rows that share their weight rows gain from a third buffer in the up-projection
+  // unless the row pitch is a power of two, which puts a tile's 256 rows on few memory channels.
+  // (Measured, three against two buffers, 16 experts of 400 / 460 rows, F = 6400, up-projection: d = 3072
+  // 8 / 3 % faster, 5120 8 / 7 %, 6144 9 / 5 %, 4608 and 7168 within 3 % either way, 4096 3 % slower, 2048
+  // 2 % faster / 3 % slower; below 384 rows faster at every d, 2 to 11 %.)
+  a.few_buffers = GATED && A / a.E >= FEW_BUFFERS_ROWS && (a.K & (a.K - 1)) == 0;
   GemmArgs b = a;
   b.tail_split = row_split ? 1 : 0;
   if (ragged(a))

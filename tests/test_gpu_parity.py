@@ -718,6 +718,16 @@ def test_grouped_ffn_whole_rounds_and_under_filled_last_rounds(rows, d, F):
     check_ffn(cfg, L, idx)
 
 
+@pytest.mark.parametrize("d", [192, 256, 520])
+@pytest.mark.parametrize("rows", [(544, 540, 530, 560), (272, 80, 80, 80, 80, 80, 80), (130, 40, 40, 40), (300, 257, 400, 640)])
+def test_grouped_ffn_tiles_of_one_expert_on_both_sides_of_a_pipeline_s_limit(rows, d):
+    # experts of two tiles with one up to and one above 256, 128 or 64 rows: both take the higher one's
+    # pipeline; the first and last case have the mean rows at which a power-of-two reduction (d = 256)
+    # keeps two weight buffers in the up-projection
+    cfg = si.small_config(T=sum(rows), d=d, E=len(rows), k=1, F=384 if d != 520 else 392, seed=d + rows[0])
+    check_ffn(cfg, si.make_layer(cfg), np.repeat(np.arange(len(rows), dtype=np.int32), rows)[:, None])
+
+
 SPLIT_CASES = [
     # (shape, whether some tile must have been split); a GEMM is eligible from K = 6144 on
     (dict(T=600, d=1024, E=2, k=1, F=6144), True),    # even tiles, down-projection cut in 4
