@@ -16,7 +16,9 @@ namespace moe {
 // neighbours, so a row's pieces travel together; in a two-dimensional grid the second slab of every token
 // came after the first slab of all of them.  (Measured, neighbours and UNR = 2 against that
 // grid and UNR = 4: 65536 tokens, d = 4096, k = 2 270 -> 251 us, 6.4 TB/s; 30000 tokens, d = 5120, k = 1
-// 111 -> 99 us; 32 to 8192 tokens within 0.4 us.  Neighbours and UNR = 4: 260 / 104 us; 8: 265 / 128.)
+// 111 -> 99 us; 32 to 8192 tokens within 0.4 us.  UNR = 8: 265 / 128 us.)  Blocks are dealt to the
+// eight XCDs in turn, so with an even number of slabs some XCDs would get the full slabs and others the
+// short last ones: combine_unr avoids that.
 template <bool BF16, int UNR>
 __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ y_perm,
                                                       const int32_t* __restrict__ dst_row,
@@ -109,22 +111,25 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
   }
 }
 
-}  // namespace moe
+// UNR for rows of row16 chunks: the least of 2, 3, 4 that cuts them into an odd number of slabs, else 2.
+// (Measured, 15000 tokens, k = 2, UNR = 2 / 3 / 4 in us: 136 chunks 21.3 / 17.2 / 17.7; 193: 27.7 / 32.6 / 24.0;
+// 257: 33.8 / 36.9 / 41.9; 385: 50.6 / 48.5 / 51.8; 577: 70.8 / 73.4 / 69.5; 641: 86.1 / 80.0 / 75.9;
+// 900: 107.6 / 102.2 / 108.4; 1025: 123.7 / 129.4 / 120.8.  Where the slabs are all full, 256, 384, 512 and
+// 768 chunks, every choice is within 1 % of the others but 3 at 256.)
+static int combine_unr(int row16) {
+  for (int unr = 2; unr <= 4; ++unr)
+    if ((row16 + unr * MOE_WAVE - 1) / (unr * MOE_WAVE) % 2 == 1) return unr;
+  return 2;
+}
 
-extern "C" int moe_combine(const moe_shape_t* shape, const void* y_perm, const int32_t* dst_row,
-                           const float* topk_w, void* y, void* hip_stream) {
-  const int rc = moe::check_shape(shape);
-  if (rc != MOE_OK) return rc;
+template <bool BF16>
+static int launch_combine(const moe_shape_t* shape, const void* y_perm, const int32_t* dst_row, const float* topk_w,
+                          void* y, hipStream_t st) {
   const int T = shape->T;
-  if (T == 0) return MOE_OK;
-  if (!y_perm || !dst_row || !topk_w || !y) return MOE_ERR_INVALID_ARG;
-  if (!moe::aligned16(y_perm) || !moe::aligned16(y)) return MOE_ERR_INVALID_ARG;
-  hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  const int row16 =
-      static_cast<int>(static_cast<int64_t>(shape->d) * moe::elem_bytes(shape->dtype) / 16);
-  constexpr int UNR = 2;
-  const int slabs = (row16 + UNR * MOE_WAVE - 1) / (UNR * MOE_WAVE);
-  const auto kernel = shape->dtype == MOE_BF16 ? moe::combine_kernel<true, UNR> : moe::combine_kernel<false, UNR>;
+  const int row16 = static_cast<int>(static_cast<int64_t>(shape->d) * elem_bytes(shape->dtype) / 16);
+  const int unr = combine_unr(row16);
+  const int slabs = (row16 + unr * MOE_WAVE - 1) / (unr * MOE_WAVE);
+  const auto kernel = unr == 2 ? combine_kernel<BF16, 2> : unr == 3 ? combine_kernel<BF16, 3> : combine_kernel<BF16, 4>;
   // one launch, unless the grid would pass the 2^32 threads that a launch may have
   const int64_t per_launch = static_cast<int64_t>(((1 << 24) - 1) / slabs) * 4;
   for (int64_t t0 = 0; t0 < T; t0 += per_launch) {
@@ -133,5 +138,19 @@ extern "C" int moe_combine(const moe_shape_t* shape, const void* y_perm, const i
                        static_cast<const uint4*>(y_perm), dst_row, topk_w, static_cast<uint4*>(y), T,
                        shape->k, row16, T * shape->k, slabs, static_cast<int>(t0));
   }
-  return moe::launch_status();
+  return launch_status();
+}
+
+}  // namespace moe
+
+extern "C" int moe_combine(const moe_shape_t* shape, const void* y_perm, const int32_t* dst_row,
+                           const float* topk_w, void* y, void* hip_stream) {
+  const int rc = moe::check_shape(shape);
+  if (rc != MOE_OK) return rc;
+  if (shape->T == 0) return MOE_OK;
+  if (!y_perm || !dst_row || !topk_w || !y) return MOE_ERR_INVALID_ARG;
+  if (!moe::aligned16(y_perm) || !moe::aligned16(y)) return MOE_ERR_INVALID_ARG;
+  hipStream_t st = static_cast<hipStream_t>(hip_stream);
+  return shape->dtype == MOE_BF16 ? moe::launch_combine<true>(shape, y_perm, dst_row, topk_w, y, st)
+                                  : moe::launch_combine<false>(shape, y_perm, dst_row, topk_w, y, st);
 }

@@ -851,6 +851,23 @@ def test_combine_at_the_edges_of_its_column_slabs(T, d, k, dtype):
     assert rel_err(orc.to_f64(host(y)), orc.combine(yp, dst, w)) <= (1e-6 if dtype == si.F32 else 4e-3)
 
 
+@pytest.mark.parametrize("chunks", [192, 193, 384, 385, 512, 513, 640, 641, 769, 896, 897, 960, 961, 1025])
+@pytest.mark.parametrize("dtype", [si.BF16, si.F32])
+def test_combine_in_slabs_of_2_3_and_4_kib(chunks, dtype):
+    # rows of so many 16-byte chunks take waves of 2, 3 or 4 KiB, whichever gives an odd number of slabs
+    T, k = 5, 3
+    cfg = si.small_config(T=T, d=chunks * (8 if dtype == si.BF16 else 4), E=8, k=k, F=64, dtype=dtype)
+    rng = np.random.default_rng(chunks)
+    w = rng.random((T, k), dtype=np.float32)
+    dst = rng.permutation(T * k).astype(np.int32)
+    yp = si.make_layer(si.small_config(T=T * k, d=cfg.d, E=1, k=1, F=8, dtype=dtype, seed=99), parts=("x",))["x"]
+    y = torch.zeros((T, cfg.d), dtype=tdtype(cfg), device="cuda")
+    B.moe_combine(shape_of(cfg), dev(yp), dev(dst), dev(w), y)
+    torch.cuda.synchronize()
+    # k fp32 products and sums, for bf16 one rounding to 8 bits
+    assert rel_err(orc.to_f64(host(y)), orc.combine(yp, dst, w)) <= (1e-6 if dtype == si.F32 else 4e-3)
+
+
 # ----------------------------------------------------------------------------- whole layer
 LAYER_CASES = [
     si.CONFIGS["tiny"],
