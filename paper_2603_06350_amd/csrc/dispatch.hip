@@ -277,11 +277,15 @@ __global__ __launch_bounds__(DR_THREADS) void rank_direct_kernel(
   }
 }
 
-// One wave per token.  row16 = row size in 16-byte units.  Non-temporal accesses: rows written with the
-// default policy stay dirty in the memory-side cache, and the next large read pays for writing them
-// back.  (Measured, 65536 tokens of 8 KiB, k = 2: this kernel 292 -> 280 us, 5.75 TB/s, and the
-// routing of the batch that follows 143 -> 102 us; hint on the stores alone 311 / 101 us; 8192 tokens
-// of 4 KiB, k = 6: 44 -> 41 us, the up-projection that reads the rows unchanged.)
+// One wave per token.  row16 = row size in 16-byte units.  The stores have the non-temporal hint: rows
+// written with the default policy stay dirty in the memory-side cache, and the next large read pays for
+// writing them back.  X_STREAM: the loads too; where x fits that cache, the routing has just left it there.
+// (Measured, route + permute + combine, loads with the hint / without: x of 245 MB, 30000 tokens, d = 5120,
+// k = 1 276 / 267 us; 98 MB, 12000 tokens, k = 3, d = 4096, this call alone 83 / 65; 295 MB, 36000 tokens,
+// d = 4096, k = 2 337 / 347; 537 MB 634 / 675.  No hint at all: 65536 tokens of 8 KiB, k = 2 725 us, 9000
+// tokens of 4 KiB, k = 6 151, with it on the stores 139.)
+constexpr int64_t MEMORY_SIDE_CACHE_BYTES = int64_t(256) << 20;
+template <bool X_STREAM>
 __global__ __launch_bounds__(256) void gather_kernel(const uint4* __restrict__ x,
                                                      const int32_t* __restrict__ dst_row,
                                                      uint4* __restrict__ x_perm, int T, int k,
@@ -293,13 +297,13 @@ __global__ __launch_bounds__(256) void gather_kernel(const uint4* __restrict__ x
   if (lane < k) my_dst = dst_row[static_cast<int64_t>(t) * k + lane];
   if (static_cast<unsigned>(my_dst) >= static_cast<unsigned>(A)) my_dst = 0;
   const uint4* src = x + static_cast<int64_t>(t) * row16;
-  constexpr int UNR = 2;   // 16-byte loads in flight per lane (four: as fast or up to 3 % slower)
+  constexpr int UNR = 4;   // 16-byte loads in flight per lane (two: as fast or up to 17 % slower)
   for (int c0 = 0; c0 < row16; c0 += UNR * MOE_WAVE) {
     uint4 v[UNR];
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
       const int c = c0 + u * MOE_WAVE + lane;
-      if (c < row16) v[u] = nt_load(src + c);
+      if (c < row16) v[u] = X_STREAM ? nt_load(src + c) : src[c];
     }
     for (int j = 0; j < k; ++j) {
       const int dst = __shfl(my_dst, j);
@@ -383,7 +387,8 @@ static int count_and_permute_impl(const moe_shape_t* shape, const void* x, const
                        grid, counts, offsets, dst_row, src_assign);
   }
   if (copy) {
-    hipLaunchKernelGGL(gather_kernel, dim3((T + 3) / 4), dim3(256), 0, st,
+    const bool x_stream = static_cast<int64_t>(T) * row16 * 16 > MEMORY_SIDE_CACHE_BYTES;
+    hipLaunchKernelGGL(x_stream ? gather_kernel<true> : gather_kernel<false>, dim3((T + 3) / 4), dim3(256), 0, st,
                        static_cast<const uint4*>(x), dst_row, static_cast<uint4*>(x_perm), T, k,
                        row16, T * k);
   }

@@ -427,6 +427,32 @@ def test_count_and_permute_on_both_sides_of_the_single_launch_limit(T, d, E, k):
     check_dispatch(cfg, L["x"], idx)
 
 
+@pytest.mark.parametrize("chunks", [1, 63, 255, 256, 257, 520])
+def test_count_and_permute_row_copy_at_the_edges_of_its_steps(chunks):
+    # above 6144 assignments a wave copies 256 chunks of 16 bytes of a token's row per step
+    cfg = si.small_config(T=2100, d=chunks * 8, E=7, k=3, F=64)
+    L = si.make_layer(cfg, parts=("x",))
+    check_dispatch(cfg, L["x"], np.random.default_rng(chunks).integers(0, 7, size=(cfg.T, 3)).astype(np.int32))
+
+
+@pytest.mark.parametrize("T", [65536, 65537, 100001])
+def test_count_and_permute_row_copy_around_the_size_of_the_memory_side_cache(T):
+    # x of 256 MiB, where its loads turn to streaming, and past it
+    d, E = 2048, 5
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    x = torch.empty((T, d), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    idx = torch.randint(0, E, (T, 1), dtype=torch.int32, device="cuda", generator=gen)
+    counts, offsets, dst, src = (torch.zeros(n, dtype=torch.int32, device="cuda") for n in (E, E + 1, T, T))
+    x_perm = torch.zeros_like(x)
+    sh = B.make_shape(T, d, E, 1, 64, si.BF16, 1)
+    nb = B.moe_workspace_bytes(sh)
+    ws = torch.empty((nb,), dtype=torch.uint8, device="cuda")
+    B.moe_count_and_permute(sh, x, idx, counts, offsets, dst, src, x_perm, ws, nb)
+    torch.cuda.synchronize()
+    order = torch.sort(idx[:, 0].long(), stable=True).indices
+    assert torch.equal(src.long(), order) and torch.equal(x_perm, x[order])
+
+
 def test_count_and_permute_leaves_invalid_experts_out():
     cfg = si.small_config(T=301, d=64, E=6, k=2, F=64)
     idx = np.random.default_rng(2).integers(0, 6, size=(cfg.T, 2)).astype(np.int32)
