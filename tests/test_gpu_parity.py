@@ -761,20 +761,36 @@ SPLIT_CASES = [
     (dict(T=600, d=6144, E=2, k=1, F=256), True),     # up-projection (gated) cut in 4
     (dict(T=700, d=1024, E=2, k=1, F=6144, seed=11), None),   # 350 rows per expert: two even tiles of 176 rows each
     (dict(T=300, d=1024, E=2, k=1, F=2048), False),   # reductions too short: exactly the plain call
+    # given rows per expert: four weight buffers (65 to 128 rows), both GEMMs
+    (dict(rows=(80, 66, 100, 125), d=1024, F=6144), True),
+    (dict(rows=(80, 66, 100, 128), d=6144, F=256), True),
+    (dict(rows=(200, 130, 256), d=6144, F=256), True),       # three, gated
+    (dict(rows=(544, 560), d=1024, F=6144), True),           # tiles of one expert on both sides of 256 rows
+    (dict(rows=(400, 410), d=8192, F=256), True),            # gated, two buffers for experts of two tiles
+    (dict(rows=(700, 690), d=1024, F=6144), True),           # 640 rows and more: the default policy's kernels
+    (dict(rows=(700, 690), d=6144, F=256), True),
+    (dict(rows=(500, 40, 40, 40, 30, 1, 65, 190), d=1024, F=6144), True),   # a hot expert in tiles of up to 192 rows
 ]
 
 
 @pytest.mark.parametrize("case,expect_split", SPLIT_CASES,
-                         ids=lambda c: "T{T}_d{d}_E{E}_k{k}_F{F}".format(**c) if isinstance(c, dict) else "")
+                         ids=lambda c: "_".join(f"{n}{v}" for n, v in c.items()) if isinstance(c, dict) else "")
 @pytest.mark.parametrize("gathered", [False, True])
 def test_grouped_ffn_with_split_tiles(case, expect_split, gathered):
     """moe_grouped_ffn_ws: tiles of an under-filled last round are computed in parts along K and
     added up by the launch after the GEMM.  Oracle parity, run-to-run identical bits whatever the
     workspace held before, rows within a bf16 step of the call without a workspace; where the
     case says so, the split did happen (some bits differ) or cannot (identical bits)."""
+    case = dict(case)
+    rows = case.pop("rows", None)
+    if rows:
+        case.update(T=sum(rows), E=len(rows), k=1)
     cfg = si.small_config(**case)
     L = si.make_layer(cfg)
-    idx, _, _ = orc.route(L["x"], L["w_gate"], cfg.k, cfg.renorm)
+    if rows:
+        idx = np.random.default_rng(len(rows)).permutation(np.repeat(np.arange(cfg.E, dtype=np.int32), rows))[:, None]
+    else:
+        idx, _, _ = orc.route(L["x"], L["w_gate"], cfg.k, cfg.renorm)
     _, offsets = orc.expert_load(idx, cfg.E)
     dst, src = orc.permutation(idx, cfg.E)
     x_perm = orc.permute_rows(L["x"], dst, cfg.k)
