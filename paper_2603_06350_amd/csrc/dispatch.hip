@@ -277,15 +277,23 @@ __global__ __launch_bounds__(DR_THREADS) void rank_direct_kernel(
   }
 }
 
-// One wave per token.  row16 = row size in 16-byte units.  The stores have the non-temporal hint: rows
-// written with the default policy stay dirty in the memory-side cache, and the next large read pays for
-// writing them back.  X_STREAM: the loads too; where x fits that cache, the routing has just left it there.
-// (Measured, route + permute + combine, loads with the hint / without: x of 245 MB, 30000 tokens, d = 5120,
-// k = 1 276 / 267 us; 98 MB, 12000 tokens, k = 3, d = 4096, this call alone 83 / 65; 295 MB, 36000 tokens,
-// d = 4096, k = 2 337 / 347; 537 MB 634 / 675.  No hint at all: 65536 tokens of 8 KiB, k = 2 725 us, 9000
-// tokens of 4 KiB, k = 6 151, with it on the stores 139.)
+// One wave per token.  row16 = row size in 16-byte units.  Where the accesses take the non-temporal hint
+// (all measurements in us):
+//   OUT_STREAM, the stores: rows written with the default policy stay dirty in the 256 MB memory-side cache.
+//     While x and x_perm fit it, and the experts are compute-bound, that is where the up-projection finds
+//     them (whole four-call layer, with the hint / without: 64-expert shape at 3500 / 6000 tokens
+//     509 / 478 and 658 / 635, skewed at 8192 tokens 948 / 939, llama4 shape at 8192 tokens 1794 / 1765).  Past
+//     that size the next large read pays for writing them back (route + permute + combine: 65536
+//     tokens, d = 4096, k = 2 632 / 698; 24000 tokens, d = 5120, k = 1 216 / 251), and where an FFN of few
+//     rows per expert streams its weights, the write-backs cost that stream (128-expert shape at 1500 / 4096
+//     tokens, 94 and 256 rows per expert, 987 / 1049 and 1453 / 1488).
+//   X_STREAM, the loads: where x fits the cache, the routing has just left it there (the same three calls,
+//     with / without: x of 245 MB, 24000 tokens, d = 5120, k = 1 234 / 216; 295 MB, 36000 tokens, d = 4096,
+//     k = 2 337 / 347; 537 MB 634 / 675), unless x_perm's rows push it out meanwhile (d = 4096: 20000
+//     tokens, k = 4, 819 MB with x_perm, 312 / 312; 32000, k = 4, 1311 MB 488 / 502; 15000, k = 8, 1106 MB 485 / 494).
 constexpr int64_t MEMORY_SIDE_CACHE_BYTES = int64_t(256) << 20;
-template <bool X_STREAM>
+constexpr int WEIGHT_BOUND_ROWS = 256;     // mean rows per expert up to which the FFN waits for its weights
+template <bool X_STREAM, bool OUT_STREAM>
 __global__ __launch_bounds__(256) void gather_kernel(const uint4* __restrict__ x,
                                                      const int32_t* __restrict__ dst_row,
                                                      uint4* __restrict__ x_perm, int T, int k,
@@ -311,7 +319,9 @@ __global__ __launch_bounds__(256) void gather_kernel(const uint4* __restrict__ x
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
         const int c = c0 + u * MOE_WAVE + lane;
-        if (c < row16) nt_store(out + c, v[u]);
+        if (c >= row16) continue;
+        if (OUT_STREAM) nt_store(out + c, v[u]);
+        else out[c] = v[u];
       }
     }
   }
@@ -387,8 +397,13 @@ static int count_and_permute_impl(const moe_shape_t* shape, const void* x, const
                        grid, counts, offsets, dst_row, src_assign);
   }
   if (copy) {
-    const bool x_stream = static_cast<int64_t>(T) * row16 * 16 > MEMORY_SIDE_CACHE_BYTES;
-    hipLaunchKernelGGL(x_stream ? gather_kernel<true> : gather_kernel<false>, dim3((T + 3) / 4), dim3(256), 0, st,
+    const int64_t x_bytes = static_cast<int64_t>(T) * row16 * 16;
+    const int64_t total_bytes = x_bytes * (k + 1);
+    const bool x_stream = x_bytes > MEMORY_SIDE_CACHE_BYTES || total_bytes > 3 * MEMORY_SIDE_CACHE_BYTES;
+    const bool out_stream = total_bytes > MEMORY_SIDE_CACHE_BYTES || A / E <= WEIGHT_BOUND_ROWS;
+    const auto kernel = x_stream ? gather_kernel<true, true>
+                        : out_stream ? gather_kernel<false, true> : gather_kernel<false, false>;
+    hipLaunchKernelGGL(kernel, dim3((T + 3) / 4), dim3(256), 0, st,
                        static_cast<const uint4*>(x), dst_row, static_cast<uint4*>(x_perm), T, k,
                        row16, T * k);
   }

@@ -428,16 +428,19 @@ def test_count_and_permute_on_both_sides_of_the_single_launch_limit(T, d, E, k):
 
 
 @pytest.mark.parametrize("chunks", [1, 63, 255, 256, 257, 520])
-def test_count_and_permute_row_copy_at_the_edges_of_its_steps(chunks):
-    # above 6144 assignments a wave copies 256 chunks of 16 bytes of a token's row per step
-    cfg = si.small_config(T=2100, d=chunks * 8, E=7, k=3, F=64)
+@pytest.mark.parametrize("E", [7, 24, 25])
+def test_count_and_permute_row_copy_at_the_edges_of_its_steps(E, chunks):
+    # above 6144 assignments a wave copies 256 chunks of 16 bytes of a token's row per step; with up to 256
+    # rows per expert (E = 25: 252, 24: 262) the stores are streamed
+    cfg = si.small_config(T=2100, d=chunks * 8, E=E, k=3, F=64)
     L = si.make_layer(cfg, parts=("x",))
-    check_dispatch(cfg, L["x"], np.random.default_rng(chunks).integers(0, 7, size=(cfg.T, 3)).astype(np.int32))
+    check_dispatch(cfg, L["x"], np.random.default_rng(chunks).integers(0, E, size=(cfg.T, 3)).astype(np.int32))
 
 
-@pytest.mark.parametrize("T", [65536, 65537, 100001])
+@pytest.mark.parametrize("T", [32768, 32769, 65536, 65537, 100001])
 def test_count_and_permute_row_copy_around_the_size_of_the_memory_side_cache(T):
-    # x of 256 MiB, where its loads turn to streaming, and past it
+    # x and x_perm of 256 MiB together, where the stores turn to streaming, x of 256 MiB alone, where the
+    # loads do, and past it
     d, E = 2048, 5
     gen = torch.Generator(device="cuda").manual_seed(T)
     x = torch.empty((T, d), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
