@@ -365,14 +365,12 @@ static int count_and_permute_impl(const moe_shape_t* shape, const void* x, const
                                   hipStream_t st) {
   const int T = shape->T, k = shape->k, E = shape->E;
   const int nth = dispatch_threads(E);
-  const int nb = (T + nth - 1) / nth;
+  const int grid = (T + nth - 1) / nth;
   const size_t lds = static_cast<size_t>(E) * nth * 2 + static_cast<size_t>(E) * 8;
-  // T == 0 still defines counts = 0 and offsets = 0: one block with no tokens does that.
-  const int grid = nb > 0 ? nb : 1;
   const int64_t A = static_cast<int64_t>(T) * k;
   bool copy = T > 0 && x_perm;
   const int row16 = static_cast<int>(static_cast<int64_t>(shape->d) * elem_bytes(shape->dtype) / 16);
-  if (A <= DR_MAX_A) {
+  if (A <= DR_MAX_A) {                            // (also A = 0: counts and offsets become zeros)
     const int lds_keys = static_cast<int>((A + DR_STEP - 1) / DR_STEP) * DR_STEP * 4;
     const int blocks = static_cast<int>(((A + 1) / 2 + E + DR_THREADS / MOE_WAVE - 1) / (DR_THREADS / MOE_WAVE));
     hipLaunchKernelGGL(copy ? rank_direct_kernel<true> : rank_direct_kernel<false>, dim3(blocks), dim3(DR_THREADS),

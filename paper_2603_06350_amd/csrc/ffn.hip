@@ -9,8 +9,9 @@
 // accumulators, h stored once) and a plain one for W2.  Both are ragged grouped
 // GEMMs, one launch each: the tile list is derived on the device from `offsets`, so the host
 // never learns the expert loads.
-//   an expert's c rows are cut into ceil(c / 320) tiles of nearly equal height (multiples of 16
-//   rows), each against 256 weight rows; the tile's height then picks its pipeline:
+//   an expert's c rows are cut into ceil(c / bm) tiles of nearly equal height (multiples of 16 rows;
+//   bm is 320, less where experts hold few rows: most_tile_rows), each against 256 weight rows;
+//   the height of a tile, or of the expert's highest, then picks its pipeline:
 //   up to 64 rows   ring tile (ffn_ring_tile): paced by the weight stream, four-stage LDS ring;
 //   65 and more     even tile (ffn_even_tile): hand-ordered MFMA pipeline, two activation buffers and
 //                   as many weight buffers as the LDS holds beside them (four, three or two).
@@ -299,7 +300,7 @@ constexpr int ROWB = BK * 2;    // bytes per tile row in LDS (eight 16-byte chun
 // bytes with zeros for both operands.  Weight rows past N do the same in the even tiles (their row
 // groups share one per-lane offset); the ring tiles re-read the last valid row.  The alternative
 // these shapes had before, a 64 x 64 fp32-FMA kernel, ran at 50 TFLOP/s (T = 1501, d = 1048, E = 12,
-// k = 3, F = 1864: 1.10 ms per layer, now 0.133).
+// k = 3, F = 1864: 1.10 ms per layer, now 0.127).
 constexpr uint32_t PAST_END = 0x80000000u;
 // what a lane that loads chunk `chunk` (0 .. 7) of its rows adds to the offset in the last stage
 __device__ __forceinline__ uint32_t ragged_tail(int K, int chunk) {
@@ -643,13 +644,13 @@ __device__ __forceinline__ void ffn_ring_sum_tile(const GemmArgs& p, const TileC
 }
 
 // --------------------------------------------------------------------------------------------
-// Even tiles: an expert's c rows are cut into ceil(c / 320) tiles of (nearly) equal height, a
+// Even tiles: an expert's c rows are cut into tiles of (nearly) equal height, a
 // multiple of 16 rows each, so no segment leaves a small remainder that would have to stream the
 // expert's weights once more for a handful of rows: the Mixtral-shaped batch (about 1024 rows
 // per expert) runs as four tiles of 256 or 272 rows per expert, whatever the counts are.
-// Block tile: up to 320 activation rows x 256 weight rows, K step 64, two LDS stages of 72 KiB
-// (the two activation buffers first, then the two weight buffers, so that a fragment read
-// selects the buffer with its 16-bit offset field).
+// Block tile: up to 320 activation rows x 256 weight rows, K step 64, two activation buffers, then
+// two to four weight buffers in LDS (activations first, so that a fragment read selects
+// their buffer with its 16-bit offset field).
 // 8 waves as 4 (rows) x 2 (weight rows); the tile's 16-row sub-tiles are dealt to the four wave
 // rows as evenly as possible (each takes MIV = 0 .. 5 of them, the first wave rows one more than
 // the last), so a wave holds up to 5 x 8 accumulator tiles.
@@ -662,8 +663,8 @@ __device__ __forceinline__ void ffn_ring_sum_tile(const GemmArgs& p, const TileC
 // before it is needed.  LDS reads return in order, so "my fragment has landed" is a count of the
 // reads issued after it.  Inline asm pins the order; the compiler does not see these LDS reads, so
 // it inserts no waits of its own.  A stage's barrier sits between the two parts of its second
-// k-step: by then every fragment of the stage is in registers, the stage's buffer takes the loads
-// of the stage after next, and the other buffer (landed: vmcnt(0)) is read from.
+// k-step: by then every fragment of the stage is in registers, the stage's buffers take the loads
+// of a later stage, and the next stage's, which have landed, are read from.
 //
 // Who issues the loads.  A wave that issues a burst of direct-to-LDS loads is held at every one of
 // them until the address unit takes it, and issues no MFMA meanwhile.  If all eight waves load
@@ -671,8 +672,8 @@ __device__ __forceinline__ void ffn_ring_sum_tile(const GemmArgs& p, const TileC
 // the matrix pipe idles.  So the waves form two sets of four, {0-3} and {4-7} (waves w and w + 4 share
 // a SIMD), that take turns: set (stage & 1) issues the whole stage while the other set goes
 // straight on with its MFMAs, so every SIMD always has a wave that multiplies.  Measured on the
-// Mixtral shape: up-projection 6 % faster than with every wave loading; llama4 shape (one tile of 256
-// rows per expert) 690 -> 646 us with three weight buffers and turns.  (One set for the weight
+// Mixtral shape: up-projection 6 % faster than with every wave loading; llama4 shape (one tile of about 256
+// rows per expert), whole layer 1050 -> 1036 us with turns and three weight buffers.  (One set for the weight
 // rows and the other for the activation rows: 12 to 20 % slower on tiles of 65 to 128 rows.)
 constexpr int EVEN_BM = 320;
 constexpr int EVEN_ACT = EVEN_BM * ROWB;                     // one activation buffer
@@ -707,7 +708,6 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
   constexpr int BM = MI * 64, NI = 8;
   constexpr int NIH = GATED ? NI / 2 : NI;
   constexpr int NLA = BM / 8 / 4;                 // up to 10 activation row groups per loading wave and stage
-  constexpr int NLW = BROWS / 8 / 4;              // up to 8 weight row groups
   constexpr int ACT = BM * ROWB;                  // one activation buffer
   constexpr int NWB = even_wgt_buffers(MI);
   constexpr int W_BASE = 2 * ACT;                 // LDS offset of the weight buffers
@@ -734,8 +734,8 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
 
   // ---- global -> LDS.  A wave instruction fills an 8-row group of 1 KiB.  A loading wave takes
   //      activation groups i * ns + lw (only those that hold a valid row) and weight groups
-  //      i * ns + lw (only those inside the weight matrix: N - n0 is a multiple of 64, so a group
-  //      is inside or outside as a whole).  The rows of a wave's weight groups are multiples of
+  //      i * ns + lw (N - n0 is a multiple of 64, RAGGED: of 8, so a group is inside the weight
+  //      matrix or outside as a whole).  The rows of a wave's weight groups are multiples of
   //      32 rows apart (same swizzle): one per-lane offset, the rest is a scalar.  Activation rows
   //      past the end of the segment re-read its last row.
   const bool gathered = p.src_assign != nullptr;
@@ -992,8 +992,8 @@ __device__ __forceinline__ void ffn_even_tile(const GemmArgs& p, const TileCoord
     ffn_store_part<MI, NI, NW * MOE_WAVE>(acc, tc, p);
     return;
   }
-  // the store turns the sub-tiles around in activation buffer 0 (every wave has read its last
-  // fragments before the store's barrier)
+  // the store turns the sub-tiles around in the first 20 (gated) or 36 KiB of the LDS, whatever buffers lie
+  // there (every wave has read its last fragments before the store's barrier)
   ffn_store_tile<GATED, RAGGED, MI, NI, WN, NW>(acc, tc, p, lds, wave, lane, miv, row0);
 }
 
@@ -1072,7 +1072,7 @@ __global__ __launch_bounds__(512) void ffn_bf16_sum_parts_kernel(GemmArgs p) {
 // which spreads the few hundred tiles of a small batch over the chip and lets one block's barriers
 // and epilogue overlap the others' loops.  Each wave takes all the tile's 16-row sub-tiles against
 // its own 16 weight rows of each matrix, so the waves are equally busy whatever the row count is;
-// segments are cut evenly, so 129 rows are 48 + 48 + 33 and not 64 + 64 + 1.  K step 32
+// segments are cut evenly, so 129 rows are 48 + 32 + 49 and not 64 + 64 + 1.  K step 32
 // (128-byte tile rows as in the bf16 kernels, the same swizzle and chunk order; a chunk is four
 // k-values, one per instruction).  Bound by the matrix pipe where there are tiles enough (8000 tokens,
 // d = 1024, E = 16, k = 2, F = 2048: 125 TFLOP/s, the vendor's fp32 GEMM of that size 141), by the
@@ -1300,8 +1300,8 @@ static int device_cu_count() {
 static int64_t max_m_tiles(int64_t A, int E, int bm) { return A / bm + (E < A ? E : A); }
 
 // `split`: the launch may use the workspace for split tiles if the caller brought one.  Only
-// GEMMs with a long reduction do: a part must be worth the exchange (one 256 to 320 KiB store per
-// part, the summing launch), and a tile of fewer than 96 stages is too short for that (measured:
+// GEMMs with a long reduction do: a part must be worth the exchange (one store of 64 to 320 KiB of
+// accumulators per part, the summing launch), and a tile of fewer than 96 stages is too short for that (measured:
 // the up-projections of the four model shapes gain nothing, their down-projections up to 27 %).
 constexpr int SPLIT_MIN_K = 96 * BK_ELEMS;
 

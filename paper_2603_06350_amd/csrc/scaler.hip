@@ -20,8 +20,6 @@
 
 namespace moe {
 
-constexpr int SC_Q = MOE_MAX_E / MOE_WAVE;   // experts per lane
-
 // Wave-wide maximum / minimum of a 32-bit value by DPP (lane swaps in quads, half-row and row mirrors,
 // two row broadcasts), read from lane 63.  ROWS = false: of lanes 0 .. 15 only (four steps).
 template <bool MAX, bool ROWS = true> __device__ __forceinline__ uint32_t wave_extreme(uint32_t v) {

@@ -523,20 +523,20 @@ def check_ffn(cfg, L, idx):
 
 
 FFN_CASES = [
-    dict(T=300, d=256, E=8, k=2, F=384),          # MFMA path, 75 rows/expert: 64-row tiles only, ragged
-    dict(T=600, d=256, E=8, k=2, F=384),          # 150 rows/expert: partial 256-row tiles + remainders
-    dict(T=1500, d=128, E=2, k=1, F=256),         # MFMA path, 256-row tiles (>= 512 rows/expert)
-    dict(T=900, d=192, E=3, k=2, F=320),          # 256-row tiles, N tails (320 = 2.5 x 128, 192 < 256)
+    dict(T=300, d=256, E=8, k=2, F=384),          # 75 rows/expert: tiles of up to 128 rows
+    dict(T=600, d=256, E=8, k=2, F=384),          # 150 rows/expert: one tile per expert
+    dict(T=1500, d=128, E=2, k=1, F=256),         # 750 rows/expert: three tiles per expert
+    dict(T=900, d=192, E=3, k=2, F=320),          # 600 rows/expert, N tails (320 = 2.5 x 128, 192 < 256)
     dict(T=64, d=512, E=64, k=6, F=128),          # many small / empty experts
-    dict(T=100, d=200, E=4, k=2, F=104),          # bf16 generic path (d, F not multiples of 64)
+    dict(T=100, d=200, E=4, k=2, F=104),          # d, F not multiples of 64
     dict(T=64, d=128, E=8, k=2, F=256, dtype=si.F32, x_std=0.02, w_std=0.02),
     dict(T=45, d=36, E=5, k=2, F=52, dtype=si.F32),
 ]
 
 
 def test_grouped_ffn_few_rows_per_expert_with_one_hot_expert():
-    # few rows per expert on average (everything runs as 64-row tiles in one launch per GEMM),
-    # but one expert holds several tiles' worth of rows and most are empty
+    # few rows per expert on average (tiles of up to 128 rows), but one expert holds several tiles'
+    # worth of rows and most are empty
     cfg = si.small_config(T=400, d=256, E=64, k=1, F=384)
     L = si.make_layer(cfg)
     rng = np.random.default_rng(5)
@@ -574,8 +574,7 @@ def test_grouped_ffn_every_stage_count_of_the_two_stage_pipeline(d, F):
 @pytest.mark.parametrize("T,E", [(37, 5), (1000, 3), (1700, 11)])
 def test_grouped_ffn_widths_that_are_multiples_of_8(T, E, d, F):
     # K tails of 1 to 7 chunks (also a single, partial stage), N tails of one row group up to one
-    # short of a tile; ring tiles, even tiles with all waves loading (154 rows per expert) and with
-    # the waves taking turns (333), ragged last sub-tiles
+    # short of a tile; ring tiles (7 rows per expert), even tiles (154 and 333), ragged last sub-tiles
     cfg = si.small_config(T=T, d=d, E=E, k=1, F=F, seed=d + F)
     L = si.make_layer(cfg)
     idx = np.random.default_rng(T).integers(0, E, size=(T, 1)).astype(np.int32)
@@ -699,11 +698,11 @@ def test_grouped_ffn_rows_around_the_limit_of_32_bit_offsets(dtype, T, d, F, for
 
 @pytest.mark.parametrize("rows", [1, 15, 16, 17, 47, 64, 65, 130, 255, 257, 319, 320, 321, 336, 641, 1000])
 def test_grouped_ffn_even_tiles_every_wave_share(rows):
-    # one hot expert with `rows` rows among experts of 128 rows (so that the mean stays above the
-    # even tiles' threshold): its tiles give the waves every count of sub-tiles from 0 to 5, tiles
-    # below and at the 320-row limit, and segments that need two or three tiles; both ways of
-    # sharing the loads among the waves (the threshold on the mean rows per expert picks one)
-    for E, others in ((3, 600), (9, 150)):             # mean rows per expert above / below 384
+    # one expert with `rows` rows among others of 600 or 150: its tiles give the waves every count of
+    # sub-tiles from 0 to 5, tiles below and at the 320-row limit, and segments that need two or three
+    # tiles; mean rows per expert above and below the 384 from which experts of several tiles may keep two
+    # weight buffers in the up-projection (d = 128 is a power of two)
+    for E, others in ((3, 600), (9, 150)):
         cfg = si.small_config(T=rows + (E - 1) * others, d=128, E=E, k=1, F=256, seed=rows + E)
         L = si.make_layer(cfg)
         idx = np.zeros((cfg.T, 1), dtype=np.int32)
@@ -760,7 +759,7 @@ def test_grouped_ffn_tiles_of_one_expert_on_both_sides_of_a_pipeline_s_limit(row
 SPLIT_CASES = [
     # (shape, whether some tile must have been split); a GEMM is eligible from K = 6144 on
     (dict(T=600, d=1024, E=2, k=1, F=6144), True),    # even tiles, down-projection cut in 4
-    (dict(T=64, d=1024, E=4, k=2, F=6144), True),     # 64-row tiles only (32 rows per expert)
+    (dict(T=64, d=1024, E=4, k=2, F=6144), True),     # ring tiles (32 rows per expert)
     (dict(T=600, d=6144, E=2, k=1, F=256), True),     # up-projection (gated) cut in 4
     (dict(T=700, d=1024, E=2, k=1, F=6144, seed=11), None),   # 350 rows per expert: two even tiles of 176 rows each
     (dict(T=300, d=1024, E=2, k=1, F=2048), False),   # reductions too short: exactly the plain call
