@@ -11,7 +11,7 @@
 // never learns the expert loads.
 //   an expert's c rows are cut into ceil(c / bm) tiles of nearly equal height (multiples of 16 rows;
 //   bm is 320, less where experts hold few rows: most_tile_rows), each against 256 weight rows;
-//   the height of a tile, or of the expert's highest, then picks its pipeline:
+//   the height of a tile, or of the expert's highest, then picks its pipeline (decode_tile):
 //   up to 64 rows   ring tile (ffn_ring_tile): paced by the weight stream, four-stage LDS ring;
 //   65 and more     even tile (ffn_even_tile): hand-ordered MFMA pipeline, two activation buffers and
 //                   as many weight buffers as the LDS holds beside them (four, three or two).
@@ -120,14 +120,16 @@ constexpr int WGT_NT_MAX_SHARERS = 2;
 // An expert with c rows has ceil(c / bm) tiles; the segment's 16-row sub-tiles are dealt to them evenly.
 // Tile order: expert-major, then n-tile, then m-tile (m fastest), cut into 8 contiguous ranges,
 // one per XCD.
-// BY_EXPERT: all tiles of an expert (and the sister pieces of a tile) take the pipeline that the highest of
-// them needs; otherwise each the one for its own rows.  Tiles that read the same weight rows side by side
+// BY_EXPERT: tiles of 129 and more rows take the pipeline that the highest tile of their expert needs,
+// otherwise each the one for its own rows.  Tiles that read the same weight rows side by side
 // with the non-temporal hint have to keep pace, or the second one finds them gone from the L2; in two
 // different pipelines they drift apart.  (Measured at 500 to 530 rows per expert, where most
 // experts are a tile below and one above 256 rows, by expert against by own rows: llama4 shape at 8480
 // tokens 1925 -> 1830 us, phi shape at 4000 tokens 1115 -> 1095, down-projection of the Mixtral shape at 2000
 // tokens 407 -> 389.  Where weight rows stay in the L2, !WNT, the third weight buffer of the lower tiles is
-// worth more: 64-expert shape at 8192 tokens, down-projection 266 us by own rows, 273 by expert.)
+// worth more: 64-expert shape at 8192 tokens, down-projection 266 us by own rows, 273 by expert.  Low tiles
+// by expert too: skewed 64-expert layer at 200 to 700 tokens 3 to 4 % slower, Mixtral shape at 480 tokens
+// 4 %, at 260 and 360 tokens 1 to 2 % faster.)
 template <bool SPLIT = false, bool BY_EXPERT = false>
 __device__ __forceinline__ bool decode_tile(const GemmArgs& p, TileCoord& tc) {
   const int32_t* __restrict__ offsets = p.offsets;
@@ -251,7 +253,7 @@ __device__ __forceinline__ bool decode_tile(const GemmArgs& p, TileCoord& tc) {
   const int b1 = 2 * ((m_idx + 1) * pairs / m_tiles) + odd;
   int s0 = b0, s1 = b1;
   int top = b1 - b0;
-  if (BY_EXPERT) {
+  if (BY_EXPERT && m_tiles > 1 && top > NSPLIT_ROWS / 16) {     // (the division is skipped where it decides nothing)
     const int q = pairs / m_tiles;
     top = max(2 * (q + (q * m_tiles < pairs ? 1 : 0)), 2 * q + odd);
   }
@@ -269,7 +271,7 @@ __device__ __forceinline__ bool decode_tile(const GemmArgs& p, TileCoord& tc) {
       tc.sharers = m_tiles + pieces - 1;
       s0 = b0 + m_piece * n_sub / pieces;
       s1 = b0 + (m_piece + 1) * n_sub / pieces;
-      top = BY_EXPERT ? (n_sub + pieces - 1) / pieces : s1 - s0;
+      top = s1 - s0;
     }
   }
   tc.m_begin = seg_begin + s0 * 16;

@@ -749,9 +749,9 @@ def test_grouped_ffn_whole_rounds_and_under_filled_last_rounds(rows, d, F):
 @pytest.mark.parametrize("d", [192, 256, 520])
 @pytest.mark.parametrize("rows", [(544, 540, 530, 560), (272, 80, 80, 80, 80, 80, 80), (130, 40, 40, 40), (300, 257, 400, 640)])
 def test_grouped_ffn_tiles_of_one_expert_on_both_sides_of_a_pipeline_s_limit(rows, d):
-    # experts of two tiles with one up to and one above 256, 128 or 64 rows: both take the higher one's
-    # pipeline; the first and last case have the mean rows at which a power-of-two reduction (d = 256)
-    # keeps two weight buffers in the up-projection
+    # experts of two tiles with one up to and one above 256 rows, which both take the higher one's pipeline,
+    # and with one up to and one above 128 or 64, which take their own; the first and last case have the
+    # mean rows at which a power-of-two reduction (d = 256) keeps two weight buffers in the up-projection
     cfg = si.small_config(T=sum(rows), d=d, E=len(rows), k=1, F=384 if d != 520 else 392, seed=d + rows[0])
     check_ffn(cfg, si.make_layer(cfg), np.repeat(np.arange(len(rows), dtype=np.int32), rows)[:, None])
 
