@@ -37,8 +37,8 @@
 // XCDs) walks a contiguous range of the tile list with the m-tiles of one weight
 // panel adjacent: CUs that share an L2 share weight tiles.
 //
-// fp32 layers: ffn_f32_kernel, smaller tiles on the fp32 matrix instruction.  Layers so wide that the
-// MFMA kernels' 32-bit offsets do not reach over a tile: ffn_wide_kernel.
+// fp32 layers: ffn_f32_kernel, smaller tiles, on the fp32 matrix instruction or on three bf16 pieces per value.
+// Layers so wide that the MFMA kernels' 32-bit offsets do not reach over a tile: ffn_wide_kernel.
 #include <type_traits>
 
 #include "moe_internal.h"
@@ -1067,47 +1067,97 @@ __global__ __launch_bounds__(512) void ffn_bf16_sum_parts_kernel(GemmArgs p) {
 }
 
 // --------------------------------------------------------------------------------------------
-// fp32 layers: v_mfma_f32_16x16x4_f32 (fp32 products and sums; twice the rate of the vector FMA).
-// The matrix instruction is 32 cycles for two 4-byte operands per lane, so LDS and L2 have ten times
-// the bf16 kernels' time per byte and small tiles cost little: a block is 4 waves on at most BM = 32
-// or 64 activation rows x 64 weight rows (gated: 64 of each matrix), three blocks or more per CU,
-// which spreads the few hundred tiles of a small batch over the chip and lets one block's barriers
-// and epilogue overlap the others' loops.  Each wave takes all the tile's 16-row sub-tiles against
-// its own 16 weight rows of each matrix, so the waves are equally busy whatever the row count is;
-// segments are cut evenly, so 129 rows are 48 + 32 + 49 and not 64 + 64 + 1.  K step 32
-// (128-byte tile rows as in the bf16 kernels, the same swizzle and chunk order; a chunk is four
-// k-values, one per instruction).  Bound by the matrix pipe where there are tiles enough (8000 tokens,
-// d = 1024, E = 16, k = 2, F = 2048: 125 TFLOP/s, the vendor's fp32 GEMM of that size 141), by the
-// last round below.  Two stages for the gated tiles (three: 11 % slower, a block per CU less).
-// The 64 x 64 vector-FMA kernel this replaces: 1000 tokens of that shape 869 us for both GEMMs, now 280.
+// fp32 layers.  Blocks of 4 waves; each wave takes all the tile's 16-row sub-tiles against its own 16 weight
+// rows of each matrix, so the waves are equally busy whatever the row count is; segments are cut evenly,
+// so 129 rows are 48 + 32 + 49 and not 64 + 64 + 1.  K step 32 (128-byte rows).  Two ways to multiply:
+//
+// f32_split_tile (33 to 64 rows).  The bf16 matrix instruction is 16 times as fast as the fp32 one.  A value
+// is cut into three bf16 pieces, each the rounded rest of the ones before: they hold its 24 bits exactly, and of
+// the nine piece products the six above 2^-24 of the whole are multiplied, smallest first.  A wave's weight rows are
+// nobody else's, so they go from memory to registers in fragment order and are cut there; the activation
+// rows are cut once per block, by the thread that loads them, and shared through three LDS planes.
+// Error against 64-bit sums (2-norm, both GEMMs, four layers of K = 36 to 2048): 1.1e-7 to 7.4e-7, the fp32
+// instruction 1.7e-7 to 8.7e-7 (192 roundings per 1024 products against 256).
+// Bound by the vector instructions of the cutting (149 beside 48 MFMAs per wave and stage) and the matrix
+// pipe, which is busy 40 %: what counts is that one wave cuts while another multiplies, so three or four blocks
+// per CU and few registers (four blocks in a wave of 128 registers spill; two with stage s + 1 cut ahead
+// between the MFMAs of stage s: 5 to 10 % slower; rows of both operands through LDS: 10 %; 128-row tiles
+// 5 % faster at 2000 tokens, 10 % slower at 1000).
+//
+// f32_exact_rows (up to 32 rows).  v_mfma_f32_16x16x4_f32.  Few rows wait for their weights, and cutting them
+// would lengthen every stage's chain of load, cut, multiply (60 tokens of the shape below 94 -> 117 us).
+// Two stages for the gated tiles (three: 11 % slower, a block per CU less).
+//
+// (d = 1024, E = 16, k = 2, F = 2048, fp32 instruction alone -> now, us: 1000 tokens, up 153 -> 118, down 96 -> 75, 130 TFLOP/s;
+// whole layer of 2000 tokens 475 -> 375; d = 1280, E = 4, k = 1, F = 2400, 2000 tokens 363 -> 278.)
 // --------------------------------------------------------------------------------------------
-constexpr int F32_NW = 4, F32_BN = 64, F32_BK = 32;
+constexpr int F32_NW = 4, F32_BN = 64, F32_BK = 32, F32_BM = 64, F32_EXACT_ROWS = 32;
+constexpr int F32_PROW = F32_BK * 2;              // bytes of a row in a plane
+constexpr int F32_PLANE = F32_BM * F32_PROW;
 constexpr int f32_stages(bool gated) { return gated ? 2 : 3; }
-constexpr int ffn_f32_lds_bytes(bool gated, int bm) { return f32_stages(gated) * (bm + (gated ? 2 : 1) * F32_BN) * ROWB; }
+constexpr int ffn_f32_lds_bytes(bool gated) {
+  const int exact = f32_stages(gated) * (F32_EXACT_ROWS + (gated ? 2 : 1) * F32_BN) * ROWB, split = 2 * 3 * F32_PLANE;
+  return exact > split ? exact : split;
+}
 
-template <bool GATED, int BM>
-__global__ __launch_bounds__(F32_NW * MOE_WAVE, 3) void ffn_f32_kernel(GemmArgs p) {
-  extern __shared__ __align__(1024) unsigned char lds[];
-  constexpr int NMAT = GATED ? 2 : 1;
+// Buffer resources of a tile's operands (see the bf16 kernels).
+struct F32Operands {
+  __amdgpu_buffer_rsrc_t a, b0, b1;
+};
+template <bool GATED>
+__device__ __forceinline__ F32Operands f32_operands(const GemmArgs& p, const TileCoord& tc, int m_first) {
+  const float* A = static_cast<const float*>(p.a) + (p.src_assign ? 0 : static_cast<int64_t>(m_first) * p.K);
+  const int64_t b_off = (static_cast<int64_t>(tc.e) * p.N + tc.n0) * p.K;
+  const float* B0 = static_cast<const float*>(p.b0) + b_off;
+  const float* B1 = GATED ? static_cast<const float*>(p.b1) + b_off : B0;
+  return {__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(A), 0, 0x7FFFFFFF, 0x00020000),
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B0), 0, 0x7FFFFFFF, 0x00020000),
+          __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B1), 0, 0x7FFFFFFF, 0x00020000)};
+}
+
+// Accumulator (v, lane) is row lane % 16 of the sub-tile, columns 4 (lane / 16) .. + 3 of the wave's 16.
+template <bool GATED, int MI>
+__device__ __forceinline__ void f32_store(const f32x4_t (&acc)[GATED ? 2 : 1][MI], const GemmArgs& p, int n0, int m_first,
+                                          int m_end) {
+  const int lane = lane_id(), wave = threadIdx.x / MOE_WAVE;
+  float* out = static_cast<float*>(p.out);
+  const int c = n0 + wave * 16 + 4 * (lane >> 4);
+  const int32_t* out_map = GATED ? nullptr : p.out_map;
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi) {
+    int gr = m_first + mi * 16 + (lane & 15);
+    if (gr >= m_end || c >= p.N) continue;        // (N is a multiple of 4)
+    float scale = 1.f;
+    if (out_map) {
+      gr = min(max(out_map[gr], 0), p.out_rows - 1);
+      scale = p.out_scale[gr];
+    }
+    f32x4_t o;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float v = acc[0][mi][u];
+      o[u] = GATED ? silu_mul<true>(v, acc[GATED ? 1 : 0][mi][u]) : out_map ? v * scale : v;
+    }
+    *reinterpret_cast<f32x4_t*>(out + static_cast<int64_t>(gr) * p.N + c) = o;
+  }
+}
+
+// Rows m_first .. m_end - 1 (at most 32) of the tile on the fp32 matrix instruction.  Tile rows in LDS as in
+// the bf16 kernels (same swizzle and chunk order; a chunk is four k-values, one per instruction).
+template <bool GATED>
+__device__ __forceinline__ void f32_exact_rows(const GemmArgs& p, const TileCoord& tc, unsigned char* lds, int m_first,
+                                               int m_end) {
+  constexpr int NMAT = GATED ? 2 : 1, BM = F32_EXACT_ROWS;
   constexpr int NSTAGE = f32_stages(GATED);
   constexpr int STAGE = (BM + NMAT * F32_BN) * ROWB;
   constexpr int NLA = BM / 8 / F32_NW, NLB = F32_BN / 8 / F32_NW, NLOAD = NLA + NMAT * NLB;
   constexpr int MI = BM / 16;
-  TileCoord tc;
-  if (!decode_tile(p, tc)) return;
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MOE_WAVE);
   const int K = p.K, N = p.N, KT = (K + F32_BK - 1) / F32_BK;
   const int n0 = tc.n0;
-  const int rows_valid = min(tc.m_end - tc.m_begin, BM);
-  const bool gathered = p.src_assign != nullptr;
-  const float* A = static_cast<const float*>(p.a) + (gathered ? 0 : static_cast<int64_t>(tc.m_begin) * K);
-  const int64_t b_off = (static_cast<int64_t>(tc.e) * N + n0) * K;
-  const float* B0 = static_cast<const float*>(p.b0) + b_off;
-  const float* B1 = GATED ? static_cast<const float*>(p.b1) + b_off : B0;
-  const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(A), 0, 0x7FFFFFFF, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rs_b0 = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B0), 0, 0x7FFFFFFF, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rs_b1 = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B1), 0, 0x7FFFFFFF, 0x00020000);
+  const int rows_valid = min(m_end - m_first, BM);
+  const F32Operands rs = f32_operands<GATED>(p, tc, m_first);
   // instruction i of a wave fills 8-row group i * 4 + wave of the stage: activation rows, then the rows
   // of W1 (or W2), then of W3; rows past the end re-read the last valid one; chunks past K in the
   // last stage come out as zeros (see ragged_tail)
@@ -1119,7 +1169,7 @@ __global__ __launch_bounds__(F32_NW * MOE_WAVE, 3) void ffn_f32_kernel(GemmArgs 
     int r;
     if (i < NLA) {
       r = min(row, rows_valid - 1);
-      if (gathered) r = a_row_of(p, tc.m_begin + r);
+      if (p.src_assign) r = a_row_of(p, m_first + r);
     } else {
       r = min((row - BM) & (F32_BN - 1), N - 1 - n0);
     }
@@ -1132,7 +1182,7 @@ __global__ __launch_bounds__(F32_NW * MOE_WAVE, 3) void ffn_f32_kernel(GemmArgs 
 #pragma unroll
     for (int i = 0; i < NLOAD; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(
-          i < NLA ? rs_a : i < NLA + NLB ? rs_b0 : rs_b1,
+          i < NLA ? rs.a : i < NLA + NLB ? rs.b0 : rs.b1,
           (__attribute__((address_space(3))) void*)(lds + stage * STAGE + (i * F32_NW + wave) * 1024), 16,
           static_cast<int>(soff[i] | past), kt * ROWB, 0, 0);
   };
@@ -1156,8 +1206,7 @@ __global__ __launch_bounds__(F32_NW * MOE_WAVE, 3) void ffn_f32_kernel(GemmArgs 
     constexpr int MIV = decltype(miv_c)::value;
     for (int kt = 0; kt < KT; ++kt) {
       const int later = min(DIST - 1, KT - 1 - kt);
-      if (later >= 2) wait_vmcnt<2 * NLOAD>();
-      else if (later == 1) wait_vmcnt<NLOAD>();
+      if (later >= 1) wait_vmcnt<NLOAD>();
       else wait_vmcnt<0>();
       lds_barrier();
       if (kt + DIST < KT) issue(kt + DIST, (kt + DIST) % NSTAGE);
@@ -1183,32 +1232,189 @@ __global__ __launch_bounds__(F32_NW * MOE_WAVE, 3) void ffn_f32_kernel(GemmArgs 
               acc[m][mi] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[kk][m][u], xf[kk][mi][u], acc[m][mi], 0, 0, 0);
     }
   };
+  static_assert(MI == 2 && DIST <= 2, "cases below and waits above");
+  if (rows_valid <= 16) k_loop(std::integral_constant<int, 1>{});     // block-uniform
+  else k_loop(std::integral_constant<int, 2>{});
+  f32_store<GATED, MI>(acc, p, n0, m_first, m_end);
+}
+
+// Four values to four bf16 of each of the three planes (exact: 8 + 8 + 8 bits and the signs of the rests).
+// top: largest absolute value seen.
+__device__ __forceinline__ void f32_split(f32x4_t r, uint2 (&q)[3], float& top) {
+  top = fmaxf(fmaxf(top, fabsf(r[0])), fabsf(r[1]));
+  top = fmaxf(fmaxf(top, fabsf(r[2])), fabsf(r[3]));
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    q[i] = make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
+    if (i < 2) r = f32x4_t{r[0] - bf16lo(q[i].x), r[1] - bf16hi(q[i].x), r[2] - bf16lo(q[i].y), r[3] - bf16hi(q[i].y)};
+  }
+}
+// Chunk swizzle of a 64-byte plane row: 8 rows x the two chunks of an LDS pass cover each bank once.
+__device__ __forceinline__ int swz64(int row) { return (row >> 1) & 2; }
+
+// The pieces of a value below 2^-109 fall out of bf16's range, those of one above its largest finite value are
+// infinite and not a number, and so are their products with others.  A row (of either operand) whose largest
+// value is zero, or lies between these two, is beyond both: what such pieces lose is 2^-59 of the row's
+// products or less, and no sum overflows.
+constexpr float F32_ROW_MIN = 0x1p-50f, F32_ROW_MAX = 0x1p50f;
+__device__ __forceinline__ bool f32_row_ok(float top) { return top == 0.f || (top >= F32_ROW_MIN && top <= F32_ROW_MAX); }
+
+// Returns false, and stores nothing, if a row is outside the range above (block-uniform).
+template <bool GATED>
+__device__ __forceinline__ bool f32_split_tile(const GemmArgs& p, const TileCoord& tc, unsigned char* lds) {
+  constexpr int NMAT = GATED ? 2 : 1, BM = F32_BM;
+  constexpr int NLA = BM / 32, MI = BM / 16;
+  constexpr int STAGE = 3 * F32_PLANE;
+  const int lane = lane_id(), tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MOE_WAVE);
+  const int K = p.K, N = p.N, KT = (K + F32_BK - 1) / F32_BK;
+  const int n0 = tc.n0;
+  const int rows_valid = min(tc.m_end - tc.m_begin, BM);
+  const F32Operands rs = f32_operands<GATED>(p, tc, tc.m_begin);
+  // activations: thread (row tid / 8 + 32 i, chunk tid % 8 of 16 bytes); weights: lane (row lane % 16 of the wave's,
+  // chunks lane / 16 and lane / 16 + 4, the k-values of its MFMA fragment).  Rows past the end re-read the
+  // last valid one; chunks past K, and stages past the last, come out as zeros.
+  const int l16 = lane & 15, kg = lane >> 4, chunk = tid & 7;
+  uint32_t soff_a[NLA], soff_w[2];
+#pragma unroll
+  for (int i = 0; i < NLA; ++i) {
+    int r = min(i * 32 + (tid >> 3), rows_valid - 1);
+    if (p.src_assign) r = a_row_of(p, tc.m_begin + r);
+    soff_a[i] = static_cast<uint32_t>(r) * static_cast<uint32_t>(K) * 4u + static_cast<uint32_t>(chunk) * 16u;
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    soff_w[h] = static_cast<uint32_t>(min(wave * 16 + l16, N - 1 - n0)) * static_cast<uint32_t>(K) * 4u +
+                static_cast<uint32_t>(kg + 4 * h) * 16u;
+  const int tail_chunks = (K & (F32_BK - 1)) >> 2;
+  auto past_end = [&](int kt, int c) { return kt >= KT || (tail_chunks != 0 && c >= tail_chunks) ? PAST_END : 0u; };
+  float top_a[NLA] = {}, top_w[NMAT] = {};
+  f32x4_t va[NLA], vw[NMAT][2];
+  auto load_a = [&](int kt) {
+    if (kt >= KT - 1) {                           // uniform
+#pragma unroll
+      for (int i = 0; i < NLA; ++i) soff_a[i] |= past_end(kt, chunk);
+    }
+#pragma unroll
+    for (int i = 0; i < NLA; ++i)
+      va[i] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs.a, static_cast<int>(soff_a[i]), kt * ROWB, 0));
+  };
+  auto load_w = [&](int kt) {
+    if (kt >= KT - 1) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) soff_w[h] |= past_end(kt, kg + 4 * h);
+    }
+#pragma unroll
+    for (int m = 0; m < NMAT; ++m)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        vw[m][h] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(m ? rs.b1 : rs.b0, static_cast<int>(soff_w[h]), kt * ROWB, 0));
+  };
+  // plane row: four 16-byte chunks, chunk j = the row's 4-value chunks j and j + 4
+  const int wr = (tid >> 3) * F32_PROW + (((chunk & 3) ^ swz64(tid >> 3)) << 4) + (chunk >> 2) * 8;
+  auto split_a = [&](int buf) {
+    unsigned char* to = lds + buf * STAGE + wr;
+#pragma unroll
+    for (int i = 0; i < NLA; ++i) {
+      uint2 q[3];
+      f32_split(va[i], q, top_a[i]);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) *reinterpret_cast<uint2*>(to + i * 32 * F32_PROW + j * F32_PLANE) = q[j];
+    }
+  };
+  bf16x8_t wf[NMAT][3];
+  auto split_w = [&]() {
+#pragma unroll
+    for (int m = 0; m < NMAT; ++m) {
+      uint2 q0[3], q1[3];
+      f32_split(vw[m][0], q0, top_w[m]);
+      f32_split(vw[m][1], q1, top_w[m]);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) wf[m][j] = __builtin_bit_cast(bf16x8_t, make_uint4(q0[j].x, q0[j].y, q1[j].x, q1[j].y));
+    }
+  };
+  const int x_base = l16 * F32_PROW + ((kg ^ swz64(l16)) << 4);
+  f32x4_t acc[NMAT][MI];
+#pragma unroll
+  for (int m = 0; m < NMAT; ++m)
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) acc[m][mi] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  load_a(0);
+  load_w(0);
+  split_a(0);
+  load_a(1);
+  lds_barrier();
+  auto k_loop = [&](auto miv_c) {
+    constexpr int MIV = decltype(miv_c)::value;
+    int buf = 0;
+    for (int kt = 0; kt < KT; ++kt, buf ^= 1) {
+      const unsigned char* s = lds + buf * STAGE + x_base;
+      bf16x8_t x[2][3];
+      auto read_x = [&](int mi) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) x[mi & 1][j] = *reinterpret_cast<const bf16x8_t*>(s + j * F32_PLANE + mi * 16 * F32_PROW);
+      };
+      read_x(0);
+      split_w();
+      load_w(kt + 1);
+#pragma unroll
+      for (int mi = 0; mi < MIV; ++mi) {
+        if (mi + 1 < MIV) read_x(mi + 1);
+        constexpr int WQ[6] = {2, 0, 1, 1, 0, 0}, XQ[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+        for (int t = 0; t < 6; ++t)
+#pragma unroll
+          for (int m = 0; m < NMAT; ++m)
+            acc[m][mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[m][WQ[t]], x[mi & 1][XQ[t]], acc[m][mi], 0, 0, 0);
+        if (mi == 0) {
+          split_a(buf ^ 1);                       // (last read before the barrier of stage kt - 1)
+          load_a(kt + 2);
+        }
+        asm volatile("" ::: "memory");            // one sub-tile's fragments ahead, not all of them
+      }
+      lds_barrier();
+    }
+  };
   switch ((rows_valid + 15) >> 4) {               // block-uniform
     case 1: k_loop(std::integral_constant<int, 1>{}); break;
     case 2: k_loop(std::integral_constant<int, 2>{}); break;
-    case 3: if constexpr (MI >= 3) k_loop(std::integral_constant<int, 3>{}); break;
-    default: if constexpr (MI >= 4) k_loop(std::integral_constant<int, 4>{}); break;
+    case 3: k_loop(std::integral_constant<int, 3>{}); break;
+    default: k_loop(std::integral_constant<int, 4>{}); break;
   }
-  // accumulator (v, lane) is row lane % 16 of the sub-tile, columns 4 (lane / 16) .. + 3 of the wave's 16
-  float* out = static_cast<float*>(p.out);
-  const int c = n0 + wave * 16 + 4 * (lane >> 4);
-  const int32_t* out_map = GATED ? nullptr : p.out_map;
+  bool ok = true;
 #pragma unroll
-  for (int mi = 0; mi < MI; ++mi) {
-    int gr = tc.m_begin + mi * 16 + l16;
-    if (gr >= tc.m_end || c >= N) continue;       // (N is a multiple of 4)
-    float scale = 1.f;
-    if (out_map) {
-      gr = min(max(out_map[gr], 0), p.out_rows - 1);
-      scale = p.out_scale[gr];
-    }
-    f32x4_t o;
+  for (int i = 0; i < NLA; ++i) {                 // the eight lanes of a row
+    float t = top_a[i];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const float v = acc[0][mi][u];
-      o[u] = GATED ? silu_mul<true>(v, acc[NMAT - 1][mi][u]) : out_map ? v * scale : v;
+    for (int off = 1; off < 8; off <<= 1) t = fmaxf(t, __shfl_xor(t, off));
+    ok = ok && f32_row_ok(t);
+  }
+#pragma unroll
+  for (int m = 0; m < NMAT; ++m) {                // the four lanes of a weight row
+    float t = fmaxf(top_w[m], __shfl_xor(top_w[m], 16));
+    t = fmaxf(t, __shfl_xor(t, 32));
+    ok = ok && f32_row_ok(t);
+  }
+  if (!__syncthreads_and(ok)) return false;
+  f32_store<GATED, MI>(acc, p, n0, tc.m_begin, tc.m_end);
+  return true;
+}
+
+// SPLIT: a launch of 64-row tiles, which takes the split path where a tile has more than 32 rows.
+template <bool GATED, bool SPLIT>
+__global__ __launch_bounds__(F32_NW * MOE_WAVE, 3) void ffn_f32_kernel(GemmArgs p) {
+  extern __shared__ __align__(1024) unsigned char lds[];
+  TileCoord tc;
+  if (!decode_tile(p, tc)) return;
+  if constexpr (!SPLIT) {
+    f32_exact_rows<GATED>(p, tc, lds, tc.m_begin, tc.m_end);
+  } else {
+    if (tc.m_end - tc.m_begin > F32_EXACT_ROWS && f32_split_tile<GATED>(p, tc, lds)) return;
+    for (int m = tc.m_begin; m < tc.m_end; m += F32_EXACT_ROWS) {
+      lds_barrier();                              // (the rows before, or the split path, have left the LDS)
+      f32_exact_rows<GATED>(p, tc, lds, m, min(m + F32_EXACT_ROWS, tc.m_end));
     }
-    *reinterpret_cast<f32x4_t*>(out + static_cast<int64_t>(gr) * N + c) = o;
   }
 }
 
@@ -1389,21 +1595,24 @@ static int launch_bf16(GemmArgs a, int64_t A, bool row_split, hipStream_t st) {
                              ffn_bf16_kernel<GATED, false, WNT, false>, once[0], nullptr, once_sum, st);
 }
 
-// 32-row tiles while 64-row tiles would be fewer than 16 per CU (measured, both GEMMs, d = 1024, E = 16,
-// F = 2048, 32- against 64-row tiles: 1000 tokens 280 / 295 us, 2000 tokens 468 / 490; 8000 tokens,
-// 31 and 62 tiles per CU, 1607 / 1587, as every weight row is then staged twice as often).
+// 64-row tiles, which take the split path, from F32_SPLIT_ROWS rows per expert on, if there is one for every CU;
+// 32-row tiles below.  (Measured, both GEMMs of d = 1024, E = 16, k = 2, F = 2048 and of d = 1280, E = 24, k = 3,
+// F = 1200, 32-row against 64-row tiles, us: 28 rows per expert 122 / 132 and 137 / 134, 36 rows 137 / 144 and 164 / 142, 44 rows
+// 132 / 123 and 165 / 145, 100 rows 231 / 196 and 267 / 237.  Fewer tiles than CUs: a tile's stages are a serial chain, longer
+// with the cutting: 5 experts of 100 rows, d = F = 300, 29 / 37 us; 8 experts of 52 rows, d = 500, F = 900, 41 / 53.)
+constexpr int F32_SPLIT_ROWS = 40;
 template <bool GATED>
 static int launch_f32(GemmArgs a, int64_t A, hipStream_t st) {
   static LdsOnce once[2], once_sum;
   if (!tile_fits(a, F32_BN, 4)) return launch_wide<float, GATED>(a, A, st);
   a.bn = F32_BN;
   a.n_tiles = (a.N + F32_BN - 1) / F32_BN;
-  const int64_t tiles64 = (A + 63) / 64 * a.n_tiles;
-  if (tiles64 < 16 * static_cast<int64_t>(a.n_cu > 0 ? a.n_cu : 256))
-    return launch_grouped_gemm(a, 32, A, F32_NW * MOE_WAVE, ffn_f32_lds_bytes(GATED, 32),
-                               ffn_f32_kernel<GATED, 32>, once[0], nullptr, once_sum, st);
-  return launch_grouped_gemm(a, 64, A, F32_NW * MOE_WAVE, ffn_f32_lds_bytes(GATED, 64),
-                             ffn_f32_kernel<GATED, 64>, once[1], nullptr, once_sum, st);
+  const int64_t tiles = (A + F32_BM - 1) / F32_BM * a.n_tiles;
+  if (A / a.E >= F32_SPLIT_ROWS && tiles >= (a.n_cu > 0 ? a.n_cu : 256))
+    return launch_grouped_gemm(a, F32_BM, A, F32_NW * MOE_WAVE, ffn_f32_lds_bytes(GATED),
+                               ffn_f32_kernel<GATED, true>, once[0], nullptr, once_sum, st);
+  return launch_grouped_gemm(a, F32_EXACT_ROWS, A, F32_NW * MOE_WAVE, ffn_f32_lds_bytes(GATED),
+                             ffn_f32_kernel<GATED, false>, once[1], nullptr, once_sum, st);
 }
 
 // Mean rows per expert below which the kernels are built with the per-tile choice of the

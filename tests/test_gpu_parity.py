@@ -638,6 +638,69 @@ def test_grouped_ffn_fp32_64_row_tiles():
     assert np.isfinite(h).all() and np.isfinite(yp).all()
 
 
+@pytest.mark.parametrize("d,F", [(1604, 2076), (1632, 2084), (2080, 1668)])
+def test_grouped_ffn_fp32_split_tiles(d, F):
+    # 64-row tiles in three bf16 pieces per value (40 rows per expert and a tile for every CU), both GEMMs: tiles of
+    # 33, 48 and 64 rows and below (which take the fp32 instruction), K tails of 1, 4 and 7 chunks, whole
+    # stages, N tails.  Bound: K products summed in fp32 one after the other (see below); a wrong or missing
+    # piece product is off by 2^-9 or 2^-17 of the scale.
+    rows = (33, 64, 65, 0, 129, 200, 48, 40)
+    cfg = si.small_config(T=sum(rows), d=d, E=len(rows), k=1, F=F, dtype=si.F32, seed=d)
+    L = si.make_layer(cfg)
+    idx = np.repeat(np.arange(len(rows), dtype=np.int32), rows)[:, None]
+    _, offsets = orc.expert_load(idx, cfg.E)          # (token order is already the permuted order)
+    h, yp = gpu_ffn(cfg, L["x"], offsets, L["w1"], L["w3"], L["w2"])
+    ry, rh = orc.grouped_ffn(L["x"], offsets, L["w1"], L["w3"], L["w2"], return_h=True)
+    assert rel_err(h, rh) <= 4.0 * d ** 0.5 * 2.0 ** -24 + 2.0 ** -22
+    # (the reference's second product takes its own h: one more such error)
+    assert rel_err(yp, ry) <= 4.0 * (d ** 0.5 + F ** 0.5) * 2.0 ** -24 + 2.0 ** -22
+
+
+@pytest.mark.parametrize("what", ["plain", "tiny", "huge", "inf", "nan", "zero", "weight"])
+def test_grouped_ffn_fp32_split_tiles_with_values_out_of_range(what):
+    # one row of an operand beyond what bf16 pieces represent: its tile takes the fp32 instruction, bit for bit
+    # what 32-row launches give; a row of zeros or with a NaN stays on the split path
+    d, F, rows = 36, 64 * 256 + 4, 64
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((rows, d), device="cuda", generator=gen)
+    w1, w3, w2 = (torch.randn(s, device="cuda", generator=gen) for s in ((1, F, d), (1, F, d), (1, d, F)))
+
+    def run(x):
+        T = x.shape[0]
+        off = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+        h, y = torch.zeros((T, F), device="cuda"), torch.zeros((T, d), device="cuda")
+        B.moe_grouped_ffn_part(B.make_shape(T, d, 1, 1, F, si.F32, 1), x, off, w1, w3, w2, h, y, 1)
+        torch.cuda.synchronize()
+        return h
+
+    ref = run(x)
+    if what == "weight":
+        w3[0, 130] *= 2.0 ** 70                       # third tile of 64 columns
+    else:
+        x[40] *= {"tiny": 2.0 ** -70, "huge": 2.0 ** 70, "zero": 0.0}.get(what, 1.0)
+        if what in ("inf", "nan"):
+            x[40, 5] = float(what)
+    got = run(x)
+    exact = torch.cat([run(x[:32].clone()), run(x[32:].clone())])
+    same = lambda a, b: torch.equal(a.view(torch.int32), b.view(torch.int32))
+    if what in ("tiny", "huge", "inf"):
+        assert same(got, exact)
+    elif what == "weight":
+        assert same(got[:, 128:192], exact[:, 128:192])
+        assert same(got[:, :128], ref[:, :128]) and same(got[:, 192:], ref[:, 192:])
+    else:
+        keep = [i for i in range(rows) if i != 40]
+        assert same(got[keep], ref[keep]) and not same(got[keep], exact[keep])
+        if what == "nan":
+            assert bool(torch.isnan(got[40]).all())
+        if what == "zero":
+            assert bool((got[40] == 0).all())
+    fine = torch.isfinite(exact)
+    assert bool((torch.isfinite(got) == fine).all())
+    scale = exact.where(fine, torch.zeros_like(exact)).abs().amax(dim=1, keepdim=True)
+    assert bool(((got - exact).where(fine, torch.zeros_like(exact)).abs() <= 8.0 * d ** 0.5 * 2.0 ** -24 * scale).all())
+
+
 @pytest.mark.parametrize("dtype,T,d,F,form", [
     (si.F32, 64, 4, 2 ** 23 + 4, "perm"), (si.F32, 64, 4, 2 ** 23 + 4, "k1"),   # 64 activation rows of the down-projection
     (si.F32, 2, 2 ** 23 + 4, 64, "perm"),                                       # 64 weight rows of the up-projection
