@@ -7,8 +7,8 @@
 // cap.  The steps depend on each other, E is at most 256 and the data fits in registers, so ONE
 // wave runs the whole loop: a lane owns experts lane, lane+64, ...; the straggler comes from a
 // wave-wide arg-max (the paper's text uses a max-heap on the host; 64 lanes comparing at once
-// replace it).  Bound by the chain of dependent instructions of a step; see scale_kernel for how
-// it is kept short.  Per-replica loads W_e / R_e are compared as fp64 quotients, which is exact: two
+// replace it).  Bound by the chain of dependent instructions; scale_kernel takes the steps that no other can
+// come between in one round of its loop.  Per-replica loads W_e / R_e are compared as fp64 quotients, which is exact: two
 // different quotients with W < 2^31 and R <= 65537 < 2^17 differ by at least one part in
 // W_a R_b < 2^48, more than a rounding (2^-53) can close, and equal ones round to the same
 // number; equal loads go to the lowest expert index.  No host synchronisation: loads in,
@@ -45,33 +45,64 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
                           __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-  return v;
+// Sum over the wave by DPP (prefix sums inside the rows of 16 lanes, two row broadcasts), read from lane 63.
+__device__ __forceinline__ double wave_sum_dpp(double v) {
+  auto step = [](double x, auto ctrl, auto rows) {
+    return x + __hiloint2double(
+        __builtin_amdgcn_update_dpp(0, __double2hiint(x), decltype(ctrl)::value, decltype(rows)::value, 0xF, false),
+        __builtin_amdgcn_update_dpp(0, __double2loint(x), decltype(ctrl)::value, decltype(rows)::value, 0xF, false));
+  };
+  using std::integral_constant;
+  v = step(v, integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});
+  v = step(v, integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});
+  v = step(v, integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});
+  v = step(v, integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});
+  v = step(v, integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});
+  v = step(v, integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});
+  return readlane_f64(v, 63);
 }
 
-// Q: experts per lane (E <= 64 Q).  What a step costs is its dependent chain, so
-//   - the straggler is the largest fp64 quotient: a DPP maximum over the upper words of the (non-
-//     negative) doubles, a ballot on equality, and a second pass over the lower words only when
-//     more than one expert shares the upper one;
-//   - the quotient after a further split, W / (R + 1), is kept beside the current one; the division
-//     for the expert just split is issued at the head of the next step, beside that step's arg-max,
-//     which does not need it;
-//   - CV is not recomputed: with S2 = sum W^2 / R it exceeds V exactly if n S2 > (1 + V^2) (sum W)^2, and
-//     a split changes S2 by W/R * W/(R+1).  Where that test is closer than 1e-9 (the increments' error
-//     is below 1e-11: S2 is summed afresh every 256 steps, over which it shrinks at most 256-fold), the
-//     definition decides, as it does for the two values reported.
-// Measured: 64 experts, 64 further replicas 80 us with CV by its definition and an arg-max by 64-bit
-// cross products over lane shuffles in every step, now 20 us.
-constexpr int SC_REFRESH = 256;
-template <int Q>
+// The same in fp32.  ROWS = false: of lanes 0 .. 15 only.
+template <bool ROWS> __device__ __forceinline__ float wave_sum_f32(float v) {
+  auto step = [](float x, auto ctrl, auto rows) {
+    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, decltype(rows)::value,
+                                                          0xF, decltype(rows)::value == 0xF));
+  };
+  using std::integral_constant;
+  v = step(v, integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});
+  v = step(v, integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});
+  v = step(v, integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});
+  v = step(v, integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});
+  if constexpr (!ROWS) return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 15));
+  v = step(v, integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});
+  v = step(v, integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// Q: experts per lane (E <= 64 Q).  One dependent chain per round of the loop, so a round takes as many steps as
+// it can:
+//   - an expert whose quotient W / R is above every expert's quotient after a further split, W / (R + 1), is
+//     split before any expert is split twice: all such experts together are the next steps.  Their order matters only
+//     where the budget ends among them (the largest first) and where CV may fall to V among them;
+//   - CV is not recomputed: with S2 = sum W^2 / R it exceeds V exactly if n S2 > (1 + V^2) (sum W)^2.  S2 falls and n
+//     grows with every step, so if (n + 1) times the S2 after the round is above (fp32 tells to 1e-4), it is above
+//     after every step of it.  If that is not enough: a step lowers S2 by W/R * W/(R+1); with m the largest such
+//     drop of the round, S2 after j of its c steps is at least S2 - j m, and (n + j) (S2 - j m) is least at j = 1
+//     or j = c.  Otherwise the round is one step, the straggler, and the sum fp64; where the test is then closer
+//     than 1e-9, the definition of CV decides, as it does for the two values reported;
+//   - the quotients after one and after two further splits are kept, so the division for the experts just split is
+//     not needed in the next round.
+// Bound by the chain of a round (DPP maxima and a DPP sum; SMALL: up to 16 experts, four DPP steps each instead of
+// six).  Measured on Zipf loads, calls back to back, one step per round -> now, us: 64 experts and 64 further replicas (26
+// rounds) 19.8 -> 9.7, 128 and 256 (86 rounds) 91 -> 33, 256 and 1000 430 -> 143; 8 and 30 with V = 0, where half
+// the rounds are one step, 10.6 -> 12.8.
+template <int Q, bool SMALL = false>
 __global__ __launch_bounds__(MOE_WAVE) void scale_kernel(const int32_t* __restrict__ loads, int E,
                                                          int max_extra, double cv_threshold,
                                                          int32_t* __restrict__ replicas,
                                                          double* __restrict__ cv_out) {
   const int lane = lane_id();
-  double w[Q], key[Q], next[Q];                // W, W / R, W / (R + 1)
+  double w[Q], key[Q], next[Q], third[Q];      // W, W / R, W / (R + 1), W / (R + 2)
   int r[Q];
   long long s1 = 0;
 #pragma unroll
@@ -81,10 +112,11 @@ __global__ __launch_bounds__(MOE_WAVE) void scale_kernel(const int32_t* __restri
     s1 += load;
     w[q] = key[q] = static_cast<double>(load);
     next[q] = 0.5 * w[q];
+    third[q] = w[q] / 3.0;
     r[q] = 1;
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) s1 += __shfl_xor(s1, off);
+  // (exact: below 2^53)
+  s1 = static_cast<long long>(wave_sum_dpp(static_cast<double>(s1)));
   int n = E;                                   // replicas in the layer
   int extra = 0;
   // CV of the multiset {W_e / R_e, R_e times}: population std / mean
@@ -99,73 +131,100 @@ __global__ __launch_bounds__(MOE_WAVE) void scale_kernel(const int32_t* __restri
         part += static_cast<double>(r[q]) * dv * dv;
       }
     }
-    return readlane_f64(sqrt(wave_sum_f64(part) / static_cast<double>(n)) / mean, 0);
-  };
-  auto sum_w2_over_r = [&]() -> double {
-    double part = 0.0;
-#pragma unroll
-    for (int q = 0; q < Q; ++q) part += w[q] * key[q];
-    return readlane_f64(wave_sum_f64(part), 0);
+    return readlane_f64(sqrt(wave_sum_dpp(part) / static_cast<double>(n)) / mean, 0);
   };
   const double cv_first = cv_exact();
-  double s2 = sum_w2_over_r();
   const double limit = (1.0 + cv_threshold * cv_threshold) * static_cast<double>(s1) * static_cast<double>(s1);
   const double surely_over = limit * (1.0 + 1e-9), surely_under = limit * (1.0 - 1e-9);
+  const float over_f32 = static_cast<float>(limit) * 1.0001f;
   bool more = max_extra > 0 && cv_first > cv_threshold;
-  int last = -1, last_q = 0;                   // the expert split in the step before: lane and slot
-  double last_w = 0.0;
-  int last_r = 1;
   while (more) {                               // wave-uniform
-    const double pending = last_w / static_cast<double>(last_r + 1);
-    uint32_t m = 0;
+    uint32_t mk = 0, mn = 0;
 #pragma unroll
-    for (int q = 0; q < Q; ++q) m = max(m, hi32(key[q]));
-    const uint32_t top = wave_extreme<true>(m);
-#pragma unroll
-    for (int q = 0; q < Q; ++q)
-      if (lane == last && q == last_q) next[q] = pending;
-    if (top == 0u) break;                      // every load is zero: nothing to split
-    unsigned long long who[Q];
+    for (int q = 0; q < Q; ++q) mn = max(mn, hi32(next[q]));
+    const uint32_t top_next = wave_extreme<true, !SMALL>(mn);
+    // (upper words of the non-negative doubles: equal ones wait for a later round)
+    bool take[Q];
     int count = 0;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      who[q] = __ballot(hi32(key[q]) == top);
-      count += __popcll(who[q]);
+      take[q] = hi32(key[q]) > top_next;
+      count += __popcll(__ballot(take[q]));
     }
-    if (count > 1) {
+    if (count > max_extra - extra) {           // only the largest fit the budget
+      const int left = max_extra - extra;
+      int rank[Q] = {};
+#pragma unroll
+      for (int p = 0; p < Q; ++p)
+        for (unsigned long long m = __ballot(take[p]); m != 0ull; m &= m - 1) {
+          const int l = __ffsll(static_cast<long long>(m)) - 1;
+          const double k = readlane_f64(key[p], l);
+          const int e = l + MOE_WAVE * p;
+#pragma unroll
+          for (int q = 0; q < Q; ++q) rank[q] += k > key[q] || (k == key[q] && e < lane + MOE_WAVE * q) ? 1 : 0;
+        }
+#pragma unroll
+      for (int q = 0; q < Q; ++q) take[q] = take[q] && rank[q] < left;
+      count = left;
+    }
+    float part_f = 0.f;                        // S2 after the round
+#pragma unroll
+    for (int q = 0; q < Q; ++q) part_f += static_cast<float>(w[q]) * static_cast<float>(take[q] ? next[q] : key[q]);
+    const float s2f = wave_sum_f32<!SMALL>(part_f);
+    bool one = count == 0 || !(cv_threshold < 0.0 || static_cast<float>(n + 1) * s2f > over_f32);
+    if (one && count > 1) {
+      float drop = 0.f, all = 0.f;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const float d = take[q] ? static_cast<float>(key[q]) * static_cast<float>(next[q]) : 0.f;
+        drop = fmaxf(drop, d);
+        all += d;
+      }
+      const float before = s2f + wave_sum_f32<!SMALL>(all);
+      drop = __uint_as_float(wave_extreme<true, !SMALL>(__float_as_uint(drop)));   // (not negative: ordered as integers)
+      one = !(fminf(static_cast<float>(n + 1) * (before - drop),
+                    static_cast<float>(n + count) * (before - static_cast<float>(count) * drop)) > over_f32);
+    }
+    double s2 = 0.0;
+    if (one) {                                 // the straggler: largest quotient, lowest index
+#pragma unroll
+      for (int q = 0; q < Q; ++q) mk = max(mk, hi32(key[q]));
+      const uint32_t top = wave_extreme<true>(mk);
+      if (top == 0u) break;                    // every load is zero: nothing to split
       uint32_t ml = 0;
 #pragma unroll
       for (int q = 0; q < Q; ++q) ml = max(ml, hi32(key[q]) == top ? lo32(key[q]) : 0u);
       const uint32_t top_lo = wave_extreme<true>(ml);
+      bool found = false;
 #pragma unroll
-      for (int q = 0; q < Q; ++q) who[q] = __ballot(hi32(key[q]) == top && lo32(key[q]) == top_lo);
+      for (int q = 0; q < Q; ++q) {
+        const unsigned long long who = __ballot(hi32(key[q]) == top && lo32(key[q]) == top_lo);
+        take[q] = !found && who != 0ull && lane == __ffsll(static_cast<long long>(who)) - 1;
+        found = found || who != 0ull;
+      }
+      count = 1;
+      double part = 0.0;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) part += w[q] * (take[q] ? next[q] : key[q]);
+      s2 = wave_sum_dpp(part);
     }
-    int qs = Q - 1;                            // lowest index: lowest slot, then lowest lane
-#pragma unroll
-    for (int q = Q - 2; q >= 0; --q)
-      if (who[q] != 0ull) qs = q;
-    double drop = 0.0;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      if (q == qs) {                           // uniform
-        last = __ffsll(static_cast<long long>(who[q])) - 1;
-        last_q = q;
-        drop = readlane_f64(key[q] * next[q], last);
-        last_w = readlane_f64(w[q], last);
-        last_r = __builtin_amdgcn_readlane(r[q], last) + 1;
-        if (lane == last) {
-          key[q] = next[q];
-          r[q] += 1;
-        }
+      if (take[q]) {
+        key[q] = next[q];
+        next[q] = third[q];
+        r[q] += 1;
       }
+      third[q] = w[q] / static_cast<double>(r[q] + 2);
     }
-    n += 1;
-    extra += 1;
-    s2 -= drop;
-    if (extra % SC_REFRESH == 0) s2 = sum_w2_over_r();
-    const double lhs = static_cast<double>(n) * s2;
-    more = cv_threshold < 0.0 || lhs > surely_over;
-    if (!more && !(lhs < surely_under)) more = cv_exact() > cv_threshold;
+    n += count;
+    extra += count;
+    more = true;
+    if (one && cv_threshold >= 0.0) {
+      const double lhs = static_cast<double>(n) * s2;
+      more = lhs > surely_over;
+      if (!more && !(lhs < surely_under)) more = cv_exact() > cv_threshold;
+    }
     more = more && extra < max_extra;
   }
   const double cv = extra > 0 ? cv_exact() : cv_first;
@@ -180,17 +239,13 @@ __global__ __launch_bounds__(MOE_WAVE) void scale_kernel(const int32_t* __restri
   }
 }
 
-// Exclusive prefix sum over the block's 256 threads; *total = the sum.  part: LDS, four entries (a
-// caller that uses it twice passes two arrays).
-__device__ __forceinline__ long long block_prefix(long long v, long long* part, long long* total) {
-  const int lane = lane_id(), wave = threadIdx.x / MOE_WAVE;
-  long long incl = v;
-#pragma unroll
-  for (int off = 1; off < MOE_WAVE; off <<= 1) {
-    const long long up = __shfl_up(incl, off);
-    if (lane >= off) incl += up;
-  }
-  if (lane == MOE_WAVE - 1) part[wave] = incl;
+// Exclusive prefix sum over the block's 256 threads of values below 2^31; *total = the sum.  By DPP on the
+// halves of the values, whose sums over a wave fit 32 bits.  part: LDS, four entries (a caller that uses it twice
+// passes two arrays).
+__device__ __forceinline__ long long block_prefix(int v, long long* part, long long* total) {
+  const int wave = threadIdx.x / MOE_WAVE;
+  const long long incl = wave_scan_add(v & 0xFFFF) + (static_cast<long long>(wave_scan_add(v >> 16)) << 16);
+  if (lane_id() == MOE_WAVE - 1) part[wave] = incl;
   __syncthreads();
   long long before = 0, all = 0;
 #pragma unroll
@@ -255,7 +310,7 @@ extern "C" int moe_scale_replicas(int32_t E, const int32_t* loads, int64_t exper
   if (E > MOE_MAX_E) return MOE_ERR_UNSUPPORTED;
   const int64_t max_extra = mem_cap / expert_mem;
   if (max_extra > MOE_MAX_EXTRA_REPLICAS) return MOE_ERR_UNSUPPORTED;
-  const auto kernel = E <= 64 ? moe::scale_kernel<1> : E <= 128 ? moe::scale_kernel<2> : moe::scale_kernel<4>;
+  const auto kernel = E <= 16 ? moe::scale_kernel<1, true> : E <= 64 ? moe::scale_kernel<1> : E <= 128 ? moe::scale_kernel<2> : moe::scale_kernel<4>;
   hipLaunchKernelGGL(kernel, dim3(1), dim3(MOE_WAVE), 0, static_cast<hipStream_t>(hip_stream), loads, E,
                      static_cast<int>(max_extra), cv_threshold, replicas, cv_out);
   return moe::launch_status();
@@ -277,27 +332,45 @@ extern "C" int moe_replica_segments(int32_t E, const int32_t* offsets, const int
 // ---------------------------------------------------------------------------------------------
 // Expert Placement (Algorithm 2, Section 4.3): replicas from the most to the least loaded; a
 // replica that is still alive where the previous round put it stays there, any other joins the
-// GPU with the smallest aggregated load.  GPU loads are fp64 sums in placement order, and every step
-// needs the loads that the step before left: ONE wave runs the steps, lane g holding GPU g's load,
-// count and slots, "shortest queue" an arg-min over the lanes with a free slot (upper words of the
-// non-negative doubles by DPP, a ballot, lower words only on a tie).  Everything a step needs that does
-// not depend on the loads is prepared by the whole block, PL_CHUNK steps at a time, in LDS: the
-// order of the experts (all replicas of an expert carry W_e / R_e, so they are placed one after the
-// other; ranks by counting, quotients compared exactly as in scale_kernel), and per step the load,
-// the warm GPU and the place of the result.  A step is then one LDS read, requested a step ahead,
-// and the arg-min.  Measured: 128 replicas of 64 experts on 8 GPUs 110 us with a 64-lane shuffle
-// arg-max per expert, one arg-min over 64 lanes of doubles and (warm rounds) one trip to memory per
-// step, now 19 us.
+// GPU with the smallest aggregated load.  GPU loads are fp64 sums in placement order, and a step
+// needs the loads that the steps before left: ONE wave runs the steps, lane g holding GPU g's load,
+// count and slots.  Everything a step needs that does not depend on the loads is prepared by the whole
+// block, PL_CHUNK steps at a time, in LDS: the order of the experts (all replicas of an expert carry
+// W_e / R_e, so they are placed one after the other; ranks by counting, quotients compared exactly
+// as in scale_kernel), and per step the load, the warm GPU and the place of the result.  Bound by
+// the chain of dependent instructions from step to step:
+//   - a run of warm steps is one fp64 addition each, in the lane of its GPU;
+//   - a run of four and more others, on up to 16 GPUs: the lanes hold the GPUs in ascending order of
+//     (load, index).  The first one takes the replica, and every lane finds by itself whether it keeps
+//     its GPU, takes its right neighbour's or the one that moved up: DPP moves and two comparisons, no trip
+//     through scalar registers;
+//   - shorter runs, more GPUs, and 64 steps in which a GPU may run out of slots: the shortest queue is an arg-min
+//     over the lanes with a free slot (upper words of the non-negative doubles by DPP, a ballot, lower words
+//     only on a tie).
+// Measured, calls back to back, every step by arg-min or warm look-up -> now, us: 64 experts, 128 replicas, 8 GPUs, all warm
+// 18.8 -> 6.8, all new 33 -> 25; 256 experts, 1256 replicas, 8 GPUs 143 -> 42 and 295 -> 221; 40 GPUs, 128
+// replicas, all new 41 -> 31; slots that run out 33 -> 34.
 // ---------------------------------------------------------------------------------------------
 namespace moe {
 
 constexpr int PL_MAX_GPUS = MOE_WAVE;
 constexpr int PL_CHUNK = 1024;
+constexpr int PL_SORT_RUN = 4;
 struct PlaceStep {
   double w;        // load of the replica
   int warm;        // GPU of the previous round, -1 = none
   int out;         // index of the replica in gpu_of
 };
+
+// DPP moves of a double; `hi` and `lo` where a lane has no source.
+template <int CTRL> __device__ __forceinline__ double dpp_f64(double x, int hi, int lo) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, __double2hiint(x), CTRL, 0xF, 0xF, false),
+                          __builtin_amdgcn_update_dpp(lo, __double2loint(x), CTRL, 0xF, 0xF, false));
+}
+__device__ __forceinline__ double push_f64(double x, int to_lane) {
+  return __hiloint2double(__builtin_amdgcn_ds_permute(to_lane * 4, __double2hiint(x)),
+                          __builtin_amdgcn_ds_permute(to_lane * 4, __double2loint(x)));
+}
 
 // WIDE: more than 16 GPUs.
 template <bool WIDE>
@@ -308,8 +381,9 @@ __global__ __launch_bounds__(256) void place_kernel(
     int32_t* __restrict__ gpu_of, double* __restrict__ gpu_load, int32_t* __restrict__ gpu_count,
     int32_t* __restrict__ n_warm) {
   __shared__ __align__(16) PlaceStep step[PL_CHUNK + 1];   // (one more: the read ahead of the last step)
+  __shared__ unsigned long long cold[PL_CHUNK / MOE_WAVE];    // steps without a warm GPU
   __shared__ double key[MOE_MAX_E];
-  __shared__ int seg_start[MOE_MAX_E], prev_n[MOE_MAX_E], rep[MOE_MAX_E];
+  __shared__ int seg_start[MOE_MAX_E], prev_n[MOE_MAX_E], rep[MOE_MAX_E], rank[MOE_MAX_E];
   __shared__ long long prev_start[MOE_MAX_E];    // (the previous round's counts are the caller's: their sum may pass 2^31)
   __shared__ int order[MOE_MAX_E], order_start[MOE_MAX_E + 1];
   __shared__ long long part[3][4];
@@ -317,20 +391,28 @@ __global__ __launch_bounds__(256) void place_kernel(
   // thread e: expert e
   const int my_r = tid < E ? min(max(replicas[tid], 1), MOE_MAX_EXTRA_REPLICAS + 1) : 0;
   const int my_p = tid < E && prev_replicas ? max(prev_replicas[tid], 0) : 0;
-  const double my_key = tid < E ? static_cast<double>(max(loads[tid], 0)) / static_cast<double>(my_r) : -1.0;
+  key[tid] = tid < E ? static_cast<double>(max(loads[tid], 0)) / static_cast<double>(my_r) : -1.0;
   long long total, dummy;
   seg_start[tid] = static_cast<int>(block_prefix(my_r, part[0], &total));    // (at most 256 * 65537)
   prev_start[tid] = block_prefix(my_p, part[1], &dummy);
   prev_n[tid] = my_p;
   rep[tid] = my_r;
-  key[tid] = my_key;
+  rank[tid] = 0;
   __syncthreads();
-  if (tid < E) {
-    int rank = 0;                              // experts before this one: more loaded, or equal and lower
+  {
+    // rank: experts before this one, more loaded, or equal and lower.  `parts` threads per expert take a share
+    // of the others each.
+    const int per = E <= 64 ? 64 : E <= 128 ? 128 : 256, parts = 256 / per;
+    const int e = tid & (per - 1), share = (E + parts - 1) / parts;
+    const int first = tid / per * share, last = min(first + share, E);
+    const double mine = key[e];
+    int before = 0;
 #pragma unroll 8
-    for (int e = 0; e < E; ++e) rank += (key[e] > my_key || (key[e] == my_key && e < tid)) ? 1 : 0;
-    order[rank] = tid;
+    for (int o = first; o < last; ++o) before += (key[o] > mine || (key[o] == mine && o < e)) ? 1 : 0;
+    if (e < E && before) atomicAdd(&rank[e], before);
   }
+  __syncthreads();
+  if (tid < E) order[rank[tid]] = tid;
   __syncthreads();
   const int my_o = tid < E ? order[tid] : 0;
   order_start[tid] = static_cast<int>(block_prefix(tid < E ? rep[my_o] : 0, part[2], &dummy));
@@ -342,54 +424,130 @@ __global__ __launch_bounds__(256) void place_kernel(
   int gcount = 0;
   const int gslots = (lane < G) ? (gpu_slots ? max(gpu_slots[lane], 0) : 0x7FFFFFFF) : 0;
   int warm = 0;
+  // the GPU with the smallest load among those of `room` (lowest index on a tie), -1 if there is none
+  auto shortest = [&](unsigned long long room) -> int {
+    const bool free_slot = (room >> lane) & 1ull;
+    const uint32_t h = free_slot ? hi32(gload) : 0xFFFFFFFFu;
+    const uint32_t least = wave_extreme<false, WIDE>(h);
+    if (least == 0xFFFFFFFFu) return -1;
+    unsigned long long who = __ballot(h == least);
+    if (__popcll(who) > 1) {
+      const uint32_t l = h == least ? lo32(gload) : 0xFFFFFFFFu;
+      const uint32_t least_lo = wave_extreme<false, WIDE>(l);
+      who = __ballot(h == least && l == least_lo);
+    }
+    return __ffsll(static_cast<long long>(who)) - 1;
+  };
+  auto put = [&](double load, int g) {
+    gload += lane == g ? load : 0.0;           // (loads are not negative: the other lanes keep their bits)
+    gcount += lane == g ? 1 : 0;
+  };
   for (int first = 0; first < steps; first += PL_CHUNK) {
     const int n = min(PL_CHUNK, steps - first);
-    for (int i = tid; i < n; i += 256) {
-      const int s = first + i;
-      int lo = 0, hi = E - 1;                  // last rank whose first step is <= s
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (order_start[mid] <= s) lo = mid; else hi = mid - 1;
-      }
-      const int e = order[lo], q = s - order_start[lo];
+    for (int base = 0; base < n; base += 256) {
+      const int i = base + tid;
       int g = -1;
-      if (q < prev_n[e]) g = prev_gpu[prev_start[e] + q];
-      step[i].w = key[e];
-      step[i].warm = g >= 0 && g < G ? g : -1;
-      step[i].out = seg_start[e] + q;
+      if (i < n) {
+        const int s = first + i;
+        int lo = 0, hi = E - 1;                // last rank whose first step is <= s
+        while (lo < hi) {
+          const int mid = (lo + hi + 1) >> 1;
+          if (order_start[mid] <= s) lo = mid; else hi = mid - 1;
+        }
+        const int e = order[lo], q = s - order_start[lo];
+        if (q < prev_n[e]) g = prev_gpu[prev_start[e] + q];
+        if (g < 0 || g >= G) g = -1;
+        step[i].w = key[e];
+        step[i].warm = g;
+        step[i].out = seg_start[e] + q;
+      }
+      const unsigned long long c = __ballot(i < n && g < 0);
+      if (lane == 0) cold[i / MOE_WAVE] = c;
     }
     __syncthreads();
     if (tid < MOE_WAVE) {
-      unsigned long long room = __ballot(gcount < gslots);
-      PlaceStep cur = step[0];
-      for (int i = 0; i < n; ++i) {
-        const PlaceStep ahead = step[i + 1];   // (past the chunk's last step: read, not used)
-        const int wg = __builtin_amdgcn_readfirstlane(cur.warm);
-        int g = -1;
-        if (wg >= 0 && ((room >> wg) & 1ull)) {
-          g = wg;
-          ++warm;
-        } else {
-          const bool free_slot = (room >> lane) & 1ull;
-          const uint32_t h = free_slot ? hi32(gload) : 0xFFFFFFFFu;
-          const uint32_t least = wave_extreme<false, WIDE>(h);
-          if (least != 0xFFFFFFFFu) {
-            unsigned long long who = __ballot(h == least);
-            if (__popcll(who) > 1) {
-              const uint32_t l = h == least ? lo32(gload) : 0xFFFFFFFFu;
-              const uint32_t least_lo = wave_extreme<false, WIDE>(l);
-              who = __ballot(h == least && l == least_lo);
+      for (int base = 0; base < n; base += MOE_WAVE) {
+        const int cnt = min(MOE_WAVE, n - base);
+        PlaceStep* const st = step + base;
+        if (__ballot(lane < G && gcount > gslots - cnt) != 0ull) {   // a GPU may run out of slots
+          unsigned long long room = __ballot(gcount < gslots);
+          PlaceStep cur = st[0];
+          for (int i = 0; i < cnt; ++i) {
+            const PlaceStep next = st[i + 1];  // (past the block's last step: read, not used)
+            const int wg = __builtin_amdgcn_readfirstlane(cur.warm);
+            int g = wg;
+            if (wg >= 0 && ((room >> wg) & 1ull)) ++warm;
+            else g = shortest(room);
+            if (lane == g) {
+              gload += cur.w;
+              gcount += 1;
             }
-            g = __ffsll(static_cast<long long>(who)) - 1;
+            room = __ballot(gcount < gslots);
+            if (lane == 0) st[i].warm = g;     // the step's result, in place of its input
+            cur = next;
           }
+          continue;
         }
-        if (lane == g) {
-          gload += cur.w;
-          gcount += 1;
+        const unsigned long long all = ~0ull >> (MOE_WAVE - G);
+        const uint32_t c_lo = __builtin_amdgcn_readfirstlane(static_cast<int>(cold[base / MOE_WAVE]));
+        const uint32_t c_hi = __builtin_amdgcn_readfirstlane(static_cast<int>(cold[base / MOE_WAVE] >> 32));
+        const unsigned long long mask = static_cast<unsigned long long>(c_hi) << 32 | c_lo;
+        int i = 0;
+        while (i < cnt) {                      // wave-uniform
+          const unsigned long long ahead = mask >> i;
+          const int end = ahead == 0ull ? cnt : i + __ffsll(static_cast<long long>(ahead)) - 1;
+          warm += end - i;
+#pragma unroll 8
+          for (; i < end; ++i) put(st[i].w, st[i].warm);
+          if (i >= cnt) break;
+          const unsigned long long again = ~(mask >> i);        // (not zero: bit 63 - i and above, or i = 0 and all cold)
+          const int run = min(cnt - i, again == 0ull ? MOE_WAVE : __ffsll(static_cast<long long>(again)) - 1);
+          if (!WIDE && run >= PL_SORT_RUN) {
+            const double inf = __hiloint2double(0x7FF00000, 0);
+            double ld = lane < G ? gload : inf;
+            int to = lane < G ? 0 : lane;      // place in the order
+            for (int g = 0; g < G; ++g) {
+              const double l = readlane_f64(ld, g);
+              to += lane < G && (l < ld || (l == ld && g < lane)) ? 1 : 0;
+            }
+            ld = push_f64(ld, to);
+            int id = __builtin_amdgcn_ds_permute(to * 4, lane), ct = __builtin_amdgcn_ds_permute(to * 4, gcount);
+            int res = 0;
+#pragma unroll 4
+            for (int t = 0; t < run; ++t) {
+              const double v = dpp_f64<0x150>(ld, 0, 0) + st[i + t].w;                    // row_newbcast:0
+              const int vid = __builtin_amdgcn_update_dpp(0, id, 0x150, 0xF, 0xF, false);
+              const int vct = __builtin_amdgcn_update_dpp(0, ct, 0x150, 0xF, 0xF, false) + 1;
+              const double nl = dpp_f64<0x101>(ld, 0x7FF00000, 0);                        // row_shl:1
+              const int nid = __builtin_amdgcn_update_dpp(lane, id, 0x101, 0xF, 0xF, false);
+              const int nct = __builtin_amdgcn_update_dpp(0, ct, 0x101, 0xF, 0xF, false);
+              const bool next_before = nl < v || (nl == v && nid < vid);
+              const bool before = lane == 0 || ld < v || (ld == v && id < vid);
+              const int joined = __builtin_amdgcn_readfirstlane(id);      // (a broadcast stays in its row of 16 lanes)
+              res = lane == t ? joined : res;
+              ld = next_before ? nl : before ? v : ld;
+              id = next_before ? nid : before ? vid : id;
+              ct = next_before ? nct : before ? vct : ct;
+            }
+            if (lane < run) st[i + lane].warm = res;
+            gload = push_f64(ld, id);
+            gcount = __builtin_amdgcn_ds_permute(id * 4, ct);
+            if (lane >= G) gload = 0.0;
+          } else {
+            double load = st[i].w;
+            for (int t = 0; t < run; ++t) {
+              const double next = st[i + t + 1].w;
+              const int g = shortest(all);
+              if (lane == g) {
+                gload += load;
+                gcount += 1;
+              }
+              if (lane == 0) st[i + t].warm = g;
+              load = next;
+            }
+          }
+          i += run;
         }
-        room = __ballot(gcount < gslots);
-        if (lane == 0) step[i].warm = g;       // the step's result, in place of its input
-        cur = ahead;
       }
     }
     __syncthreads();

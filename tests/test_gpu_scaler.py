@@ -404,3 +404,37 @@ def test_place_replicas_after_a_round_of_more_than_2_31_replicas():
     torch.cuda.synchronize()
     assert np.array_equal(gpu_of.cpu().numpy(), want[0]) and np.array_equal(load.cpu().numpy(), want[1])
     assert np.array_equal(count.cpu().numpy(), want[2]) and int(n_warm.item()) == want[3]
+
+
+@pytest.mark.parametrize("E,total,alpha", [(5, 3000, 1.3), (64, 49152, 1.2), (70, 900, 0.6), (129, 5000, 0.9)])
+def test_scale_replicas_stops_at_every_step(E, total, alpha):
+    # the kernel takes several steps in one round of its loop: budgets and thresholds that end it at each of the first steps
+    loads = si.zipf_loads(E, total, alpha, E)
+    for cap in range(40):
+        check_scale(loads, 1, cap, 0.0)
+    _, trace = sc.expert_scaling(loads, 1, 40, 0.0)
+    seen = np.inf
+    for a, b in zip(trace[:-1], trace[1:]):
+        V = 0.5 * (a + b)
+        if V < seen and abs(a - b) > 1e-8:        # (CV may rise from step to step)
+            seen = V
+            check_scale(loads, 1, 64, V)
+
+
+@pytest.mark.parametrize("G", [1, 2, 15, 16, 17, 64])
+@pytest.mark.parametrize("new", [0.0, 0.1, 0.5, 0.97, 1.0])
+def test_place_replicas_in_runs_of_warm_and_new_ones(G, new):
+    # runs of warm steps, of new ones shorter and longer than four and across the kernel's 64-step blocks; many
+    # equal loads; without slots, with slots that run out near the end, and with few
+    rng = np.random.default_rng(int(100 * new) + G)
+    E = 90
+    loads = rng.integers(0, 6, size=E) * 12
+    replicas = rng.integers(1, 6, size=E)
+    steps = int(replicas.sum())
+    prev_gpu = np.where(rng.random(steps) < new, -1, rng.integers(0, G, size=steps))
+    for run in (3, 4, 5, 130):
+        at = int(rng.integers(0, steps - run))
+        prev_gpu[at:at + run] = -1 if rng.random() < 0.7 else 0
+    start = np.concatenate([[0], np.cumsum(replicas)])
+    for slots in (None, np.full(G, steps), np.full(G, steps // G + 1), np.full(G, 2)):
+        check_place(loads, replicas, G, start, prev_gpu, slots)
