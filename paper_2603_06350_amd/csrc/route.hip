@@ -210,15 +210,14 @@ __device__ int route_token(const float (&s)[QE], float bnd, bool check, int E, i
   return 0;
 }
 
-// Exact gate sum (fp64) of one (token row, expert row) pair per candidate slot, this wave's part
-// of the hidden dimension.  Lane = (candidate slot lane % RT_CMAX, one of four sub-slices); the
-// four sub-slice sums of a slot are added by two lane exchanges; the lanes of sub-slice 0 return
-// the slot's sum.
+// Exact gate sum (fp64) of one (token row, expert row) pair per slot, this wave's part of the hidden
+// dimension, for 2^slots_log2 pairs.  Lane = (slot, one of 64 / slots sub-slices); the sub-slice sums of a slot
+// are added by lane exchanges; every lane returns its slot's sum.
 template <bool BF16>
-__device__ __forceinline__ double exact_slot_sum(const uint4* __restrict__ xrow,
-                                                 const uint4* __restrict__ wrow, int row16, int wave) {
-  const int sub = lane_id() / RT_CMAX;
-  constexpr int NSUB = MOE_WAVE / RT_CMAX;
+__device__ __forceinline__ double exact_slot_sum(const uint4* __restrict__ xrow, const uint4* __restrict__ wrow,
+                                                 int row16, int wave, int slots_log2) {
+  const int NSUB = MOE_WAVE >> slots_log2;
+  const int sub = lane_id() >> slots_log2;
   const int cw = (row16 + RT_NW - 1) / RT_NW;
   const int c0 = wave * cw;
   const int c1 = min(row16, c0 + cw);
@@ -255,8 +254,7 @@ __device__ __forceinline__ double exact_slot_sum(const uint4* __restrict__ xrow,
       }
     }
   }
-  acc += __shfl_xor(acc, 16);
-  acc += __shfl_xor(acc, 32);
+  for (int off = 1 << slots_log2; off < MOE_WAVE; off <<= 1) acc += __shfl_xor(acc, off);
   return acc;
 }
 
@@ -268,7 +266,7 @@ __device__ void exact_candidates(const uint4* __restrict__ xrow, const uint4* __
   const int lane = lane_id();
   const int c = lane & (RT_CMAX - 1);
   const int e = cand[c < n ? c : 0];
-  const double acc = exact_slot_sum<BF16>(xrow, wg + static_cast<int64_t>(e) * row16, row16, wave);
+  const double acc = exact_slot_sum<BF16>(xrow, wg + static_cast<int64_t>(e) * row16, row16, wave, 4);
   if (lane < RT_CMAX && c < n) dpart[wave * RT_CMAX + c] = acc;
 }
 
@@ -564,8 +562,8 @@ __global__ __launch_bounds__(RT_THREADS) void route_kernel(
 // token, each lane a contiguous range of experts.  A lane finds its best remaining score by a
 // tournament over its registers, the lanes of a token merge by DPP butterflies, so one pick
 // costs a few dozen instructions for all the wave's tokens together.  Ambiguous tokens follow the
-// same protocol as above (exact re-scoring of the listed candidates by the whole block, four
-// tokens per pass), after which their lanes patch the scores they hold and select once more.
+// same protocol as above (exact re-scoring of the listed candidates by the whole block, up to sixteen
+// (token, candidate) pairs per pass), after which their lanes patch the scores they hold and select once more.
 constexpr int RT_KSEL = 16;      // largest k this path handles (the picks of a tile sit in LDS)
 
 __device__ __forceinline__ int rt_swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
@@ -771,17 +769,26 @@ __device__ void select_tile(const float (&s)[S], float bnd, bool check, bool com
 // Exact gate sums of up to RT_CMAX (token, candidate expert) pairs, a token of its own per slot.
 // pairs[] holds (row | position in the token's candidate list << 16).
 // Result: dpart[wave * RT_CMAX + pair].
+template <bool FEW>
 __device__ void exact_pairs(const uint4* __restrict__ x, const uint4* __restrict__ wg, int row16,
                             int64_t t0, const int* __restrict__ pairs, int npairs,
                             const int* __restrict__ cand_all, int wave, double* __restrict__ dpart) {
   const int lane = lane_id();
-  const int c = lane & (RT_CMAX - 1);
+  // FEW: the pass takes no more slots than there are pairs, as long as that saves a trip to memory (eight chunks
+  // per lane are requested together).  A block of 8 or 16 experts has two pairs as a rule.  (Measured: d = 4096, 4096
+  // tokens, E = 8 / 16 19.8 / 19.5 -> 18.6 / 18.3 us, d = 5120, E = 16 22.3 -> 19.6; at 64 and 128 experts, where
+  // there are more pairs, 2 to 4 % slower: the run-time slot count costs registers.)
+  int slots_log2 = 4;
+  if constexpr (FEW)
+    while (slots_log2 > 1 && npairs <= 1 << (slots_log2 - 1) && (row16 + RT_NW - 1) / RT_NW > 8 * (MOE_WAVE >> slots_log2)) --slots_log2;
+  const int slots = 1 << slots_log2;
+  const int c = lane & (slots - 1);
   const int entry = pairs[c < npairs ? c : 0];
   const int prow = entry & 0xFFFF, pos = entry >> 16;
   const int e = cand_all[prow * RT_CMAX + pos];
   const double acc = exact_slot_sum<true>(x + (t0 + prow) * row16, wg + static_cast<int64_t>(e) * row16,
-                                          row16, wave);
-  if (lane < RT_CMAX && c < npairs) dpart[wave * RT_CMAX + c] = acc;
+                                          row16, wave, slots_log2);
+  if (lane < slots && c < npairs) dpart[wave * RT_CMAX + c] = acc;
 }
 
 template <int NT, int TILES>
@@ -993,7 +1000,7 @@ __global__ __launch_bounds__(RT_THREADS, (RouteTileLds<NT, TILES>::TOTAL <= 80 *
   for (int base = 0; base < np; base += RT_CMAX) {
     // up to RT_CMAX (token, candidate) pairs share one pass over the hidden dimension
     const int cnt = min(RT_CMAX, np - base);
-    exact_pairs(x, wg, row16, t0, plist + base, cnt, cand_all, wave, dpart);
+    exact_pairs<NT == 1>(x, wg, row16, t0, plist + base, cnt, cand_all, wave, dpart);
     __syncthreads();
     for (int c = 0; c < cnt; ++c) {
       const int prow = plist[base + c] & 0xFFFF;
@@ -1171,20 +1178,13 @@ template <bool BF16, int NT>
 static int launch_route(const moe_shape_t* s, const void* x, const void* wg, const float* bias,
                         int32_t* idx, float* w, float* scores, float* scratch, float* norms,
                         hipStream_t st) {
-  // Tokens per block: a full 16-row tile when that still gives every CU a block (every wave then
-  // has its whole slice of the tile's rows, 16 KiB at d = 4096, requested at once); fewer (the other
-  // tile rows idle) for smaller batches, where latency, not MFMA use, is what counts.
-  // (Measured at T = 4096, d = 4096, E = 8 with x cold: 25.7 us with 8 tokens per block and
-  // batches of 8 steps, 21.8 us with full tiles and the slice in one batch.)
-  constexpr int GRID_TARGET = 256;
-  int tpb = RT_TM;
-  while (tpb > 1 && (s->T + tpb - 1) / tpb < GRID_TARGET) tpb >>= 1;
-  if (tpb == RT_TM)
-    return launch_route_rpw<BF16, NT, 2, false>(s, x, wg, bias, idx, w, nullptr, nullptr, scores, tpb, st);
+  constexpr int CUS = 256;
   if constexpr (BF16) {
-    // gate product spread over the chip first, if there is somewhere to put the scores and the
+    // Gate product spread over the chip first, if there is somewhere to put the scores and the
     // gate matrix is large enough (256 KB: 8 us through one CU) to pay for the second launch
-    if (scratch && norms && s->T <= RT_PRE_MAX_T && static_cast<int64_t>(s->E) * s->d * 2 >= 256 * 1024) {
+    int tpb = RT_TM;                   // (the selection alone needs few registers: 256 blocks or more, two to a CU)
+    while (tpb > 1 && (s->T + tpb - 1) / tpb < CUS) tpb >>= 1;
+    if (tpb < RT_TM && scratch && norms && s->T <= RT_PRE_MAX_T && static_cast<int64_t>(s->E) * s->d * 2 >= 256 * 1024) {
       const int t_tiles = (s->T + RT_TM - 1) / RT_TM;
       if (static_cast<int64_t>(t_tiles) * ((s->E + 63) / 64) >= 256)
         hipLaunchKernelGGL(gate_tile_kernel<4>, dim3(t_tiles, (s->E + 63) / 64), dim3(RT_THREADS), 0, st,
@@ -1198,6 +1198,19 @@ static int launch_route(const moe_shape_t* s, const void* x, const void* wg, con
       return launch_route_rpw<BF16, NT, 1, true>(s, x, wg, bias, idx, w, scratch, norms, scores, tpb, st);
     }
   }
+  // Tokens per block, the other rows of the 16-row tile idle.  bf16: the fewest that leave no more than one block
+  // per CU.  A block has a CU to itself (512 threads of more than 128 registers), so blocks past the 256th are a second
+  // round, which costs more than the shorter tail of every block saves; from 4097 tokens on the tile is full.  (Measured,
+  // the most tokens that still give 256 blocks -> this, us: d = 4096, E = 8, 257 tokens 13.4 -> 8.1, 500 13.8 -> 8.0, 1000
+  // 14.6 -> 8.5, 1500 15.7 -> 10.2; d = 5120, E = 16, 1000 tokens 25.6 -> 14.5, 3000 30.9 -> 26.3; d = 1048, E = 12,
+  // 1501 tokens 13.0 -> 11.1; the same at 512, 1024 and 2048.)
+  // fp32: one.  Every token takes the exact pass, in which the whole block works on one token after the other.
+  // (Measured against the rule that bf16 had: d = 1024, E = 16, 512 tokens 10.0 -> 8.3, 1024 18.3 -> 13.7, 6000 88 -> 68; d = 1280,
+  // E = 24, 1500 tokens 55 -> 38; up to 5 % slower at 1000 and 2000 tokens, where that rule's blocks just filled the chip.)
+  int tpb = 1;
+  while (BF16 && tpb < RT_TM && (s->T + tpb - 1) / tpb > CUS) tpb <<= 1;
+  if (tpb == RT_TM)
+    return launch_route_rpw<BF16, NT, 2, false>(s, x, wg, bias, idx, w, nullptr, nullptr, scores, tpb, st);
   return launch_route_rpw<BF16, NT, 1, false>(s, x, wg, bias, idx, w, nullptr, nullptr, scores, tpb, st);
 }
 

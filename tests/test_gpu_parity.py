@@ -251,6 +251,37 @@ def test_route_large_batch_ties_and_near_ties(T, E):
     assert np.all(idx[:, 0] == 3) and idx.max() < 20
 
 
+@pytest.mark.parametrize("T", [255, 257, 300, 512, 513, 1025, 2049, 4097])
+@pytest.mark.parametrize("dtype", [si.BF16, si.F32])
+def test_route_tokens_per_block(T, dtype):
+    # around the batch sizes at which a block of the per-tile kernel takes twice the tokens (fp32: always one)
+    cfg = si.small_config(T=T, d=136, E=12, k=3, F=64, dtype=dtype)
+    L = si.make_layer(cfg, parts=("x", "w_gate"))
+    check_route(cfg, L["x"], L["w_gate"], None)
+
+
+@pytest.mark.parametrize("d", [1024, 4096, 5120, 16384])
+def test_route_few_near_ties_per_block(d):
+    # 0 to 11 tokens of every 32-token block have two equal scores beside chosen ones up to a bias that only the
+    # exact pass sees: 0 to 22 (token, expert) pairs per block, in passes of 2, 4, 8 or 16 (wider rows, fewer)
+    cfg = si.small_config(T=3100, d=d, E=8, k=2, F=64)
+    L = si.make_layer(cfg, parts=("x", "w_gate"))
+    wg = L["w_gate"].copy()
+    wg[5] = wg[3]
+    w3 = si.bf16_bits_to_f32(wg[3]).astype(np.float64)
+    x = si.bf16_bits_to_f32(L["x"]).astype(np.float64)
+    x -= np.outer(x @ w3 / (w3 @ w3), w3)             # experts 3 and 5 score 0 ...
+    t = np.arange(cfg.T)
+    near = t % 32 < (t // 32) % 12
+    x += np.outer(np.where(near, 8.0, -8.0), w3 / np.sqrt(w3 @ w3))   # ... then far above or far below the others
+    x = si.f32_to_bf16_bits(x.astype(np.float32))
+    bias = np.zeros(cfg.E, dtype=np.float32)
+    bias[5] = 1e-6
+    idx, _ = check_route(cfg, x, wg, bias)
+    pair = np.isin(idx, (3, 5)).sum(axis=1)
+    assert (pair[near] == 2).mean() > 0.9 and pair[~near].max() == 0
+
+
 def test_route_large_batch_without_scores_output():
     cfg = si.small_config(T=8200, d=256, E=64, k=6, F=64)
     L = si.make_layer(cfg, parts=("x", "w_gate"))
