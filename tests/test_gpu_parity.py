@@ -458,6 +458,17 @@ def test_count_and_permute_on_both_sides_of_the_single_launch_limit(T, d, E, k):
     check_dispatch(cfg, L["x"], idx)
 
 
+@pytest.mark.parametrize("T", [2816, 6145, 20001])
+@pytest.mark.parametrize("E,k", [(1, 1), (3, 3), (7, 7), (17, 8), (64, 9), (128, 16), (129, 24), (256, 5)])
+def test_count_and_permute_two_launches_by_experts_and_choices(T, E, k):
+    # up to eight choices per token stay in registers, more are read again; tables of experts that divide a block's
+    # threads or not; blocks with one token, and partial counts of one batch of loads and several
+    cfg = si.small_config(T=max(T, 6145 // k + 1), d=16, E=E, k=k, F=64)
+    L = si.make_layer(cfg, parts=("x",))
+    idx = np.random.default_rng(T + E).integers(0, E, size=(cfg.T, k)).astype(np.int32)
+    check_dispatch(cfg, L["x"], idx)
+
+
 @pytest.mark.parametrize("chunks", [1, 63, 255, 256, 257, 520])
 @pytest.mark.parametrize("E", [7, 24, 25])
 def test_count_and_permute_row_copy_at_the_edges_of_its_steps(E, chunks):
