@@ -75,6 +75,7 @@ int moe_workspace_bytes(const moe_shape_t* shape, size_t* out_bytes);
  * whose leading k+1 scores are not clearly separated after the fast fp32 gate
  * product (closer than 2^-19 |x_t| max_e |w_e|, a margin that follows the size of
  * the terms that were added, not of their sum) is re-evaluated with fp64 sums.
+ * A batch beyond what one launch takes (never below 2^27 - 15 tokens) is MOE_ERR_UNSUPPORTED.
  */
 int moe_route(const moe_shape_t* shape, const void* x, const void* w_gate,
               const float* gate_bias, int32_t* topk_idx, float* topk_w, float* scores_out,

@@ -35,6 +35,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "launch_rules.h"
 #include "moe_internal.h"
 
 namespace moe {
@@ -42,9 +43,8 @@ namespace moe {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
-constexpr int RT_TM = 16;
 constexpr int RT_NW = 8;
-constexpr int RT_THREADS = RT_NW * MOE_WAVE;
+static_assert(RT_THREADS == RT_NW * MOE_WAVE, "waves of a block");
 constexpr int RT_BATCH = 16;  // MFMA steps whose x fragments are requested together
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -1164,7 +1164,8 @@ static int launch_route_rpw(const moe_shape_t* s, const void* x, const void* wg,
   if (ensure_dynamic_lds(once, reinterpret_cast<const void*>(route_kernel<BF16, NT, RPW, PRE>),
                          static_cast<int>(route_lds_bytes(MOE_MAX_E))) != MOE_OK)
     return MOE_ERR_HIP;
-  const int grid = (s->T + tpb - 1) / tpb;
+  const int grid = static_cast<int>((static_cast<int64_t>(s->T) + tpb - 1) / tpb);
+  if (!launch_fits(grid, RT_THREADS)) return MOE_ERR_UNSUPPORTED;
   hipLaunchKernelGGL((route_kernel<BF16, NT, RPW, PRE>), dim3(grid), dim3(RT_THREADS),
                      route_lds_bytes(s->E), st, static_cast<const uint4*>(x),
                      static_cast<const uint4*>(wg), bias, s->T, s->d, s->E, s->k, s->renorm, tpb,
@@ -1178,8 +1179,8 @@ template <bool BF16, int NT>
 static int launch_route(const moe_shape_t* s, const void* x, const void* wg, const float* bias,
                         int32_t* idx, float* w, float* scores, float* scratch, float* norms,
                         hipStream_t st) {
-  constexpr int CUS = 256;
   if constexpr (BF16) {
+    constexpr int CUS = 256;
     // Gate product spread over the chip first, if there is somewhere to put the scores and the
     // gate matrix is large enough (256 KB: 8 us through one CU) to pay for the second launch
     int tpb = RT_TM;                   // (the selection alone needs few registers: 256 blocks or more, two to a CU)
@@ -1207,8 +1208,8 @@ static int launch_route(const moe_shape_t* s, const void* x, const void* wg, con
   // fp32: one.  Every token takes the exact pass, in which the whole block works on one token after the other.
   // (Measured against the rule that bf16 had: d = 1024, E = 16, 512 tokens 10.0 -> 8.3, 1024 18.3 -> 13.7, 6000 88 -> 68; d = 1280,
   // E = 24, 1500 tokens 55 -> 38; up to 5 % slower at 1000 and 2000 tokens, where that rule's blocks just filled the chip.)
-  int tpb = 1;
-  while (BF16 && tpb < RT_TM && (s->T + tpb - 1) / tpb > CUS) tpb <<= 1;
+  // From 2^23 tokens on a launch does not take a block per token.
+  const int tpb = route_tokens_per_block(BF16, s->T);
   if (tpb == RT_TM)
     return launch_route_rpw<BF16, NT, 2, false>(s, x, wg, bias, idx, w, nullptr, nullptr, scores, tpb, st);
   return launch_route_rpw<BF16, NT, 1, false>(s, x, wg, bias, idx, w, nullptr, nullptr, scores, tpb, st);
@@ -1221,7 +1222,8 @@ static int launch_route_tile(const moe_shape_t* s, const void* x, const void* wg
   static LdsOnce once;
   if (ensure_dynamic_lds(once, reinterpret_cast<const void*>(route_tile_kernel<NT, TILES>), L::TOTAL) != MOE_OK)
     return MOE_ERR_HIP;
-  const int grid = (s->T + 16 * TILES - 1) / (16 * TILES);
+  const int grid = static_cast<int>((static_cast<int64_t>(s->T) + 16 * TILES - 1) / (16 * TILES));
+  if (!launch_fits(grid, RT_THREADS)) return MOE_ERR_UNSUPPORTED;
   hipLaunchKernelGGL((route_tile_kernel<NT, TILES>), dim3(grid), dim3(RT_THREADS), L::TOTAL, st,
                      static_cast<const uint4*>(x), static_cast<const uint4*>(wg), bias, s->T, s->d, s->E,
                      s->k, s->renorm, idx, w, scores);

@@ -260,6 +260,23 @@ def test_route_tokens_per_block(T, dtype):
     check_route(cfg, L["x"], L["w_gate"], None)
 
 
+def test_route_fp32_batch_too_large_for_a_block_per_token():
+    # 2^23 blocks of 512 threads are one more than a launch takes
+    T, d, E = 2 ** 23 + 3, 4, 3
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    x = torch.randn((T, d), device="cuda", generator=gen)
+    w = torch.randn((E, d), device="cuda", generator=gen)
+    idx = torch.full((T, 1), -1, dtype=torch.int32, device="cuda")
+    weight = torch.zeros((T, 1), device="cuda")
+    B.moe_route(B.make_shape(T, d, E, 1, 64, si.F32, 0), x, w, None, idx, weight)
+    torch.cuda.synchronize()
+    score = (x.double()[:, None, :] * w.double()[None]).sum(dim=2).float()   # (products exact, one rounding)
+    want = score.argmax(dim=1)
+    best = score.gather(1, want[:, None])
+    assert bool(((idx[:, 0] == want) | (score.gather(1, idx.long()) == best)[:, 0]).all())
+    assert bool(((weight - torch.softmax(score, dim=1).gather(1, want[:, None])).abs() <= 1e-5).all())
+
+
 @pytest.mark.parametrize("d", [1024, 4096, 5120, 16384])
 def test_route_few_near_ties_per_block(d):
     # 0 to 11 tokens of every 32-token block have two equal scores beside chosen ones up to a bias that only the
