@@ -211,29 +211,34 @@ __device__ int route_token(const float (&s)[QE], float bnd, bool check, int E, i
 }
 
 // Exact gate sum (fp64) of one (token row, expert row) pair per slot, this wave's part of the hidden
-// dimension, for 2^slots_log2 pairs.  Lane = (slot, one of 64 / slots sub-slices); the sub-slice sums of a slot
-// are added by lane exchanges; every lane returns its slot's sum.
-template <bool BF16>
+// dimension, for SLOTS pairs.  Lane = (slot, one of 64 / SLOTS sub-slices); the sub-slice sums of a slot
+// are added by lane exchanges; every lane returns its slot's sum.  The order of the sum follows from SLOTS and
+// row16 alone.
+template <bool BF16, int SLOTS>
 __device__ __forceinline__ double exact_slot_sum(const uint4* __restrict__ xrow, const uint4* __restrict__ wrow,
-                                                 int row16, int wave, int slots_log2) {
-  const int NSUB = MOE_WAVE >> slots_log2;
-  const int sub = lane_id() >> slots_log2;
+                                                 int row16, int wave) {
+  constexpr int NSUB = MOE_WAVE / SLOTS;
+  const int sub = lane_id() / SLOTS;
   const int cw = (row16 + RT_NW - 1) / RT_NW;
-  const int c0 = wave * cw;
+  const int c0 = __builtin_amdgcn_readfirstlane(wave) * cw;
   const int c1 = min(row16, c0 + cw);
   double acc = 0.0;
-  constexpr int XB = 8;
-  for (int cb = c0 + sub; cb < c1; cb += XB * NSUB) {
+  constexpr int XB = 8, XG = 2;      // chunk pairs requested together, in groups that are left out past the slice's end
+  for (int cb = c0; cb < c1; cb += XB * NSUB) {      // wave-uniform
     uint4 av[XB], bv[XB];
 #pragma unroll
-    for (int u = 0; u < XB; ++u) {
-      const int cc = min(cb + u * NSUB, row16 - 1);
-      av[u] = xrow[cc];
-      bv[u] = wrow[cc];
+    for (int g = 0; g < XB; g += XG) {
+      if (g > 0 && cb + g * NSUB >= c1) break;
+#pragma unroll
+      for (int u = g; u < g + XG; ++u) {
+        const int cc = min(cb + sub + u * NSUB, row16 - 1);
+        av[u] = xrow[cc];
+        bv[u] = wrow[cc];
+      }
     }
 #pragma unroll
     for (int u = 0; u < XB; ++u) {
-      if (cb + u * NSUB < c1) {
+      if (cb + sub + u * NSUB < c1) {
         const uint4 a = av[u];
         const uint4 b = bv[u];
         if (BF16) {
@@ -254,7 +259,8 @@ __device__ __forceinline__ double exact_slot_sum(const uint4* __restrict__ xrow,
       }
     }
   }
-  for (int off = 1 << slots_log2; off < MOE_WAVE; off <<= 1) acc += __shfl_xor(acc, off);
+#pragma unroll
+  for (int off = SLOTS; off < MOE_WAVE; off <<= 1) acc += __shfl_xor(acc, off);
   return acc;
 }
 
@@ -266,7 +272,7 @@ __device__ void exact_candidates(const uint4* __restrict__ xrow, const uint4* __
   const int lane = lane_id();
   const int c = lane & (RT_CMAX - 1);
   const int e = cand[c < n ? c : 0];
-  const double acc = exact_slot_sum<BF16>(xrow, wg + static_cast<int64_t>(e) * row16, row16, wave, 4);
+  const double acc = exact_slot_sum<BF16, RT_CMAX>(xrow, wg + static_cast<int64_t>(e) * row16, row16, wave);
   if (lane < RT_CMAX && c < n) dpart[wave * RT_CMAX + c] = acc;
 }
 
@@ -766,29 +772,23 @@ __device__ void select_tile(const float (&s)[S], float bnd, bool check, bool com
   }
 }
 
-// Exact gate sums of up to RT_CMAX (token, candidate expert) pairs, a token of its own per slot.
+// Exact gate sums of up to RT_CMAX (token, candidate expert) pairs, SLOTS at a time, a token of its own per slot.
 // pairs[] holds (row | position in the token's candidate list << 16).
 // Result: dpart[wave * RT_CMAX + pair].
-template <bool FEW>
+template <int SLOTS>
 __device__ void exact_pairs(const uint4* __restrict__ x, const uint4* __restrict__ wg, int row16,
                             int64_t t0, const int* __restrict__ pairs, int npairs,
                             const int* __restrict__ cand_all, int wave, double* __restrict__ dpart) {
   const int lane = lane_id();
-  // FEW: the pass takes no more slots than there are pairs, as long as that saves a trip to memory (eight chunks
-  // per lane are requested together).  A block of 8 or 16 experts has two pairs as a rule.  (Measured: d = 4096, 4096
-  // tokens, E = 8 / 16 19.8 / 19.5 -> 18.6 / 18.3 us, d = 5120, E = 16 22.3 -> 19.6; at 64 and 128 experts, where
-  // there are more pairs, 2 to 4 % slower: the run-time slot count costs registers.)
-  int slots_log2 = 4;
-  if constexpr (FEW)
-    while (slots_log2 > 1 && npairs <= 1 << (slots_log2 - 1) && (row16 + RT_NW - 1) / RT_NW > 8 * (MOE_WAVE >> slots_log2)) --slots_log2;
-  const int slots = 1 << slots_log2;
-  const int c = lane & (slots - 1);
-  const int entry = pairs[c < npairs ? c : 0];
-  const int prow = entry & 0xFFFF, pos = entry >> 16;
-  const int e = cand_all[prow * RT_CMAX + pos];
-  const double acc = exact_slot_sum<true>(x + (t0 + prow) * row16, wg + static_cast<int64_t>(e) * row16,
-                                          row16, wave, slots_log2);
-  if (lane < slots && c < npairs) dpart[wave * RT_CMAX + c] = acc;
+  for (int first = 0; first < npairs; first += SLOTS) {
+    const int c = first + (lane & (SLOTS - 1));
+    const int entry = pairs[c < npairs ? c : 0];
+    const int prow = entry & 0xFFFF, pos = entry >> 16;
+    const int e = cand_all[prow * RT_CMAX + pos];
+    const double acc = exact_slot_sum<true, SLOTS>(x + (t0 + prow) * row16, wg + static_cast<int64_t>(e) * row16,
+                                                   row16, wave);
+    if (lane < SLOTS && c < npairs) dpart[wave * RT_CMAX + c] = acc;
+  }
 }
 
 template <int NT, int TILES>
@@ -816,9 +816,10 @@ struct RouteTileLds {
   static_assert(TOTAL <= 160 * 1024, "LDS of the large-batch routing kernel");
 };
 
-// Requires d % (64 KS) == 0 and k <= RT_KSEL (the host checks).
+// Requires d % (64 KS) == 0 and k <= RT_KSEL (the host checks).  SLOTS: pairs that a wave of the exact pass sums at a
+// time (see launch_route_tile).
 // Four waves per SIMD (two blocks per CU, 128 registers) wherever the LDS use allows two blocks.
-template <int NT, int TILES>
+template <int NT, int TILES, int SLOTS>
 __global__ __launch_bounds__(RT_THREADS, (RouteTileLds<NT, TILES>::TOTAL <= 80 * 1024 ? 4 : 2)) void route_tile_kernel(
     const uint4* __restrict__ x, const uint4* __restrict__ wg, const float* __restrict__ bias, int T,
     int d, int E, int k, int renorm, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
@@ -1000,7 +1001,7 @@ __global__ __launch_bounds__(RT_THREADS, (RouteTileLds<NT, TILES>::TOTAL <= 80 *
   for (int base = 0; base < np; base += RT_CMAX) {
     // up to RT_CMAX (token, candidate) pairs share one pass over the hidden dimension
     const int cnt = min(RT_CMAX, np - base);
-    exact_pairs<NT == 1>(x, wg, row16, t0, plist + base, cnt, cand_all, wave, dpart);
+    exact_pairs<SLOTS>(x, wg, row16, t0, plist + base, cnt, cand_all, wave, dpart);
     __syncthreads();
     for (int c = 0; c < cnt; ++c) {
       const int prow = plist[base + c] & 0xFFFF;
@@ -1215,19 +1216,36 @@ static int launch_route(const moe_shape_t* s, const void* x, const void* wg, con
   return launch_route_rpw<BF16, NT, 1, false>(s, x, wg, bias, idx, w, nullptr, nullptr, scores, tpb, st);
 }
 
-template <int NT, int TILES>
-static int launch_route_tile(const moe_shape_t* s, const void* x, const void* wg, const float* bias,
-                             int32_t* idx, float* w, float* scores, hipStream_t st) {
+template <int NT, int TILES, int SLOTS>
+static int launch_route_tile_slots(const moe_shape_t* s, const void* x, const void* wg, const float* bias,
+                                   int32_t* idx, float* w, float* scores, hipStream_t st) {
   using L = RouteTileLds<NT, TILES>;
   static LdsOnce once;
-  if (ensure_dynamic_lds(once, reinterpret_cast<const void*>(route_tile_kernel<NT, TILES>), L::TOTAL) != MOE_OK)
+  if (ensure_dynamic_lds(once, reinterpret_cast<const void*>(route_tile_kernel<NT, TILES, SLOTS>), L::TOTAL) != MOE_OK)
     return MOE_ERR_HIP;
   const int grid = static_cast<int>((static_cast<int64_t>(s->T) + 16 * TILES - 1) / (16 * TILES));
   if (!launch_fits(grid, RT_THREADS)) return MOE_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL((route_tile_kernel<NT, TILES>), dim3(grid), dim3(RT_THREADS), L::TOTAL, st,
+  hipLaunchKernelGGL((route_tile_kernel<NT, TILES, SLOTS>), dim3(grid), dim3(RT_THREADS), L::TOTAL, st,
                      static_cast<const uint4*>(x), static_cast<const uint4*>(wg), bias, s->T, s->d, s->E,
                      s->k, s->renorm, idx, w, scores);
   return launch_status();
+}
+
+template <int NT, int TILES>
+static int launch_route_tile(const moe_shape_t* s, const void* x, const void* wg, const float* bias,
+                             int32_t* idx, float* w, float* scores, hipStream_t st) {
+  // A block of up to 16 experts has two pairs for the exact pass as a rule, and with fewer slots a slot's lanes
+  // request a row of 2048 (16 slots), 4096 (8) or 8192 elements (4) in one trip to memory.  By the width alone
+  // and not by the pairs that a pass has: the order of a sum must not depend on what shares the pass, or equal gate
+  // rows could get different scores.  (Measured at 4096 tokens, 16 slots -> this, us: d = 4096, E = 8 / 16 20.1 / 20.3 ->
+  // 18.6 / 18.8, d = 5120 27.3 / 28.3 -> 24.2 / 25.0, d = 7168 33.7 / 34.7 -> 29.2 / 30.0; with every token in the exact
+  // pass, E = 8: d = 4096 143 -> 143, 5120 179 -> 187, 8192 233 -> 226.  At 64 and 128 experts, where there are more pairs,
+  // fewer slots were 2 to 4 % slower.)
+  if constexpr (NT == 1) {
+    if (s->d > 4096) return launch_route_tile_slots<NT, TILES, 4>(s, x, wg, bias, idx, w, scores, st);
+    if (s->d > 2048) return launch_route_tile_slots<NT, TILES, 8>(s, x, wg, bias, idx, w, scores, st);
+  }
+  return launch_route_tile_slots<NT, TILES, RT_CMAX>(s, x, wg, bias, idx, w, scores, st);
 }
 
 // The large-batch path takes over when the batch gives enough blocks of at least two tiles (the

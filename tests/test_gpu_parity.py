@@ -260,6 +260,32 @@ def test_route_tokens_per_block(T, dtype):
     check_route(cfg, L["x"], L["w_gate"], None)
 
 
+@pytest.mark.parametrize("d", [2048, 2560, 4096, 5120, 8192])
+@pytest.mark.parametrize("near", [2, 3])
+def test_route_equal_gate_rows_get_equal_exact_scores(d, near):
+    # `near` tokens of every 32-token block go through the exact pass with all 12 experts: 24 or 36 pairs, so a
+    # token's pairs are split between a group of 16, 8 or 4 and a shorter one.  Their large terms cancel, and the sums of
+    # such terms depend on their order even in fp64: the equal rows 3 and 5 have to be summed in one order.
+    T, E, k, A = 4096, 12, 4, 2.0 ** 30
+    rng = np.random.default_rng(d)
+    w = rng.standard_normal((E, d))
+    w[:, 0:d // 2:2] = np.abs(w[:, 0:d // 2:2]) + 0.5
+    w[:, d // 2::2] = w[:, 0:d // 2:2]
+    w[5] = w[3]
+    x = rng.standard_normal((T, d))
+    x -= np.outer(x @ w[3] / (w[3] @ w[3]) + 8.0 / np.sqrt(w[3] @ w[3]), w[3])    # (3 and 5 last for all other tokens)
+    large = np.arange(T) % 32 < near
+    u = A * rng.uniform(0.5, 2.0, size=(int(large.sum()), d // 4))
+    half = x[large]
+    half[:, 0:d // 2:2], half[:, d // 2::2] = u, -u
+    x[large] = half
+    cfg = si.small_config(T=T, d=d, E=E, k=k, F=64)
+    idx, _, sc = gpu_route(cfg, si.f32_to_bf16_bits(x.astype(np.float32)), si.f32_to_bf16_bits(w.astype(np.float32)), None)
+    assert np.array_equal(sc[:, 3].view(np.int32), sc[:, 5].view(np.int32))
+    at = np.where(idx == 3, np.arange(k), k).min(axis=1)
+    assert np.all(np.where(idx == 5, np.arange(k), k).min(axis=1) >= np.minimum(at + 1, k))
+
+
 def test_route_fp32_batch_too_large_for_a_block_per_token():
     # 2^23 blocks of 512 threads are one more than a launch takes
     T, d, E = 2 ** 23 + 3, 4, 3
@@ -280,7 +306,7 @@ def test_route_fp32_batch_too_large_for_a_block_per_token():
 @pytest.mark.parametrize("d", [1024, 4096, 5120, 16384])
 def test_route_few_near_ties_per_block(d):
     # 0 to 11 tokens of every 32-token block have two equal scores beside chosen ones up to a bias that only the
-    # exact pass sees: 0 to 22 (token, expert) pairs per block, in passes of 2, 4, 8 or 16 (wider rows, fewer)
+    # exact pass sees: 0 to 22 (token, expert) pairs per block, summed 16, 8 or 4 at a time (wider rows, fewer)
     cfg = si.small_config(T=3100, d=d, E=8, k=2, F=64)
     L = si.make_layer(cfg, parts=("x", "w_gate"))
     wg = L["w_gate"].copy()
