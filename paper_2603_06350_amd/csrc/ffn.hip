@@ -1489,20 +1489,6 @@ __global__ __launch_bounds__(256) void ffn_wide_kernel(GemmArgs p) {
   }
 }
 
-// Compute units of the current device, looked up once per device (0 if the query fails: the
-// kernels then assume 256).
-static int device_cu_count() {
-  static int cached[MOE_MAX_DEVICES] = {};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MOE_MAX_DEVICES) return 0;
-  if (cached[dev] == 0) {
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    cached[dev] = n;
-  }
-  return cached[dev];
-}
-
 // Upper bound on the number of m-tiles that needs no knowledge of the counts: an expert with c rows
 // has ceil(c / bm) <= c / bm + 1 tiles, and at most min(E, A) experts have any.
 static int64_t max_m_tiles(int64_t A, int E, int bm) { return A / bm + (E < A ? E : A); }

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "launch_rules.h"
 #include "moe.h"
 
 #define MOE_MAX_E 256
@@ -56,6 +57,20 @@ inline int ensure_dynamic_lds(LdsOnce& once, const void* kernel, int bytes) {
     return MOE_ERR_HIP;
   once.done[dev] = true;
   return MOE_OK;
+}
+
+// Compute units of the current device, looked up once per device (0 if the query fails: the
+// kernels then assume 256).
+inline int device_cu_count() {
+  static int cached[MOE_MAX_DEVICES] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MOE_MAX_DEVICES) return 0;
+  if (cached[dev] == 0) {
+    int n = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    cached[dev] = n;
+  }
+  return cached[dev];
 }
 
 // ---- device helpers -------------------------------------------------------------------------

@@ -35,7 +35,6 @@
 #include <type_traits>
 #include <utility>
 
-#include "launch_rules.h"
 #include "moe_internal.h"
 
 namespace moe {
@@ -300,7 +299,40 @@ __device__ void exact_partial(const uint4* __restrict__ xrow, const uint4* __res
     // eight chunk pairs are requested before the first is used (the loads are L2/HBM round
     // trips; the fp64 sum order stays ascending in c)
     constexpr int XB = 8;
-    for (int cb = c0 + sub; cb < c1; cb += XB * nsub) {
+    auto add = [&](uint4 a, uint4 b) {
+      if (BF16) {
+        acc = fma(static_cast<double>(bf16lo(a.x)), static_cast<double>(bf16lo(b.x)), acc);
+        acc = fma(static_cast<double>(bf16hi(a.x)), static_cast<double>(bf16hi(b.x)), acc);
+        acc = fma(static_cast<double>(bf16lo(a.y)), static_cast<double>(bf16lo(b.y)), acc);
+        acc = fma(static_cast<double>(bf16hi(a.y)), static_cast<double>(bf16hi(b.y)), acc);
+        acc = fma(static_cast<double>(bf16lo(a.z)), static_cast<double>(bf16lo(b.z)), acc);
+        acc = fma(static_cast<double>(bf16hi(a.z)), static_cast<double>(bf16hi(b.z)), acc);
+        acc = fma(static_cast<double>(bf16lo(a.w)), static_cast<double>(bf16lo(b.w)), acc);
+        acc = fma(static_cast<double>(bf16hi(a.w)), static_cast<double>(bf16hi(b.w)), acc);
+      } else {
+        acc = fma(static_cast<double>(__uint_as_float(a.x)), static_cast<double>(__uint_as_float(b.x)), acc);
+        acc = fma(static_cast<double>(__uint_as_float(a.y)), static_cast<double>(__uint_as_float(b.y)), acc);
+        acc = fma(static_cast<double>(__uint_as_float(a.z)), static_cast<double>(__uint_as_float(b.z)), acc);
+        acc = fma(static_cast<double>(__uint_as_float(a.w)), static_cast<double>(__uint_as_float(b.w)), acc);
+      }
+    };
+    int cb = c0 + sub;
+    if constexpr (!BF16 && QE >= 4) {
+      // whole trips without clamps between the loads: more than 128 experts leave one block per CU, and nothing else
+      // hides what the clamps cost (256 experts, d = 1024, 512 tokens 102 -> 82 us, d = 4096 312 -> 299).  With fewer
+      // experts a second copy of the trip is no gain.
+      for (; cb - sub + XB <= c1; cb += XB) {          // (nsub is 1)
+        uint4 av[XB], bv[XB];
+#pragma unroll
+        for (int u = 0; u < XB; ++u) {
+          av[u] = xrow[cb + u];
+          bv[u] = wrow[cb + u];
+        }
+#pragma unroll
+        for (int u = 0; u < XB; ++u) add(av[u], bv[u]);
+      }
+    }
+    for (; cb < c1; cb += XB * nsub) {
       uint4 av[XB], bv[XB];
 #pragma unroll
       for (int u = 0; u < XB; ++u) {
@@ -309,27 +341,8 @@ __device__ void exact_partial(const uint4* __restrict__ xrow, const uint4* __res
         bv[u] = wrow[c];
       }
 #pragma unroll
-      for (int u = 0; u < XB; ++u) {
-        if (cb + u * nsub < c1) {
-          const uint4 a = av[u];
-          const uint4 b = bv[u];
-          if (BF16) {
-            acc = fma(static_cast<double>(bf16lo(a.x)), static_cast<double>(bf16lo(b.x)), acc);
-            acc = fma(static_cast<double>(bf16hi(a.x)), static_cast<double>(bf16hi(b.x)), acc);
-            acc = fma(static_cast<double>(bf16lo(a.y)), static_cast<double>(bf16lo(b.y)), acc);
-            acc = fma(static_cast<double>(bf16hi(a.y)), static_cast<double>(bf16hi(b.y)), acc);
-            acc = fma(static_cast<double>(bf16lo(a.z)), static_cast<double>(bf16lo(b.z)), acc);
-            acc = fma(static_cast<double>(bf16hi(a.z)), static_cast<double>(bf16hi(b.z)), acc);
-            acc = fma(static_cast<double>(bf16lo(a.w)), static_cast<double>(bf16lo(b.w)), acc);
-            acc = fma(static_cast<double>(bf16hi(a.w)), static_cast<double>(bf16hi(b.w)), acc);
-          } else {
-            acc = fma(static_cast<double>(__uint_as_float(a.x)), static_cast<double>(__uint_as_float(b.x)), acc);
-            acc = fma(static_cast<double>(__uint_as_float(a.y)), static_cast<double>(__uint_as_float(b.y)), acc);
-            acc = fma(static_cast<double>(__uint_as_float(a.z)), static_cast<double>(__uint_as_float(b.z)), acc);
-            acc = fma(static_cast<double>(__uint_as_float(a.w)), static_cast<double>(__uint_as_float(b.w)), acc);
-          }
-        }
-      }
+      for (int u = 0; u < XB; ++u)
+        if (cb + u * nsub < c1) add(av[u], bv[u]);
     }
     for (int off = ep; off < MOE_WAVE; off <<= 1) acc += __shfl_xor(acc, off);
     if (sub == 0 && e < E) dpart[wave * E + e] = acc;
@@ -340,7 +353,8 @@ __device__ void exact_partial(const uint4* __restrict__ xrow, const uint4* __res
 //              int cand[RT_TM][RT_CMAX] | int flag[RT_TM] | float xn[RT_NW * 4][RT_TM] |
 //              float wn[RT_NW * 4][<= 16 NT]   (per wave and lane group: parts of |x_t|^2 and |w_e|^2)
 // RPW = tile rows routed per wave: 2 (a full 16-token tile; compile-time so that the two tokens'
-// dependency chains interleave) or 1 (tpb <= 8 tokens per block).
+// dependency chains interleave) or 1 (tpb <= 8 tokens per block; fp32 layers, whose tokens all go through the
+// exact pass).
 // PRE: the fast scores (bias included) were already written to scores_in[T][E] by
 // gate_tile_kernel, and |x_t|^2, |w_e|^2 to norms[T + E]; this kernel only selects and runs the
 // exact pass.  scores_in may be the same buffer as scores_out: a token's scores are read before
@@ -517,14 +531,14 @@ __global__ __launch_bounds__(RT_THREADS) void route_kernel(
     const int t = t0 + row;
     const uint4* xrow = x + static_cast<int64_t>(t) * row16;
     const int* cand = cand_all + row * RT_CMAX;
-    if (n <= RT_CMAX)
+    if (BF16 && n <= RT_CMAX)
       exact_candidates<BF16>(xrow, wg, row16, cand, n, wave, dpart);
     else
       exact_partial<BF16, QE>(xrow, wg, row16, E, wave, dpart);
     __syncthreads();
     if (wave == (row % RT_NW)) {
       float s[QE];
-      if (n <= RT_CMAX) {
+      if (BF16 && n <= RT_CMAX) {
         // fast scores everywhere, exact (fp64 sum, one rounding) for the listed candidates
         fast_scores(row, s);
         for (int c = 0; c < n; ++c) {
@@ -1180,12 +1194,12 @@ template <bool BF16, int NT>
 static int launch_route(const moe_shape_t* s, const void* x, const void* wg, const float* bias,
                         int32_t* idx, float* w, float* scores, float* scratch, float* norms,
                         hipStream_t st) {
+  const int n_cu = device_cu_count(), cus = n_cu > 0 ? n_cu : 256;
   if constexpr (BF16) {
-    constexpr int CUS = 256;
     // Gate product spread over the chip first, if there is somewhere to put the scores and the
     // gate matrix is large enough (256 KB: 8 us through one CU) to pay for the second launch
-    int tpb = RT_TM;                   // (the selection alone needs few registers: 256 blocks or more, two to a CU)
-    while (tpb > 1 && (s->T + tpb - 1) / tpb < CUS) tpb >>= 1;
+    int tpb = RT_TM;                   // (the selection alone needs few registers: a block per CU or more, two fit one)
+    while (tpb > 1 && (s->T + tpb - 1) / tpb < cus) tpb >>= 1;
     if (tpb < RT_TM && scratch && norms && s->T <= RT_PRE_MAX_T && static_cast<int64_t>(s->E) * s->d * 2 >= 256 * 1024) {
       const int t_tiles = (s->T + RT_TM - 1) / RT_TM;
       if (static_cast<int64_t>(t_tiles) * ((s->E + 63) / 64) >= 256)
@@ -1200,19 +1214,11 @@ static int launch_route(const moe_shape_t* s, const void* x, const void* wg, con
       return launch_route_rpw<BF16, NT, 1, true>(s, x, wg, bias, idx, w, scratch, norms, scores, tpb, st);
     }
   }
-  // Tokens per block, the other rows of the 16-row tile idle.  bf16: the fewest that leave no more than one block
-  // per CU.  A block has a CU to itself (512 threads of more than 128 registers), so blocks past the 256th are a second
-  // round, which costs more than the shorter tail of every block saves; from 4097 tokens on the tile is full.  (Measured,
-  // the most tokens that still give 256 blocks -> this, us: d = 4096, E = 8, 257 tokens 13.4 -> 8.1, 500 13.8 -> 8.0, 1000
-  // 14.6 -> 8.5, 1500 15.7 -> 10.2; d = 5120, E = 16, 1000 tokens 25.6 -> 14.5, 3000 30.9 -> 26.3; d = 1048, E = 12,
-  // 1501 tokens 13.0 -> 11.1; the same at 512, 1024 and 2048.)
-  // fp32: one.  Every token takes the exact pass, in which the whole block works on one token after the other.
-  // (Measured against the rule that bf16 had: d = 1024, E = 16, 512 tokens 10.0 -> 8.3, 1024 18.3 -> 13.7, 6000 88 -> 68; d = 1280,
-  // E = 24, 1500 tokens 55 -> 38; up to 5 % slower at 1000 and 2000 tokens, where that rule's blocks just filled the chip.)
-  // From 2^23 tokens on a launch does not take a block per token.
-  const int tpb = route_tokens_per_block(BF16, s->T);
-  if (tpb == RT_TM)
-    return launch_route_rpw<BF16, NT, 2, false>(s, x, wg, bias, idx, w, nullptr, nullptr, scores, tpb, st);
+  const int tpb = route_tokens_per_block(BF16, s->T, s->E, s->d, cus);
+  if constexpr (BF16) {
+    if (tpb == RT_TM)
+      return launch_route_rpw<BF16, NT, 2, false>(s, x, wg, bias, idx, w, nullptr, nullptr, scores, tpb, st);
+  }
   return launch_route_rpw<BF16, NT, 1, false>(s, x, wg, bias, idx, w, nullptr, nullptr, scores, tpb, st);
 }
 

@@ -251,11 +251,22 @@ def test_route_large_batch_ties_and_near_ties(T, E):
     assert np.all(idx[:, 0] == 3) and idx.max() < 20
 
 
-@pytest.mark.parametrize("T", [255, 257, 300, 512, 513, 1025, 2049, 4097])
+@pytest.mark.parametrize("T", [255, 256, 257, 300, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097])
 @pytest.mark.parametrize("dtype", [si.BF16, si.F32])
 def test_route_tokens_per_block(T, dtype):
-    # around the batch sizes at which a block of the per-tile kernel takes twice the tokens (fp32: always one)
+    # around the batch sizes at which a bf16 block of the per-tile kernel takes twice the tokens (up to 2049) or the
+    # blocks are more than the compute units (4097)
     cfg = si.small_config(T=T, d=136, E=12, k=3, F=64, dtype=dtype)
+    L = si.make_layer(cfg, parts=("x", "w_gate"))
+    check_route(cfg, L["x"], L["w_gate"], None)
+
+
+@pytest.mark.parametrize("T,d,E", [(1000, 136, 12), (2047, 136, 12), (8191, 32, 48), (2000, 1024, 16), (513, 16, 129),
+                                   (1023, 2048, 129), (4095, 16, 256), (511, 1024, 128), (2047, 1024, 128)])
+def test_route_fp32_several_tokens_per_block(T, d, E):
+    # 2, 4, 16 and 2 tokens per block of layers with a small gate, 1 (three rounds), 4 and 16 with more than 128 experts,
+    # 2 and 8 with a large gate; the last block is short
+    cfg = si.small_config(T=T, d=d, E=E, k=3, F=64, dtype=si.F32)
     L = si.make_layer(cfg, parts=("x", "w_gate"))
     check_route(cfg, L["x"], L["w_gate"], None)
 
