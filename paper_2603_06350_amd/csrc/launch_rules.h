@@ -34,7 +34,6 @@ constexpr int RT_THREADS = 512;        // threads of a routing block
 //   - gates of 512 KiB and more of 65 to 128 experts, if one block per CU is left: tokens that a CU takes one after the
 //     other find more of the gate in its caches than the tokens of two blocks at once.  d = 1024, E = 128, 512 tokens
 //     60 -> 52, 2048 205 -> 191; the same layer with d = 512 is slower so (1000 tokens 16 %).
-// (Against the rule that gave a CU a block or more, as bf16 had: E = 4 to 256, d = 128 to 4096, 300 to 16384 tokens, 0.98
 // (Against the rule that gave every CU a block or more, as bf16 had: E = 4 to 256, d = 128 to 4096, 16 to 16384 tokens,
 // 397 shapes: 0.97 to 1.76 times as fast.)
 inline int route_tokens_per_block(bool bf16, int T, int E, int d, int cus) {
