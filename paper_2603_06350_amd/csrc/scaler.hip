@@ -340,37 +340,24 @@ extern "C" int moe_replica_segments(int32_t E, const int32_t* offsets, const int
 // as in scale_kernel), and per step the load, the warm GPU and the place of the result.  Bound by
 // the chain of dependent instructions from step to step:
 //   - a run of warm steps is one fp64 addition each, in the lane of its GPU;
-//   - a run of four and more others, on up to 16 GPUs: the lanes hold the GPUs in ascending order of
-//     (load, index).  The first one takes the replica, and every lane finds by itself whether it keeps
-//     its GPU, takes its right neighbour's or the one that moved up: DPP moves and two comparisons, no trip
-//     through scalar registers;
-//   - shorter runs, more GPUs, and 64 steps in which a GPU may run out of slots: the shortest queue is an arg-min
-//     over the lanes with a free slot (upper words of the non-negative doubles by DPP, a ballot, lower words
-//     only on a tie).
-// Measured, calls back to back, every step by arg-min or warm look-up -> now, us: 64 experts, 128 replicas, 8 GPUs, all warm
-// 18.8 -> 6.8, all new 33 -> 25; 256 experts, 1256 replicas, 8 GPUs 143 -> 42 and 295 -> 221; 40 GPUs, 128
-// replicas, all new 41 -> 31; slots that run out 33 -> 34.
+//   - a run of others, each to the shortest queue: an arg-min over the lanes (upper words of the non-negative doubles by
+//     DPP, a ballot, lower words only on a tie);
+//   - 64 steps in which a GPU may run out of slots: the same step by step, over the lanes with a free slot.
+// Measured, calls back to back, every step looked up by itself -> now, us: 64 experts, 128 replicas, 8 GPUs, all warm
+// 19.0 -> 7.1, 30 % new 22.5 -> 17.0, all new 31.5 -> 23.2; 256 experts, 1256 replicas, 8 GPUs 143 -> 42, 179 -> 137 and
+// 270 -> 204; 40 GPUs, 128 replicas, all new 38.4 -> 28.6; slots that run out 32 -> 31.  (Lanes kept in the order of
+// their loads, so that a run of new replicas needs no arg-min: a step is no shorter, and sorting them for each run
+// cost 1.5 us on 16 GPUs.)
 // ---------------------------------------------------------------------------------------------
 namespace moe {
 
 constexpr int PL_MAX_GPUS = MOE_WAVE;
 constexpr int PL_CHUNK = 1024;
-constexpr int PL_SORT_RUN = 4;
 struct PlaceStep {
   double w;        // load of the replica
   int warm;        // GPU of the previous round, -1 = none
   int out;         // index of the replica in gpu_of
 };
-
-// DPP moves of a double; `hi` and `lo` where a lane has no source.
-template <int CTRL> __device__ __forceinline__ double dpp_f64(double x, int hi, int lo) {
-  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, __double2hiint(x), CTRL, 0xF, 0xF, false),
-                          __builtin_amdgcn_update_dpp(lo, __double2loint(x), CTRL, 0xF, 0xF, false));
-}
-__device__ __forceinline__ double push_f64(double x, int to_lane) {
-  return __hiloint2double(__builtin_amdgcn_ds_permute(to_lane * 4, __double2hiint(x)),
-                          __builtin_amdgcn_ds_permute(to_lane * 4, __double2loint(x)));
-}
 
 // WIDE: more than 16 GPUs.
 template <bool WIDE>
@@ -502,49 +489,16 @@ __global__ __launch_bounds__(256) void place_kernel(
           if (i >= cnt) break;
           const unsigned long long again = ~(mask >> i);        // (not zero: bit 63 - i and above, or i = 0 and all cold)
           const int run = min(cnt - i, again == 0ull ? MOE_WAVE : __ffsll(static_cast<long long>(again)) - 1);
-          if (!WIDE && run >= PL_SORT_RUN) {
-            const double inf = __hiloint2double(0x7FF00000, 0);
-            double ld = lane < G ? gload : inf;
-            int to = lane < G ? 0 : lane;      // place in the order
-            for (int g = 0; g < G; ++g) {
-              const double l = readlane_f64(ld, g);
-              to += lane < G && (l < ld || (l == ld && g < lane)) ? 1 : 0;
+          double load = st[i].w;
+          for (int t = 0; t < run; ++t) {
+            const double next = st[i + t + 1].w;
+            const int g = shortest(all);
+            if (lane == g) {
+              gload += load;
+              gcount += 1;
             }
-            ld = push_f64(ld, to);
-            int id = __builtin_amdgcn_ds_permute(to * 4, lane), ct = __builtin_amdgcn_ds_permute(to * 4, gcount);
-            int res = 0;
-#pragma unroll 4
-            for (int t = 0; t < run; ++t) {
-              const double v = dpp_f64<0x150>(ld, 0, 0) + st[i + t].w;                    // row_newbcast:0
-              const int vid = __builtin_amdgcn_update_dpp(0, id, 0x150, 0xF, 0xF, false);
-              const int vct = __builtin_amdgcn_update_dpp(0, ct, 0x150, 0xF, 0xF, false) + 1;
-              const double nl = dpp_f64<0x101>(ld, 0x7FF00000, 0);                        // row_shl:1
-              const int nid = __builtin_amdgcn_update_dpp(lane, id, 0x101, 0xF, 0xF, false);
-              const int nct = __builtin_amdgcn_update_dpp(0, ct, 0x101, 0xF, 0xF, false);
-              const bool next_before = nl < v || (nl == v && nid < vid);
-              const bool before = lane == 0 || ld < v || (ld == v && id < vid);
-              const int joined = __builtin_amdgcn_readfirstlane(id);      // (a broadcast stays in its row of 16 lanes)
-              res = lane == t ? joined : res;
-              ld = next_before ? nl : before ? v : ld;
-              id = next_before ? nid : before ? vid : id;
-              ct = next_before ? nct : before ? vct : ct;
-            }
-            if (lane < run) st[i + lane].warm = res;
-            gload = push_f64(ld, id);
-            gcount = __builtin_amdgcn_ds_permute(id * 4, ct);
-            if (lane >= G) gload = 0.0;
-          } else {
-            double load = st[i].w;
-            for (int t = 0; t < run; ++t) {
-              const double next = st[i + t + 1].w;
-              const int g = shortest(all);
-              if (lane == g) {
-                gload += load;
-                gcount += 1;
-              }
-              if (lane == 0) st[i + t].warm = g;
-              load = next;
-            }
+            if (lane == 0) st[i + t].warm = g;
+            load = next;
           }
           i += run;
         }

@@ -424,8 +424,8 @@ def test_scale_replicas_stops_at_every_step(E, total, alpha):
 @pytest.mark.parametrize("G", [1, 2, 15, 16, 17, 64])
 @pytest.mark.parametrize("new", [0.0, 0.1, 0.5, 0.97, 1.0])
 def test_place_replicas_in_runs_of_warm_and_new_ones(G, new):
-    # runs of warm steps, of new ones shorter and longer than four and across the kernel's 64-step blocks; many
-    # equal loads; without slots, with slots that run out near the end, and with few
+    # runs of warm steps and of new ones, of all lengths and across the kernel's 64-step blocks; many equal loads;
+    # without slots, with slots that run out near the end, and with few
     rng = np.random.default_rng(int(100 * new) + G)
     E = 90
     loads = rng.integers(0, 6, size=E) * 12
