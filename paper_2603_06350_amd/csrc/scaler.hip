@@ -46,7 +46,8 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
 }
 
 // Sum over the wave by DPP (prefix sums inside the rows of 16 lanes, two row broadcasts), read from lane 63.
-__device__ __forceinline__ double wave_sum_dpp(double v) {
+// ROWS = false: of lanes 0 .. 15 only.
+template <bool ROWS = true> __device__ __forceinline__ double wave_sum_dpp(double v) {
   auto step = [](double x, auto ctrl, auto rows) {
     return x + __hiloint2double(
         __builtin_amdgcn_update_dpp(0, __double2hiint(x), decltype(ctrl)::value, decltype(rows)::value, 0xF, false),
@@ -57,6 +58,7 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
   v = step(v, integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});
   v = step(v, integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});
   v = step(v, integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});
+  if constexpr (!ROWS) return readlane_f64(v, 15);
   v = step(v, integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});
   v = step(v, integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});
   return readlane_f64(v, 63);
@@ -88,14 +90,17 @@ template <bool ROWS> __device__ __forceinline__ float wave_sum_f32(float v) {
 //     grows with every step, so if (n + 1) times the S2 after the round is above (fp32 tells to 1e-4), it is above
 //     after every step of it.  If that is not enough: a step lowers S2 by W/R * W/(R+1); with m the largest such
 //     drop of the round, S2 after j of its c steps is at least S2 - j m, and (n + j) (S2 - j m) is least at j = 1
-//     or j = c.  Otherwise the round is one step, the straggler, and the sum fp64; where the test is then closer
-//     than 1e-9, the definition of CV decides, as it does for the two values reported;
+//     or j = c.  Where that does not settle it, the next SC_SINGLES steps (one, if no expert is above all further
+//     splits) are taken one by one: the straggler by arg-max, S2 in fp64, summed once for these steps and lowered by each
+//     step's drop (the error, below 1e-13, is far inside the 1e-9 within which the definition of CV decides, as it does
+//     for the two values reported).  CV near V stays near V for a while, and each attempt at a whole round costs a step;
 //   - the quotients after one and after two further splits are kept, so the division for the experts just split is
 //     not needed in the next round.
 // Bound by the chain of a round (DPP maxima and a DPP sum; SMALL: up to 16 experts, four DPP steps each instead of
-// six).  Measured on Zipf loads, calls back to back, one step per round -> now, us: 64 experts and 64 further replicas (26
-// rounds) 19.8 -> 9.7, 128 and 256 (86 rounds) 91 -> 33, 256 and 1000 430 -> 143; 8 and 30 with V = 0, where half
-// the rounds are one step, 10.6 -> 12.8.
+// six).  Measured on Zipf loads, calls back to back, every step by itself -> rounds, one step where they fail -> now, us:
+// 64 experts and 64 further replicas 20.2 -> 10.2 -> 9.2, 128 and 256 91 -> 33 -> 32, 256 and 1000 433 -> 144 -> 137;
+// 8 and 30, V = 0 10.8 -> 11.8 -> 7.9, V = 0.1 10.8 -> 16.5 -> 8.9, V = 0.3 (4 steps) 4.4 -> 5.5 -> 3.9.
+constexpr int SC_SINGLES = 16;
 template <int Q, bool SMALL = false>
 __global__ __launch_bounds__(MOE_WAVE) void scale_kernel(const int32_t* __restrict__ loads, int E,
                                                          int max_extra, double cv_threshold,
@@ -139,7 +144,7 @@ __global__ __launch_bounds__(MOE_WAVE) void scale_kernel(const int32_t* __restri
   const float over_f32 = static_cast<float>(limit) * 1.0001f;
   bool more = max_extra > 0 && cv_first > cv_threshold;
   while (more) {                               // wave-uniform
-    uint32_t mk = 0, mn = 0;
+    uint32_t mn = 0;
 #pragma unroll
     for (int q = 0; q < Q; ++q) mn = max(mn, hi32(next[q]));
     const uint32_t top_next = wave_extreme<true, !SMALL>(mn);
@@ -171,8 +176,8 @@ __global__ __launch_bounds__(MOE_WAVE) void scale_kernel(const int32_t* __restri
 #pragma unroll
     for (int q = 0; q < Q; ++q) part_f += static_cast<float>(w[q]) * static_cast<float>(take[q] ? next[q] : key[q]);
     const float s2f = wave_sum_f32<!SMALL>(part_f);
-    bool one = count == 0 || !(cv_threshold < 0.0 || static_cast<float>(n + 1) * s2f > over_f32);
-    if (one && count > 1) {
+    bool over = cv_threshold < 0.0 || static_cast<float>(n + 1) * s2f > over_f32;
+    if (!over && count > 1) {
       float drop = 0.f, all = 0.f;
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
@@ -182,50 +187,78 @@ __global__ __launch_bounds__(MOE_WAVE) void scale_kernel(const int32_t* __restri
       }
       const float before = s2f + wave_sum_f32<!SMALL>(all);
       drop = __uint_as_float(wave_extreme<true, !SMALL>(__float_as_uint(drop)));   // (not negative: ordered as integers)
-      one = !(fminf(static_cast<float>(n + 1) * (before - drop),
-                    static_cast<float>(n + count) * (before - static_cast<float>(count) * drop)) > over_f32);
+      over = fminf(static_cast<float>(n + 1) * (before - drop),
+                   static_cast<float>(n + count) * (before - static_cast<float>(count) * drop)) > over_f32;
     }
-    double s2 = 0.0;
-    if (one) {                                 // the straggler: largest quotient, lowest index
+    int singles = count == 0 ? 1 : over ? 0 : SC_SINGLES;      // steps to be taken one by one
+    if (singles == 0) {
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        if (take[q]) {
+          key[q] = next[q];
+          next[q] = third[q];
+          r[q] += 1;
+        }
+        third[q] = w[q] / static_cast<double>(r[q] + 2);
+      }
+      n += count;
+      extra += count;
+      more = extra < max_extra;
+      continue;
+    }
+    double part = 0.0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) part += w[q] * key[q];
+    double s2 = wave_sum_dpp<!SMALL>(part);
+    for (; singles > 0 && more; --singles) {
+      // the straggler: largest quotient, lowest index
+      uint32_t mk = 0;
 #pragma unroll
       for (int q = 0; q < Q; ++q) mk = max(mk, hi32(key[q]));
-      const uint32_t top = wave_extreme<true>(mk);
-      if (top == 0u) break;                    // every load is zero: nothing to split
-      uint32_t ml = 0;
+      const uint32_t top = wave_extreme<true, !SMALL>(mk);
+      if (top == 0u) {                         // every load is zero: nothing to split
+        more = false;
+        break;
+      }
+      unsigned long long who[Q];
+      int tied = 0;
 #pragma unroll
-      for (int q = 0; q < Q; ++q) ml = max(ml, hi32(key[q]) == top ? lo32(key[q]) : 0u);
-      const uint32_t top_lo = wave_extreme<true>(ml);
+      for (int q = 0; q < Q; ++q) {
+        who[q] = __ballot(hi32(key[q]) == top);
+        tied += __popcll(who[q]);
+      }
+      if (tied > 1) {
+        uint32_t ml = 0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) ml = max(ml, hi32(key[q]) == top ? lo32(key[q]) : 0u);
+        const uint32_t top_lo = wave_extreme<true, !SMALL>(ml);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) who[q] = __ballot(hi32(key[q]) == top && lo32(key[q]) == top_lo);
+      }
       bool found = false;
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
-        const unsigned long long who = __ballot(hi32(key[q]) == top && lo32(key[q]) == top_lo);
-        take[q] = !found && who != 0ull && lane == __ffsll(static_cast<long long>(who)) - 1;
-        found = found || who != 0ull;
+        if (!found && who[q] != 0ull) {        // uniform
+          found = true;
+          const int l = __ffsll(static_cast<long long>(who[q])) - 1;
+          s2 -= readlane_f64(key[q] * next[q], l);
+          if (lane == l) {
+            key[q] = next[q];
+            next[q] = third[q];
+            r[q] += 1;
+          }
+          third[q] = w[q] / static_cast<double>(r[q] + 2);
+        }
       }
-      count = 1;
-      double part = 0.0;
-#pragma unroll
-      for (int q = 0; q < Q; ++q) part += w[q] * (take[q] ? next[q] : key[q]);
-      s2 = wave_sum_dpp(part);
-    }
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      if (take[q]) {
-        key[q] = next[q];
-        next[q] = third[q];
-        r[q] += 1;
+      n += 1;
+      extra += 1;
+      if (cv_threshold >= 0.0) {
+        const double lhs = static_cast<double>(n) * s2;
+        more = lhs > surely_over;
+        if (!more && !(lhs < surely_under)) more = cv_exact() > cv_threshold;
       }
-      third[q] = w[q] / static_cast<double>(r[q] + 2);
+      more = more && extra < max_extra;
     }
-    n += count;
-    extra += count;
-    more = true;
-    if (one && cv_threshold >= 0.0) {
-      const double lhs = static_cast<double>(n) * s2;
-      more = lhs > surely_over;
-      if (!more && !(lhs < surely_under)) more = cv_exact() > cv_threshold;
-    }
-    more = more && extra < max_extra;
   }
   const double cv = extra > 0 ? cv_exact() : cv_first;
 #pragma unroll

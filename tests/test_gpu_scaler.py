@@ -406,7 +406,8 @@ def test_place_replicas_after_a_round_of_more_than_2_31_replicas():
     assert np.array_equal(count.cpu().numpy(), want[2]) and int(n_warm.item()) == want[3]
 
 
-@pytest.mark.parametrize("E,total,alpha", [(5, 3000, 1.3), (64, 49152, 1.2), (70, 900, 0.6), (129, 5000, 0.9)])
+@pytest.mark.parametrize("E,total,alpha", [(2, 300, 1.0), (5, 3000, 1.3), (8, 32768, 1.2), (16, 32768, 1.2), (17, 4000, 1.1),
+                                           (64, 49152, 1.2), (70, 900, 0.6), (129, 5000, 0.9)])
 def test_scale_replicas_stops_at_every_step(E, total, alpha):
     # the kernel takes several steps in one round of its loop: budgets and thresholds that end it at each of the first steps
     loads = si.zipf_loads(E, total, alpha, E)
