@@ -1068,28 +1068,32 @@ __global__ __launch_bounds__(512) void ffn_bf16_sum_parts_kernel(GemmArgs p) {
 
 // --------------------------------------------------------------------------------------------
 // fp32 layers.  Blocks of 4 waves; each wave takes all the tile's 16-row sub-tiles against its own 16 weight
-// rows of each matrix, so the waves are equally busy whatever the row count is; segments are cut evenly,
-// so 129 rows are 48 + 32 + 49 and not 64 + 64 + 1.  K step 32 (128-byte rows).  Two ways to multiply:
+// rows of each matrix, so the waves are equally busy whatever the row count is.  Segments are cut as for the
+// bf16 kernels, in pairs of sub-tiles (singly: no difference at 44 to 250 rows per expert).  K step 32
+// (128-byte rows).  Two ways to multiply:
 //
 // f32_split_tile (33 to 64 rows).  The bf16 matrix instruction is 16 times as fast as the fp32 one.  A value
-// is cut into three bf16 pieces, each the rounded rest of the ones before: they hold its 24 bits exactly, and of
-// the nine piece products the six above 2^-24 of the whole are multiplied, smallest first.  A wave's weight rows are
-// nobody else's, so they go from memory to registers in fragment order and are cut there; the activation
-// rows are cut once per block, by the thread that loads them, and shared through three LDS planes.
-// Error against 64-bit sums (2-norm, both GEMMs, four layers of K = 36 to 2048): 1.1e-7 to 7.4e-7, the fp32
-// instruction 1.7e-7 to 8.7e-7 (192 roundings per 1024 products against 256).
-// Bound by the vector instructions of the cutting (149 beside 48 MFMAs per wave and stage) and the matrix
-// pipe, which is busy 40 %: what counts is that one wave cuts while another multiplies, so three or four blocks
-// per CU and few registers (four blocks in a wave of 128 registers spill; two with stage s + 1 cut ahead
-// between the MFMAs of stage s: 5 to 10 % slower; rows of both operands through LDS: 10 %; 128-row tiles
-// 5 % faster at 2000 tokens, 10 % slower at 1000).
+// is cut into three bf16 pieces, each the rounded rest of the ones before: they hold its 24 bits exactly.  All
+// piece products but the smallest (2^-32 of the whole or less) are multiplied.  The matrix instruction does not round its sum
+// to nearest, so the leading products have an accumulator of their own and the seven others, 2^-7 of them and less, another;
+// the two are added by a rounded addition, per stage (gated) or at the end (ungated: there are registers
+// for both).  A wave's weight rows are nobody else's, so they go from memory to registers in fragment order and are cut
+// there; the activation rows are cut once per block, by the thread that loads them, and shared through three LDS planes.
+// Error against 64-bit sums (2-norm, each GEMM by itself, K = 260 to 2048): 1.7e-7 to 4.7e-7, the fp32 instruction 4.4e-7
+// to 1.23e-6.  A sum of one product: within 1.0002 x 2^-24 of it, 0.15 % not the nearest fp32 number (six products in one
+// accumulator: 2.4 x 2^-24 and 19 %).
+// Bound by the matrix pipe and the vector instructions of the cutting, which overlap only between waves:
+// three or four blocks per CU and few registers (four blocks in a wave of 128 registers spill; two with
+// stage s + 1 cut ahead between the MFMAs of stage s: 5 to 10 % slower; rows of both operands through LDS: 10 %;
+// 128-row tiles 5 % faster at 2000 tokens, 10 % slower at 1000).
 //
 // f32_exact_rows (up to 32 rows).  v_mfma_f32_16x16x4_f32.  Few rows wait for their weights, and cutting them
 // would lengthen every stage's chain of load, cut, multiply (60 tokens of the shape below 94 -> 117 us).
 // Two stages for the gated tiles (three: 11 % slower, a block per CU less).
 //
-// (d = 1024, E = 16, k = 2, F = 2048, fp32 instruction alone -> now, us: 1000 tokens, up 153 -> 118, down 96 -> 75, 130 TFLOP/s;
-// whole layer of 2000 tokens 475 -> 375; d = 1280, E = 4, k = 1, F = 2400, 2000 tokens 363 -> 278.)
+// (d = 1024, E = 16, k = 2, F = 2048, fp32 instruction alone -> now, us: 1000 tokens, up 151 -> 140, down 98 -> 87, 115 TFLOP/s;
+// whole layer of 2000 tokens 436 -> 386; d = 1280, E = 4, k = 1, F = 2400, 2000 tokens 331 -> 289.  Six products in one
+// accumulator of unscaled pieces: 121 and 77, 336, 242.)
 // --------------------------------------------------------------------------------------------
 constexpr int F32_NW = 4, F32_BN = 64, F32_BK = 32, F32_BM = 64, F32_EXACT_ROWS = 32;
 constexpr int F32_PROW = F32_BK * 2;              // bytes of a row in a plane
@@ -1115,10 +1119,11 @@ __device__ __forceinline__ F32Operands f32_operands(const GemmArgs& p, const Til
           __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B1), 0, 0x7FFFFFFF, 0x00020000)};
 }
 
-// Accumulator (v, lane) is row lane % 16 of the sub-tile, columns 4 (lane / 16) .. + 3 of the wave's 16.
+// Accumulator (v, lane) is row lane % 16 of the sub-tile, columns 4 (lane / 16) .. + 3 of the wave's 16; it holds
+// 1 / UNIT of the product.
 template <bool GATED, int MI>
 __device__ __forceinline__ void f32_store(const f32x4_t (&acc)[GATED ? 2 : 1][MI], const GemmArgs& p, int n0, int m_first,
-                                          int m_end) {
+                                          int m_end, const float UNIT = 1.f) {
   const int lane = lane_id(), wave = threadIdx.x / MOE_WAVE;
   float* out = static_cast<float*>(p.out);
   const int c = n0 + wave * 16 + 4 * (lane >> 4);
@@ -1135,8 +1140,8 @@ __device__ __forceinline__ void f32_store(const f32x4_t (&acc)[GATED ? 2 : 1][MI
     f32x4_t o;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const float v = acc[0][mi][u];
-      o[u] = GATED ? silu_mul<true>(v, acc[GATED ? 1 : 0][mi][u]) : out_map ? v * scale : v;
+      const float v = acc[0][mi][u] * UNIT;
+      o[u] = GATED ? silu_mul<true>(v, acc[GATED ? 1 : 0][mi][u] * UNIT) : out_map ? v * scale : v;
     }
     *reinterpret_cast<f32x4_t*>(out + static_cast<int64_t>(gr) * p.N + c) = o;
   }
@@ -1238,11 +1243,15 @@ __device__ __forceinline__ void f32_exact_rows(const GemmArgs& p, const TileCoor
   f32_store<GATED, MI>(acc, p, n0, m_first, m_end);
 }
 
+// Values are cut at F32_SCALE times their size: the pieces of every normal fp32 value are then normal bf16 values, and
+// no bit of a product that fp32 can hold falls below the range, whatever else its row holds.  At the upper end
+// a value of 2^104 and more, or products that add up to 2^80, give an infinite piece or sum, and an infinity stays
+// one or turns into a NaN: see f32_split_tile.
+constexpr float F32_SCALE = 0x1p24f, F32_UNSCALE = 0x1p-48f;
+
 // Four values to four bf16 of each of the three planes (exact: 8 + 8 + 8 bits and the signs of the rests).
-// top: largest absolute value seen.
-__device__ __forceinline__ void f32_split(f32x4_t r, uint2 (&q)[3], float& top) {
-  top = fmaxf(fmaxf(top, fabsf(r[0])), fabsf(r[1]));
-  top = fmaxf(fmaxf(top, fabsf(r[2])), fabsf(r[3]));
+__device__ __forceinline__ void f32_split(f32x4_t r, uint2 (&q)[3]) {
+  r *= F32_SCALE;
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     q[i] = make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
@@ -1252,14 +1261,9 @@ __device__ __forceinline__ void f32_split(f32x4_t r, uint2 (&q)[3], float& top) 
 // Chunk swizzle of a 64-byte plane row: 8 rows x the two chunks of an LDS pass cover each bank once.
 __device__ __forceinline__ int swz64(int row) { return (row >> 1) & 2; }
 
-// The pieces of a value below 2^-109 fall out of bf16's range, those of one above its largest finite value are
-// infinite and not a number, and so are their products with others.  A row (of either operand) whose largest
-// value is zero, or lies between these two, is beyond both: what such pieces lose is 2^-59 of the row's
-// products or less, and no sum overflows.
-constexpr float F32_ROW_MIN = 0x1p-50f, F32_ROW_MAX = 0x1p50f;
-__device__ __forceinline__ bool f32_row_ok(float top) { return top == 0.f || (top >= F32_ROW_MIN && top <= F32_ROW_MAX); }
-
-// Returns false, and stores nothing, if a row is outside the range above (block-uniform).
+// Returns false, and stores nothing, if a sum is not finite (block-uniform): the operands may have left the pieces'
+// range, which costs such a tile twice its time and more (2000 tokens of d = 1024, F = 2048 that all hit it in the
+// down-projection: 324 us, 155 if none does, 162 by the fp32 instruction alone).
 template <bool GATED>
 __device__ __forceinline__ bool f32_split_tile(const GemmArgs& p, const TileCoord& tc, unsigned char* lds) {
   constexpr int NMAT = GATED ? 2 : 1, BM = F32_BM;
@@ -1288,7 +1292,6 @@ __device__ __forceinline__ bool f32_split_tile(const GemmArgs& p, const TileCoor
                 static_cast<uint32_t>(kg + 4 * h) * 16u;
   const int tail_chunks = (K & (F32_BK - 1)) >> 2;
   auto past_end = [&](int kt, int c) { return kt >= KT || (tail_chunks != 0 && c >= tail_chunks) ? PAST_END : 0u; };
-  float top_a[NLA] = {}, top_w[NMAT] = {};
   f32x4_t va[NLA], vw[NMAT][2];
   auto load_a = [&](int kt) {
     if (kt >= KT - 1) {                           // uniform
@@ -1317,7 +1320,7 @@ __device__ __forceinline__ bool f32_split_tile(const GemmArgs& p, const TileCoor
 #pragma unroll
     for (int i = 0; i < NLA; ++i) {
       uint2 q[3];
-      f32_split(va[i], q, top_a[i]);
+      f32_split(va[i], q);
 #pragma unroll
       for (int j = 0; j < 3; ++j) *reinterpret_cast<uint2*>(to + i * 32 * F32_PROW + j * F32_PLANE) = q[j];
     }
@@ -1327,18 +1330,21 @@ __device__ __forceinline__ bool f32_split_tile(const GemmArgs& p, const TileCoor
 #pragma unroll
     for (int m = 0; m < NMAT; ++m) {
       uint2 q0[3], q1[3];
-      f32_split(vw[m][0], q0, top_w[m]);
-      f32_split(vw[m][1], q1, top_w[m]);
+      f32_split(vw[m][0], q0);
+      f32_split(vw[m][1], q1);
 #pragma unroll
       for (int j = 0; j < 3; ++j) wf[m][j] = __builtin_bit_cast(bf16x8_t, make_uint4(q0[j].x, q0[j].y, q1[j].x, q1[j].y));
     }
   };
   const int x_base = l16 * F32_PROW + ((kg ^ swz64(l16)) << 4);
-  f32x4_t acc[NMAT][MI];
+  f32x4_t acc[NMAT][MI], rest[GATED ? 1 : MI][NMAT];
 #pragma unroll
   for (int m = 0; m < NMAT; ++m)
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi) acc[m][mi] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int mi = 0; mi < MI; ++mi) {
+      acc[m][mi] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      rest[GATED ? 0 : mi][m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
 
   load_a(0);
   load_w(0);
@@ -1361,12 +1367,23 @@ __device__ __forceinline__ bool f32_split_tile(const GemmArgs& p, const TileCoor
 #pragma unroll
       for (int mi = 0; mi < MIV; ++mi) {
         if (mi + 1 < MIV) read_x(mi + 1);
-        constexpr int WQ[6] = {2, 0, 1, 1, 0, 0}, XQ[6] = {0, 2, 1, 0, 1, 0};
+        f32x4_t (&low)[NMAT] = rest[GATED ? 0 : mi];
+        constexpr int WQ[7] = {2, 1, 2, 0, 1, 1, 0}, XQ[7] = {1, 2, 0, 2, 1, 0, 1};
 #pragma unroll
-        for (int t = 0; t < 6; ++t)
+        for (int t = 0; t < 7; ++t)
 #pragma unroll
           for (int m = 0; m < NMAT; ++m)
-            acc[m][mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[m][WQ[t]], x[mi & 1][XQ[t]], acc[m][mi], 0, 0, 0);
+            low[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[m][WQ[t]], x[mi & 1][XQ[t]], low[m], 0, 0, 0);
+#pragma unroll
+        for (int m = 0; m < NMAT; ++m)
+          acc[m][mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[m][0], x[mi & 1][0], acc[m][mi], 0, 0, 0);
+        if constexpr (GATED) {
+#pragma unroll
+          for (int m = 0; m < NMAT; ++m) {
+            acc[m][mi] += low[m];
+            low[m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+          }
+        }
         if (mi == 0) {
           split_a(buf ^ 1);                       // (last read before the barrier of stage kt - 1)
           load_a(kt + 2);
@@ -1382,22 +1399,19 @@ __device__ __forceinline__ bool f32_split_tile(const GemmArgs& p, const TileCoor
     case 3: k_loop(std::integral_constant<int, 3>{}); break;
     default: k_loop(std::integral_constant<int, 4>{}); break;
   }
-  bool ok = true;
+  if constexpr (!GATED) {
 #pragma unroll
-  for (int i = 0; i < NLA; ++i) {                 // the eight lanes of a row
-    float t = top_a[i];
-#pragma unroll
-    for (int off = 1; off < 8; off <<= 1) t = fmaxf(t, __shfl_xor(t, off));
-    ok = ok && f32_row_ok(t);
+    for (int mi = 0; mi < MI; ++mi) acc[0][mi] += rest[mi][0];
   }
+  bool finite = true;
 #pragma unroll
-  for (int m = 0; m < NMAT; ++m) {                // the four lanes of a weight row
-    float t = fmaxf(top_w[m], __shfl_xor(top_w[m], 16));
-    t = fmaxf(t, __shfl_xor(t, 32));
-    ok = ok && f32_row_ok(t);
-  }
-  if (!__syncthreads_and(ok)) return false;
-  f32_store<GATED, MI>(acc, p, n0, tc.m_begin, tc.m_end);
+  for (int m = 0; m < NMAT; ++m)
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) finite = finite && __builtin_isfinite(acc[m][mi][u]);
+  if (!__syncthreads_and(finite)) return false;
+  f32_store<GATED, MI>(acc, p, n0, tc.m_begin, tc.m_end, F32_UNSCALE);
   return true;
 }
 
@@ -1581,12 +1595,13 @@ static int launch_bf16(GemmArgs a, int64_t A, bool row_split, hipStream_t st) {
                              ffn_bf16_kernel<GATED, false, WNT, false>, once[0], nullptr, once_sum, st);
 }
 
-// 64-row tiles, which take the split path, from F32_SPLIT_ROWS rows per expert on, if there is one for every CU;
-// 32-row tiles below.  (Measured, both GEMMs of d = 1024, E = 16, k = 2, F = 2048 and of d = 1280, E = 24, k = 3,
-// F = 1200, 32-row against 64-row tiles, us: 28 rows per expert 122 / 132 and 137 / 134, 36 rows 137 / 144 and 164 / 142, 44 rows
-// 132 / 123 and 165 / 145, 100 rows 231 / 196 and 267 / 237.  Fewer tiles than CUs: a tile's stages are a serial chain, longer
-// with the cutting: 5 experts of 100 rows, d = F = 300, 29 / 37 us; 8 experts of 52 rows, d = 500, F = 900, 41 / 53.)
-constexpr int F32_SPLIT_ROWS = 40;
+// 64-row tiles, which take the split path, from F32_SPLIT_ROWS rows per expert on, if there are more than 5/4 for every
+// CU; 32-row tiles, on the fp32 instruction, below.  (Measured, 32-row against 64-row tiles, us.  Rows per expert, both
+// GEMMs: d = 1024, E = 40, F = 2048, 26 rows 230 / 242, 32 231 / 232, 36 259 / 230, 44 285 / 265; d = F = 768, E = 64, 36 rows
+// 123 / 102, 64 156 / 155, 200 396 / 370.  Tiles, with few of which a tile's stages are a serial chain, longer with the cutting,
+// each GEMM: 256 tiles 58 / 66 and 153 / 170, 304 66 / 72, 320 58 / 66 and 73 / 60; 340 85 / 80, 352 78 / 68, 384 73 / 68 and
+// 198 / 185.)
+constexpr int F32_SPLIT_ROWS = 36;
 template <bool GATED>
 static int launch_f32(GemmArgs a, int64_t A, hipStream_t st) {
   static LdsOnce once[2], once_sum;
@@ -1594,7 +1609,7 @@ static int launch_f32(GemmArgs a, int64_t A, hipStream_t st) {
   a.bn = F32_BN;
   a.n_tiles = (a.N + F32_BN - 1) / F32_BN;
   const int64_t tiles = (A + F32_BM - 1) / F32_BM * a.n_tiles;
-  if (A / a.E >= F32_SPLIT_ROWS && tiles >= (a.n_cu > 0 ? a.n_cu : 256))
+  if (A / a.E >= F32_SPLIT_ROWS && 4 * tiles > 5 * static_cast<int64_t>(a.n_cu > 0 ? a.n_cu : 256))
     return launch_grouped_gemm(a, F32_BM, A, F32_NW * MOE_WAVE, ffn_f32_lds_bytes(GATED),
                                ffn_f32_kernel<GATED, true>, once[0], nullptr, once_sum, st);
   return launch_grouped_gemm(a, F32_EXACT_ROWS, A, F32_NW * MOE_WAVE, ffn_f32_lds_bytes(GATED),

@@ -752,49 +752,98 @@ def test_grouped_ffn_fp32_split_tiles(d, F):
     assert rel_err(yp, ry) <= 4.0 * (d ** 0.5 + F ** 0.5) * 2.0 ** -24 + 2.0 ** -22
 
 
-@pytest.mark.parametrize("what", ["plain", "tiny", "huge", "inf", "nan", "zero", "weight"])
-def test_grouped_ffn_fp32_split_tiles_with_values_out_of_range(what):
-    # one row of an operand beyond what bf16 pieces represent: its tile takes the fp32 instruction, bit for bit
-    # what 32-row launches give; a row of zeros or with a NaN stays on the split path
-    d, F, rows = 36, 64 * 256 + 4, 64
-    gen = torch.Generator(device="cuda").manual_seed(3)
-    x = torch.randn((rows, d), device="cuda", generator=gen)
-    w1, w3, w2 = (torch.randn(s, device="cuda", generator=gen) for s in ((1, F, d), (1, F, d), (1, d, F)))
+# (exponent of the row's value, of the weights, of further values in the same rows that meet zeros only)
+ONE_TERM = [(0, 0, None), (0, 0, 60), (-115, 20, 30), (20, -115, 40), (-60, -60, None), (-60, -58, 50), (39, 38, None)]
 
-    def run(x):
-        T = x.shape[0]
-        off = torch.tensor([0, T], dtype=torch.int32, device="cuda")
-        h, y = torch.zeros((T, F), device="cuda"), torch.zeros((T, d), device="cuda")
-        B.moe_grouped_ffn_part(B.make_shape(T, d, 1, 1, F, si.F32, 1), x, off, w1, w3, w2, h, y, 1)
-        torch.cuda.synchronize()
-        return h
 
-    ref = run(x)
-    if what == "weight":
-        w3[0, 130] *= 2.0 ** 70                       # third tile of 64 columns
+@pytest.mark.parametrize("ex,ew,big", ONE_TERM)
+@pytest.mark.parametrize("part", [1, 2])
+@pytest.mark.parametrize("at", [1, 70])
+def test_grouped_ffn_fp32_split_tiles_sums_of_one_product(part, at, ex, ew, big):
+    # every sum is one product, so each of the eight piece products (the smallest are 2^-25 of the whole) shows in the
+    # result: the rounded product, within 2^-24 and what the pieces' own sum adds (2^-31).  Values near the lower end of
+    # fp32, also beside values that are far larger.  A missing product of order 2^-25 gives 1.2 x 2^-24 and more.
+    K, N, rows = 100, 64 * 322, 64
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    v = (torch.rand(rows, device="cuda", generator=gen) + 1.0) * 2.0 ** ex
+    w = (torch.rand(N, device="cuda", generator=gen) + 1.0) * 2.0 ** ew
+    a, b = torch.zeros((rows, K), device="cuda"), torch.zeros((N, K), device="cuda")
+    a[:, at], b[:, at] = v, w
+    if big is not None:
+        a[:, 50], b[:, 51] = 2.0 ** big, 2.0 ** big
+    off = torch.tensor([0, rows], dtype=torch.int32, device="cuda")
+    if part == 1:                                     # gate values of 128: silu(128) is 128 in fp32
+        a[:, 0] = 1.0
+        gate = torch.zeros_like(b)
+        gate[:, 0] = 128.0
+        out, other = torch.zeros((rows, N), device="cuda"), torch.zeros((rows, K), device="cuda")
+        B.moe_grouped_ffn_part(B.make_shape(rows, K, 1, 1, N, si.F32, 1), a, off, gate[None], b[None],
+                               torch.zeros((1, K, N), device="cuda"), out, other, 1)
+        out = out / 128.0
     else:
-        x[40] *= {"tiny": 2.0 ** -70, "huge": 2.0 ** 70, "zero": 0.0}.get(what, 1.0)
+        out, other = torch.zeros((rows, N), device="cuda"), torch.zeros((1, K, N), device="cuda")
+        B.moe_grouped_ffn_part(B.make_shape(rows, N, 1, 1, K, si.F32, 1), torch.zeros((rows, N), device="cuda"), off,
+                               torch.zeros((1, K, N), device="cuda"), other, b[None], a, out, 2)
+    torch.cuda.synchronize()
+    want = v.double()[:, None] * w.double()[None]
+    assert float(((out.double() - want).abs() / want).max()) <= 2.0 ** -24 * (1.0 + 2.0 ** -6)
+
+
+@pytest.mark.parametrize("part,K,rows", [(1, 36, 64), (1, 68, 37), (2, 36, 64), (2, 68, 37), (2, 100, 64), (2, 132, 48)])
+@pytest.mark.parametrize("what", ["tiny", "huge", "sum", "inf", "nan", "zero", "weight", "weight_sum"])
+def test_grouped_ffn_fp32_split_tiles_with_values_out_of_range(what, part, K, rows):
+    # one row of an operand beyond what bf16 pieces represent, or sums beyond their range: its tile takes the fp32
+    # instruction, bit for bit what 32-row launches give; small rows and rows of zeros stay on the split path.
+    # Odd and even numbers of K stages, through the fp32 instruction's two and three LDS stages.
+    N, hot = 64 * 321 + 4, rows - 3
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    a = torch.randn((rows, K), device="cuda", generator=gen)
+    b, gate = (torch.randn((N, K), device="cuda", generator=gen) for _ in range(2))
+
+    def run(a):
+        T = a.shape[0]
+        off = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+        out = torch.zeros((T, N), device="cuda")
+        if part == 1:
+            B.moe_grouped_ffn_part(B.make_shape(T, K, 1, 1, N, si.F32, 1), a, off, gate[None], b[None],
+                                   torch.zeros((1, K, N), device="cuda"), out, torch.zeros((T, K), device="cuda"), 1)
+        else:
+            up = torch.zeros((1, K, N), device="cuda")
+            B.moe_grouped_ffn_part(B.make_shape(T, N, 1, 1, K, si.F32, 1), torch.zeros((T, N), device="cuda"), off, up, up,
+                                   b[None], a, out, 2)
+        torch.cuda.synchronize()
+        return out
+
+    ref = run(a)
+    if what == "weight":
+        b[130] *= 2.0 ** 110                          # third tile of 64 columns: an infinite piece
+    elif what == "weight_sum":
+        b[130] *= 2.0 ** 85                           # pieces finite, their sums are not
+    else:
+        a[hot] *= {"tiny": 2.0 ** -50, "huge": 2.0 ** 110, "sum": 2.0 ** 85, "zero": 0.0}.get(what, 1.0)
         if what in ("inf", "nan"):
-            x[40, 5] = float(what)
-    got = run(x)
-    exact = torch.cat([run(x[:32].clone()), run(x[32:].clone())])
-    same = lambda a, b: torch.equal(a.view(torch.int32), b.view(torch.int32))
-    if what in ("tiny", "huge", "inf"):
+            a[hot, 5] = float(what)
+    got = run(a)
+    exact = torch.cat([run(a[:32].clone()), run(a[32:].clone())])
+    same = lambda p, q: torch.equal(p.view(torch.int32), q.view(torch.int32))
+    if what in ("huge", "sum", "inf", "nan"):
         assert same(got, exact)
-    elif what == "weight":
+    elif what in ("weight", "weight_sum"):
         assert same(got[:, 128:192], exact[:, 128:192])
         assert same(got[:, :128], ref[:, :128]) and same(got[:, 192:], ref[:, 192:])
     else:
-        keep = [i for i in range(rows) if i != 40]
+        keep = [i for i in range(rows) if i != hot]
         assert same(got[keep], ref[keep]) and not same(got[keep], exact[keep])
-        if what == "nan":
-            assert bool(torch.isnan(got[40]).all())
         if what == "zero":
-            assert bool((got[40] == 0).all())
+            assert bool((got[hot] == 0).all())
     fine = torch.isfinite(exact)
     assert bool((torch.isfinite(got) == fine).all())
-    scale = exact.where(fine, torch.zeros_like(exact)).abs().amax(dim=1, keepdim=True)
-    assert bool(((got - exact).where(fine, torch.zeros_like(exact)).abs() <= 8.0 * d ** 0.5 * 2.0 ** -24 * scale).all())
+    # (by rows and by columns, one of which holds the scaled values)
+    exact = exact.where(fine, torch.zeros_like(exact)).double()
+    scale = torch.minimum(exact.abs().amax(dim=1, keepdim=True), exact.abs().amax(dim=0, keepdim=True).expand_as(exact))
+    if what == "tiny":                                # (a sum of its own size, in a column of ordinary ones)
+        scale = exact.abs().amax(dim=1, keepdim=True)
+    assert bool(((got.where(fine, torch.zeros_like(got)).double() - exact).abs() <= 8.0 * K ** 0.5 * 2.0 ** -24 * scale).all())
 
 
 @pytest.mark.parametrize("dtype,T,d,F,form", [
