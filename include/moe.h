@@ -145,6 +145,11 @@ int moe_count_and_permute_static(const moe_shape_t* shape, const void* x, const 
  * 128 rows into 2 or 4 pieces along the weight rows, higher ones into 2 to 4 pieces (of 64 rows or
  * more) along their own rows.  An element's sum does not depend on what shares its tile, so the
  * outputs are the same bits whether tiles are cut or not.
+ * fp32 layers: a tile of many rows may be multiplied in exact bf16 pieces of its values instead of by the
+ * fp32 matrix instruction; its error against 64-bit sums is the smaller one.  Which of the two a row takes follows
+ * from the number of rows and experts of the call, from the rows that share its tile, and from whether every sum of
+ * its tile is finite and below 2^80.  A call's results are deterministic, but an fp32 row's last bits may
+ * change with what else is in the batch.
  * Two launches (one per GEMM) on `hip_stream`; the library keeps no stream, event or other state
  * of its own, so calls from several host threads or on several streams are independent, and a
  * stream capture records exactly these launches.
