@@ -1092,8 +1092,8 @@ __global__ __launch_bounds__(512) void ffn_bf16_sum_parts_kernel(GemmArgs p) {
 // Two stages for the gated tiles (three: 11 % slower, a block per CU less).
 //
 // (d = 1024, E = 16, k = 2, F = 2048, fp32 instruction alone -> now, us: 1000 tokens, up 151 -> 140, down 98 -> 87, 115 TFLOP/s;
-// whole layer of 2000 tokens 436 -> 386; d = 1280, E = 4, k = 1, F = 2400, 2000 tokens 331 -> 289.  Six products in one
-// accumulator of unscaled pieces: 121 and 77, 336, 242.)
+// both GEMMs of 2000 tokens 436 -> 387; d = 1280, E = 4, k = 1, F = 2400, 2000 tokens 331 -> 289.  Six products in one
+// accumulator of unscaled pieces: 121 and 77, 335, 242.)
 // --------------------------------------------------------------------------------------------
 constexpr int F32_NW = 4, F32_BN = 64, F32_BK = 32, F32_BM = 64, F32_EXACT_ROWS = 32;
 constexpr int F32_PROW = F32_BK * 2;              // bytes of a row in a plane
