@@ -857,6 +857,37 @@ def test_grouped_ffn_fp32_split_tiles_with_values_out_of_range(what, part, K, ro
     assert bool(((got.where(fine, torch.zeros_like(got)).double() - exact).abs() <= 8.0 * K ** 0.5 * 2.0 ** -24 * scale).all())
 
 
+@pytest.mark.parametrize("part", [1, 2])
+@pytest.mark.parametrize("E,rows,panels,pieces", [(1, 35, 321, False), (1, 36, 321, True), (1, 64, 320, False), (1, 64, 321, True),
+                                                  (3, 36, 161, True), (3, 36, 160, False), (9, 36, 54, True)])
+def test_grouped_ffn_fp32_on_both_sides_of_the_split_rule(part, E, rows, panels, pieces):
+    # 36 rows per expert and more than 5/4 tiles (64-row tiles of all rows x panels of 64 columns) per CU: pieces, else the fp32
+    # instruction.  Which of the two it was shows in the error: the fp32 instruction does not round to nearest and adds four
+    # products at a time, 65 times at K = 260 (2.9e-7 of the 2-norm, gated 4.4e-7), the pieces 32, 9 times (up to 1.7e-7).
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the sizes are for 256 compute units")
+    K, N, T = 260, 64 * panels, E * rows
+    gen = torch.Generator(device="cuda").manual_seed(E + rows)
+    a = torch.randn((T, K), device="cuda", generator=gen)
+    b, gate = (torch.randn((E, N, K), device="cuda", generator=gen) * K ** -0.5 for _ in range(2))
+    off = torch.arange(E + 1, dtype=torch.int32, device="cuda") * rows
+    out = torch.zeros((T, N), device="cuda")
+    if part == 1:
+        B.moe_grouped_ffn_part(B.make_shape(T, K, E, 1, N, si.F32, 1), a, off, gate, b, torch.zeros((E, K, N), device="cuda"),
+                               out, torch.zeros((T, K), device="cuda"), 1)
+    else:
+        up = torch.zeros((E, K, N), device="cuda")
+        B.moe_grouped_ffn_part(B.make_shape(T, N, E, 1, K, si.F32, 1), torch.zeros((T, N), device="cuda"), off, up, up, b, a, out, 2)
+    torch.cuda.synchronize()
+    rows64 = [a[e * rows:(e + 1) * rows].double() for e in range(E)]
+    ref = torch.cat([r @ b[e].double().t().contiguous() for e, r in enumerate(rows64)])
+    if part == 1:
+        g = torch.cat([r @ gate[e].double().t().contiguous() for e, r in enumerate(rows64)])
+        ref = ref * g / (1.0 + torch.exp(-g))
+    err = float((out.double() - ref).norm() / ref.norm())
+    assert err <= 1e-6 and (err <= 2.2e-7) == pieces, err
+
+
 @pytest.mark.parametrize("E,T,k", [(8, 330, 2), (5, 650, 1)])
 def test_grouped_ffn_fp32_split_tiles_through_the_maps(E, T, k):
     # split tiles of many K stages that read x by src_assign and, with one expert per token, store scaled rows of y
